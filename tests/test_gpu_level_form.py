@@ -1,0 +1,54 @@
+"""GPU: complex128 evolutions from |s> in the level form (counts of the cost
+table, a recursion over the occupied levels, one write of the state) against
+the oracle's statevector, at the edges of its pieces: one launch up to n = 15
+and three beyond; levels held 64, 128 and 256 to the wave (synthetic tables
+with that many levels); chunks of 16, 8 and 4 rounds and their remainders;
+angles as kernel arguments up to 112 rounds and from memory beyond; p = 0; a
+cost table at an odd address. Bars: the complex128 ones of the statevector
+tests, 1e-12 on P_sol, the norm and every amplitude, 1e-12 m on E."""
+import numpy as np
+import pytest
+
+from gpu_common import log, need_gpu
+from oracle.evolve import evolve_sv
+from paper_2402_02585_amd import gqaoa as g
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,levels,p,odd", [
+    (3, 3, 1, False), (4, 2, 0, False), (6, 1, 5, True), (8, 64, 16, False), (8, 65, 17, False), (10, 128, 9, False),
+    (11, 129, 5, True), (12, 256, 4, False), (12, 30, 112, False), (12, 30, 113, False), (15, 40, 33, False),
+    (16, 40, 15, False), (16, 255, 3, True), (17, 100, 40, False), (20, 50, 2, False)])
+def test_level_form_matches_statevector_oracle(n, levels, p, odd):
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(600 + 7 * n + levels))
+    m = max(levels - 1, 1)
+    cost = rng.integers(0, levels, 2 ** n).astype(np.uint8)
+    cost[:levels] = np.arange(levels)[:2 ** n]           # every level occupied
+    buf = torch.zeros(2 ** n + 16, dtype=torch.uint8, device="cuda")
+    dev = buf[1:2 ** n + 1] if odd else buf[:2 ** n]
+    dev.copy_(torch.from_numpy(cost))
+    b, gm = rng.uniform(0, 2 * np.pi, p), rng.uniform(0, np.pi, p)
+    target = int(rng.integers(0, levels))
+    log(f"level form n={n} levels={levels} p={p} odd={odd}")
+    for rep in range(2):                                 # the second call finds the first one's scratch
+        psi, ps, en, no = g.gqaoa_evolve(n, m, dev, b, gm, dtype=g.C128, target_level=target)
+    rpsi, rp, re, rn = evolve_sv(n, cost, b, gm, target=target)
+    assert np.abs(ps - rp).max() < 1e-12 and np.abs(no - rn).max() < 1e-12
+    assert np.abs(en - re).max() < 1e-12 * m
+    assert np.abs(psi.cpu().numpy() - rpsi).max() < 1e-12
+    if p:
+        plan = g.EvolvePlan(n, m, dev, p, dtype=g.C128, target_level=target)
+        try:
+            for rep in range(2):
+                plan.psi.fill_(0)
+                got = plan.run(b, gm)
+                assert all(np.array_equal(x, y) for x, y in zip(got, (ps, en, no))), rep
+                assert torch.equal(plan.psi, psi), rep
+                torch.cuda.synchronize()
+        finally:
+            plan.close()
+    absent = m if levels == 1 else None                  # an unoccupied target level
+    if absent is not None:
+        assert g.gqaoa_evolve(n, m, dev, b, gm, dtype=g.C128, target_level=absent)[1].max() == 0.0
