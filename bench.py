@@ -472,6 +472,15 @@ def adjoint_leg(torch, g, inst, reps: int = 2):
     amp_rounds = N * p
 
     def timed(every):
+        # the statevector sweep: from |s> a call takes the level form unless a
+        # form of the passes is asked for
+        os.environ["GQAOA_SV_RESIDENT"] = "0"
+        try:
+            return timed_sweep(every)
+        finally:
+            del os.environ["GQAOA_SV_RESIDENT"]
+
+    def timed_sweep(every):
         ws = torch.empty(g.gqaoa_grad_workspace_bytes(I, n, p, g.C128, every), dtype=torch.uint8, device="cuda")
         out = g.gqaoa_grad_batched(n, [m] * I, costs, betas, gammas, g.C128, None, every, workspace=ws)  # warm-up
         torch.cuda.synchronize()
@@ -502,6 +511,19 @@ def adjoint_leg(torch, g, inst, reps: int = 2):
                          "GBps": fwd_bytes / (fwd_ms / max(fwd_cnt, 1) * 1e-3) / 1e9},
         "mean_psol": float(np.mean(P)),
     }
+    # the default call (level form)
+    ws = torch.empty(g.gqaoa_grad_workspace_bytes(I, n, p, g.C128, ckpt), dtype=torch.uint8, device="cuda")
+    call = lambda: g.gqaoa_grad_batched(n, [m] * I, costs, betas, gammas, g.C128, None, ckpt, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(10 * reps):
+        Pl, dbl, dgl = call()
+    res["level_form"] = {"seconds_per_gradient_batch": (time.perf_counter() - t0) / (10 * reps),
+                         "max_abs_diff_vs_sweep": float(max(np.abs(Pl - P).max(), np.abs(dbl - db).max(),
+                                                            np.abs(dgl - dg).max()))}
+    del ws
+    torch.cuda.empty_cache()
     need = g.gqaoa_grad_workspace_bytes(I, n, p, g.C128, 0)
     free = torch.cuda.mem_get_info()[0]
     if need + (4 << 30) <= free:

@@ -141,6 +141,28 @@ struct LevelAngles {
     double v[2 * ROUNDS];  // beta[p], gamma[p]
 };
 
+// Thread t < 256: the sum of column t of the counting blocks' rows (tmp: 256 words of LDS).
+__device__ __forceinline__ uint64_t sum_rows(const uint32_t *rows, int nrows, uint64_t *tmp) {
+    const int t = threadIdx.x;
+    const uint32_t *r = rows + (t & (kLevels - 1));
+    uint64_t count = 0;
+    int b = t / kLevels;
+    constexpr int U = 16;  // rows in flight per thread: the sum is a few memory latencies long
+    for (; b + (U - 1) * 2 < nrows; b += 2 * U) {
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = r[(size_t)(b + 2 * u) * kLevels];
+#pragma unroll
+        for (int u = 0; u < U; ++u) count += v[u];
+    }
+    for (; b < nrows; b += 2) count += r[(size_t)b * kLevels];
+    if (t >= kLevels) tmp[t - kLevels] = count;
+    __syncthreads();
+    if (t < kLevels) count += tmp[t];
+    return count;
+}
+static_assert(kRunThreads == 2 * kLevels, "two threads per level");
+
 // Compacts the occupied levels (thread t < 256 holds level t's count) into
 // L.w / L.lev in level order; every thread of the block calls this.
 __device__ __forceinline__ void compact_levels(LevelLds &L, uint64_t count, int n, int target) {
@@ -318,21 +340,7 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
         count_levels<kRunThreads>(a.cost, 1ull << a.n, 0, 1, h);
         if (t < kLevels) count = level_total(h, t);
     } else {
-        uint64_t *half = reinterpret_cast<uint64_t *>(smem);
-        const uint32_t *r = a.rows + (t & (kLevels - 1));
-        int b = t / kLevels;
-        constexpr int U = 16;  // rows in flight per thread: the sum is a few memory latencies long
-        for (; b + (U - 1) * 2 < a.nrows; b += 2 * U) {
-            uint32_t v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = r[(size_t)(b + 2 * u) * kLevels];
-#pragma unroll
-            for (int u = 0; u < U; ++u) count += v[u];
-        }
-        for (; b < a.nrows; b += 2) count += r[(size_t)b * kLevels];
-        if (t >= kLevels) half[t - kLevels] = count;
-        __syncthreads();
-        if (t < kLevels) count += half[t];
+        count = sum_rows(a.rows, a.nrows, reinterpret_cast<uint64_t *>(smem));
     }
     compact_levels(L, count, a.n, a.target);  // its barriers also end the counters' use of smem
     const double *beta = INLINE > 1 ? L.ang : a.angles;
@@ -407,6 +415,264 @@ int level_evolve(const LevelEvolve &e, bool captured, hipStream_t st) {
     GQ_LAUNCH_CHECK();
     const unsigned blocks = (unsigned)std::min<uint64_t>(N / (kExpThreads * kExpU), (uint64_t)dev.num_cus * 64);
     hipLaunchKernelGGL(level_expand_kernel, dim3(blocks), dim3(kExpThreads), 0, st, e.cost, table, N, psi);
+    GQ_LAUNCH_CHECK();
+    return GQAOA_OK;
+}
+
+// ---- adjoint gradient -----------------------------------------------------------------
+// The reverse sweep of the adjoint gradient in the level space, one block per
+// instance, split as the rounds above: wave 0 carries the amplitudes, the
+// other waves compute the tables of the next chunk and sum the dgamma terms of
+// the chunk before. Forward: phi_k = e^{-i gamma_k l} psi_{k-1}, S_k = sum_l w_l
+// phi_l, psi_k = phi_k + (e^{-i beta_k} - 1) S_k. Reverse, from lambda_p = Pi_t psi_p:
+//   s = sum_l w_l lambda_l,  mu = lambda + (e^{+i beta_k} - 1) s
+//   dP/dbeta_k  = 2 Re(-i e^{-i beta_k} conj(s) S_k)
+//   dP/dgamma_k = 2 sum_l w_l l Im(conj(mu_l) phi_l)
+//   lambda <- e^{+i gamma_k l} mu.
+// The forward states are not stored: phi_k = psi_k - (e^{-i beta_k} - 1) S_k
+// with the S_k of the forward sweep (kept in the gradient arrays until round
+// k's entries replace them), psi_{k-1} = e^{+i gamma_k l} phi_k. So the serial
+// chain is one pair of wave sums per round in each direction: 0.56 us per round
+// for both (200 instances, p = 100: 56 us, where one wave per instance doing
+// everything by itself took 182 us). 128 registers keep two blocks on a CU
+// (512 instances, p = 100: 260 us a call against 307 us with 168 registers and
+// one block; one wave per instance 374 us; from 2048 instances on the two
+// splits meet, so there is one kernel for all).
+struct LevelGradRun {
+    LevelGrad g;
+    int nrows;
+};
+
+struct GradLds {
+    double2 S[2][16];  // S_k of the chunk in reverse and of the next one
+};
+
+template <int LPL>
+__device__ __forceinline__ void level_grad_rounds(LevelLds &L, GradLds &G, double2 *ph, double *qb, int m, int p,
+                                                  const double *beta, const double *gamma, double *db, double *dg,
+                                                  double *psol) {
+    constexpr int KP = kWave * LPL, R = kChunkStates / KP;  // R = 16, 8, 4 rounds per chunk
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int K = L.K, nchunk = (p + R - 1) / R;
+    double w[LPL], lv[LPL], br[LPL], bi[LPL];
+    bool on[LPL];
+#pragma unroll
+    for (int i = 0; i < LPL; ++i) {
+        const int k = lane + kWave * i;
+        on[i] = k < K;
+        w[i] = on[i] ? L.w[k] : 0.0;
+        lv[i] = on[i] ? (double)L.lev[k] : 0.0;
+        br[i] = on[i] ? 1.0 : 0.0;
+        bi[i] = 0.0;
+    }
+    auto tables = [&](int c, int w0, int nw, bool sums) {
+        const int j0 = c * R, nr = min(R, p - j0);
+        for (int r = w0; r < nr; r += nw)
+#pragma unroll
+            for (int i = 0; i < LPL; ++i)
+                if (on[i]) {
+                    double s, cs;
+                    sincos(gamma[j0 + r] * lv[i], &s, &cs);
+                    const bool in = lv[i] <= (double)m;
+                    ph[((c & 1) * R + r) * KP + lane + kWave * i] = in ? double2{cs, -s} : double2{0.0, 0.0};
+                }
+        if (w0 == nw - 1 && lane < nr) {
+            double s, cs;
+            sincos(beta[j0 + lane], &s, &cs);
+            L.mix[c & 1][lane] = double2{cs - 1.0, -s};
+            if (sums) G.S[c & 1][lane] = double2{db[j0 + lane], dg[j0 + lane]};
+        }
+    };
+    tables(0, wave, kRunWaves, false);
+    __syncthreads();
+    for (int c = 0; c < nchunk; ++c) {
+        if (wave == 0) {
+            const int j0 = c * R, nr = min(R, p - j0);
+            const double2 *e0 = ph + (c & 1) * R * KP + lane;
+            double2 e[LPL], mx = L.mix[c & 1][0];
+#pragma unroll
+            for (int i = 0; i < LPL; ++i) e[i] = on[i] ? e0[kWave * i] : double2{0.0, 0.0};
+            for (int r = 0; r < nr; ++r) {
+                double sr = 0.0, si = 0.0;
+#pragma unroll
+                for (int i = 0; i < LPL; ++i) {
+                    const double nb = e[i].x * br[i] - e[i].y * bi[i];
+                    bi[i] = e[i].x * bi[i] + e[i].y * br[i];
+                    br[i] = nb;
+                    sr += w[i] * br[i];
+                    si += w[i] * bi[i];
+                }
+                const double2 mc = mx;
+                const int rn = min(r + 1, nr - 1);
+#pragma unroll
+                for (int i = 0; i < LPL; ++i) e[i] = on[i] ? e0[rn * KP + kWave * i] : double2{0.0, 0.0};
+                mx = L.mix[c & 1][rn];
+                sr = wave_sum_dpp(sr);
+                si = wave_sum_dpp(si);
+                if (lane == 0) {
+                    db[j0 + r] = sr;
+                    dg[j0 + r] = si;
+                }
+                const double dr = mc.x * sr - mc.y * si, di = mc.x * si + mc.y * sr;
+#pragma unroll
+                for (int i = 0; i < LPL; ++i) {
+                    br[i] += dr;
+                    bi[i] += di;
+                }
+            }
+        } else if (c + 1 < nchunk) {
+            tables(c + 1, wave - 1, kRunWaves - 1, false);
+        }
+        __syncthreads();
+    }
+    // P, lambda_p, and the last chunk's S (its phases and factors are still in place)
+    double lr[LPL], li[LPL];
+    if (wave == 0) {
+        double P = 0.0;
+#pragma unroll
+        for (int i = 0; i < LPL; ++i) {
+            const bool t = lane + kWave * i == L.t_idx;
+            lr[i] = t ? br[i] : 0.0;
+            li[i] = t ? bi[i] : 0.0;
+            P += t ? w[i] * (br[i] * br[i] + bi[i] * bi[i]) : 0.0;
+        }
+        P = wave_sum_dpp(P);
+        if (lane == 0) *psol = P;
+    } else if (wave == 1) {
+        const int j0 = (nchunk - 1) * R;
+        if (lane < p - j0) G.S[(nchunk - 1) & 1][lane] = double2{db[j0 + lane], dg[j0 + lane]};
+    }
+    __syncthreads();
+    for (int c = nchunk - 1; c >= -1; --c) {
+        if (wave == 0) {
+            if (c >= 0) {
+                const int j0 = c * R, nr = min(R, p - j0);
+                const double2 *e0 = ph + (c & 1) * R * KP + lane;
+                double *q0 = qb + (c & 1) * R * kWave + lane;
+                double2 e[LPL], mx = L.mix[c & 1][nr - 1], S = G.S[c & 1][nr - 1];
+#pragma unroll
+                for (int i = 0; i < LPL; ++i) e[i] = on[i] ? e0[(nr - 1) * KP + kWave * i] : double2{0.0, 0.0};
+                for (int r = nr - 1; r >= 0; --r) {
+                    double sr = 0.0, si = 0.0;
+#pragma unroll
+                    for (int i = 0; i < LPL; ++i) {
+                        sr += w[i] * lr[i];
+                        si += w[i] * li[i];
+                    }
+                    const double2 mc = mx, Sc = S;
+                    double2 ec[LPL];
+                    const int rn = max(r - 1, 0);
+#pragma unroll
+                    for (int i = 0; i < LPL; ++i) {
+                        ec[i] = e[i];
+                        e[i] = on[i] ? e0[rn * KP + kWave * i] : double2{0.0, 0.0};
+                    }
+                    mx = L.mix[c & 1][rn];
+                    S = G.S[c & 1][rn];
+                    const double dr = mc.x * Sc.x - mc.y * Sc.y, di = mc.x * Sc.y + mc.y * Sc.x;
+                    sr = wave_sum_dpp(sr);
+                    si = wave_sum_dpp(si);
+                    // (e^{+i beta} - 1) s
+                    const double ur = mc.x * sr + mc.y * si, ui = mc.x * si - mc.y * sr;
+                    double q = 0.0;
+#pragma unroll
+                    for (int i = 0; i < LPL; ++i) {
+                        const double fr = br[i] - dr, fi = bi[i] - di;   // phi
+                        const double ar = lr[i] + ur, ai = li[i] + ui;   // mu
+                        q += w[i] * lv[i] * (ar * fi - ai * fr);
+                        // times e^{+i gamma l} = conj(ec)
+                        br[i] = ec[i].x * fr + ec[i].y * fi;
+                        bi[i] = ec[i].x * fi - ec[i].y * fr;
+                        lr[i] = ec[i].x * ar + ec[i].y * ai;
+                        li[i] = ec[i].x * ai - ec[i].y * ar;
+                    }
+                    q0[r * kWave] = q;
+                    // conj(s) S, times -i e^{-i beta} = (-sin beta, -cos beta)
+                    const double zr = sr * Sc.x + si * Sc.y, zi = sr * Sc.y - si * Sc.x;
+                    if (lane == 0) db[j0 + r] = 2.0 * (mc.y * zr + (mc.x + 1.0) * zi);
+                }
+            }
+        } else {
+            if (c > 0) tables(c - 1, wave - 1, kRunWaves - 1, true);
+            if (c + 1 < nchunk) {
+                const int j0 = (c + 1) * R, nr = min(R, p - j0);
+                for (int r = wave - 1; r < nr; r += kRunWaves - 1) {
+                    const double q = wave_sum_dpp(qb[(((c + 1) & 1) * R + r) * kWave + lane]);
+                    if (lane == 0) dg[j0 + r] = 2.0 * q;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+enum LevelSource { kFromCosts = 0, kFromRows = 1, kCompacted = 2 };
+
+template <int SRC>
+__global__ void __launch_bounds__(kRunThreads, 4) level_grad_kernel(LevelGradRun a) {
+    constexpr size_t kWork = 2 * kChunkStates * sizeof(double2) + 2 * 16 * kWave * sizeof(double);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SRC == kFromCosts ? kCountBytes : kWork];
+    static_assert(kWork <= kCountBytes, "chunk buffers");
+    __shared__ LevelLds L;
+    __shared__ GradLds G;
+    const LevelGrad &g = a.g;
+    const int t = threadIdx.x;
+    int inst = blockIdx.x, p = g.pstride, m = kLevels;
+    if constexpr (SRC == kCompacted) {
+        const HistGradSlot sl = g.slots[blockIdx.x];
+        inst = sl.inst;
+        p = sl.p;
+        for (int k = t; k < sl.K; k += kRunThreads) {
+            L.lev[k] = g.lev[sl.lev_off + k];
+            L.w[k] = g.w[sl.lev_off + k];
+        }
+        if (t == 0) {
+            L.K = sl.K;
+            L.t_idx = sl.t_idx;
+        }
+        __syncthreads();
+    } else {
+        uint64_t count = 0;
+        if constexpr (SRC == kFromCosts) {
+            uint32_t *h = reinterpret_cast<uint32_t *>(smem);
+            count_levels<kRunThreads>(g.cost + ((uint64_t)inst << g.n), 1ull << g.n, 0, 1, h);
+            if (t < kLevels) count = level_total(h, t);
+        } else {
+            count = sum_rows(g.rows + (size_t)inst * a.nrows * kLevels, a.nrows, reinterpret_cast<uint64_t *>(smem));
+        }
+        m = g.m[inst];
+        compact_levels(L, count, g.n, g.target[inst]);
+    }
+    double2 *ph = reinterpret_cast<double2 *>(smem);
+    double *qb = reinterpret_cast<double *>(ph + 2 * kChunkStates);
+    const size_t o = (size_t)inst * g.pstride;
+    double *db = g.dbeta + o, *dg = g.dgamma + o;
+    if (L.K <= kWave) level_grad_rounds<1>(L, G, ph, qb, m, p, g.beta + o, g.gamma + o, db, dg, g.psol + inst);
+    else if (L.K <= 2 * kWave) level_grad_rounds<2>(L, G, ph, qb, m, p, g.beta + o, g.gamma + o, db, dg, g.psol + inst);
+    else level_grad_rounds<4>(L, G, ph, qb, m, p, g.beta + o, g.gamma + o, db, dg, g.psol + inst);
+    for (int r = p + t; r < g.pstride; r += kRunThreads) db[r] = dg[r] = 0.0;  // rounds beyond this instance's p
+}
+
+int level_grad(const LevelGrad &g, hipStream_t st) {
+    LevelGradRun a{g, 0};
+    const dim3 grid(g.num_inst), block(kRunThreads);
+    if (!g.cost) {
+        hipLaunchKernelGGL(level_grad_kernel<kCompacted>, grid, block, 0, st, a);
+    } else if (g.n <= kLevelFusedMaxN) {
+        hipLaunchKernelGGL(level_grad_kernel<kFromCosts>, grid, block, 0, st, a);
+    } else {
+        // counting blocks: two per CU over the batch while each has 16 KiB to read
+        DeviceInfo dev;
+        int s = device_info(&dev);
+        if (s) return s;
+        const uint64_t N = 1ull << g.n;
+        const int want = std::max(1, 2 * dev.num_cus / g.num_inst);
+        a.nrows = (int)std::min<uint64_t>(std::min(want, std::min(g.row_cap, kLevelMaxRows)), N / 16 / kCountThreads);
+        hipLaunchKernelGGL(level_count_kernel, dim3(a.nrows, g.num_inst), dim3(kCountThreads), 0, st, g.cost, N,
+                           g.rows);
+        GQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(level_grad_kernel<kFromRows>, grid, block, 0, st, a);
+    }
     GQ_LAUNCH_CHECK();
     return GQAOA_OK;
 }

@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <complex>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -1200,9 +1201,62 @@ int run_solution_prob(int n, const uint8_t *cost, const void *psi, int dtype, in
     return GQAOA_OK;
 }
 
+// Gradients in the level form: per instance one count of its cost table and
+// the sweep over its levels. The tables go up in one copy and the results come
+// down in one, through the small regions of the workspace (the state slots of
+// the statevector sweep are not touched).
+static int run_grad_level(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int p, const double *beta,
+                          const double *gamma, const int32_t *targets, double *psol, double *dbeta, double *dgamma,
+                          void *ws, hipStream_t st) {
+    const SvLayout L = sv_layout(num_inst, n, p, GQAOA_C128, 0, false);
+    char *w = reinterpret_cast<char *>(ws);
+    const size_t I = (size_t)num_inst, ang = I * p * 8;
+    // angles | targets | m: consecutive regions, one upload
+    std::vector<char> up(L.counter - L.angles + I * 4);
+    memcpy(up.data(), beta, ang);
+    memcpy(up.data() + ang, gamma, ang);
+    memcpy(up.data() + (L.target - L.angles), targets, I * 4);
+    memcpy(up.data() + (L.counter - L.angles), m_of, I * 4);
+    GQ_HIP(hipMemcpyAsync(w + L.angles, up.data(), up.size(), hipMemcpyHostToDevice, st));
+    LevelGrad g{};
+    g.num_inst = num_inst;
+    g.pstride = p;
+    g.n = n;
+    g.cost = cost;
+    g.m = reinterpret_cast<const int32_t *>(w + L.counter);
+    g.target = reinterpret_cast<const int32_t *>(w + L.target);
+    // count rows of 1 KiB: in the partials while each instance gets as many there
+    // as in the phase tables (4 KiB per round and instance), else in those
+    const int in_partials = (int)((L.folded - L.partials) / 1024 / I);
+    const int in_tables = (int)std::min<size_t>(4 * (size_t)p, 1 << 20);
+    g.rows = reinterpret_cast<uint32_t *>(w + (in_partials >= in_tables ? L.partials : L.lut));
+    g.row_cap = std::max(in_partials, in_tables);
+    g.beta = reinterpret_cast<const double *>(w + L.angles);
+    g.gamma = g.beta + I * p;
+    g.psol = reinterpret_cast<double *>(w + L.T);
+    g.dbeta = reinterpret_cast<double *>(w + L.dbeta);
+    g.dgamma = reinterpret_cast<double *>(w + L.dgamma);
+    int s;
+    {
+        ProfScope ps("level_grad", st);
+        if ((s = level_grad(g, st))) return s;
+        ps.end();
+    }
+    std::vector<char> down(L.dgamma - L.T + ang);
+    GQ_HIP(hipMemcpyAsync(down.data(), w + L.T, down.size(), hipMemcpyDeviceToHost, st));
+    GQ_HIP(hipStreamSynchronize(st));
+    if (prof_on()) prof_collect();
+    if (psol) memcpy(psol, down.data(), I * 8);
+    if (dbeta) memcpy(dbeta, down.data() + (L.dbeta - L.T), ang);
+    if (dgamma) memcpy(dgamma, down.data() + (L.dgamma - L.T), ang);
+    return GQAOA_OK;
+}
+
 int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int p,
              const double *beta, const double *gamma, int dtype, const int32_t *targets,
              int ckpt_every, double *psol, double *dbeta, double *dgamma, void *ws, hipStream_t st) {
+    if (level_form(dtype, 1))
+        return run_grad_level(num_inst, n, m_of, cost, p, beta, gamma, targets, psol, dbeta, dgamma, ws, st);
     FwdPlan P;
     std::vector<char> lut;
     std::vector<double> f, b, e;

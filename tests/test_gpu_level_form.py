@@ -5,12 +5,17 @@ and three beyond; levels held 64, 128 and 256 to the wave (synthetic tables
 with that many levels); chunks of 16, 8 and 4 rounds and their remainders;
 angles as kernel arguments up to 112 rounds and from memory beyond; p = 0; a
 cost table at an odd address. Bars: the complex128 ones of the statevector
-tests, 1e-12 on P_sol, the norm and every amplitude, 1e-12 m on E."""
+tests, 1e-12 on P_sol, the norm and every amplitude, 1e-12 m on E.
+
+Gradients in the level form against the oracle's statevector sweep at the same
+edges, batched (each instance its own table, m and target): 1e-12 on P and
+dP/dbeta, 1e-12 m on dP/dgamma."""
 import numpy as np
 import pytest
 
 from gpu_common import log, need_gpu
 from oracle.evolve import evolve_sv
+from oracle.grad import grad_sv
 from paper_2402_02585_amd import gqaoa as g
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +57,26 @@ def test_level_form_matches_statevector_oracle(n, levels, p, odd):
     absent = m if levels == 1 else None                  # an unoccupied target level
     if absent is not None:
         assert g.gqaoa_evolve(n, m, dev, b, gm, dtype=g.C128, target_level=absent)[1].max() == 0.0
+
+
+@pytest.mark.parametrize("n,I,levels,p,odd", [
+    (3, 5, 3, 1, False), (7, 3, 64, 16, True), (7, 2, 65, 17, False), (9, 3, 129, 5, False), (10, 2, 256, 9, False),
+    (12, 4, 30, 33, False), (15, 2, 40, 2, False), (16, 3, 40, 15, False), (16, 2, 200, 5, True), (17, 1, 30, 1, False)])
+def test_level_gradient_matches_statevector_oracle(n, I, levels, p, odd):
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(700 + 7 * n + levels))
+    cost = rng.integers(0, levels, (I, 2 ** n)).astype(np.uint8)
+    cost[:, :levels] = np.arange(levels)[:2 ** n]
+    buf = torch.zeros(I * 2 ** n + 16, dtype=torch.uint8, device="cuda")
+    dev = buf[1:I * 2 ** n + 1] if odd else buf[:I * 2 ** n]
+    dev.copy_(torch.from_numpy(cost.reshape(-1)))
+    ms = np.minimum(levels - 1 + np.arange(I), 255).astype(np.int32)
+    tg = rng.integers(0, levels, I).astype(np.int32)
+    b, gm = rng.uniform(0, 2 * np.pi, (I, p)), rng.uniform(0, np.pi, (I, p))
+    log(f"level gradient n={n} I={I} levels={levels} p={p} odd={odd}")
+    for ckpt in (0, 3):
+        P, db, dg = g.gqaoa_grad_batched(n, ms, dev, b, gm, dtype=g.C128, targets=tg, ckpt_every=ckpt)
+    for i in range(I):
+        rP, rb, rg = grad_sv(n, cost[i], b[i], gm[i], target=int(tg[i]))
+        assert abs(P[i] - rP) < 1e-12 and np.abs(db[i] - rb).max() < 1e-12, i
+        assert np.abs(dg[i] - rg).max() < 1e-12 * levels, i
