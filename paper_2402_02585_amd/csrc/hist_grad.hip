@@ -9,6 +9,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 namespace gqaoa {
@@ -33,8 +35,9 @@ int run_hist_grad(int num_inst, const int32_t *n_host, const int32_t *m_host, co
     // compact the occupied levels
     size_t cap = 0;
     for (int i = 0; i < num_inst; ++i) cap += (size_t)m_host[i] + 1;
-    std::vector<int32_t> lev(cap);
-    std::vector<double> w(cap);
+    const std::unique_ptr<int32_t[]> lev(new (std::nothrow) int32_t[cap]);
+    const std::unique_ptr<double[]> w(new (std::nothrow) double[cap]);
+    if (!lev || !w) return fail(GQAOA_EINVAL, "out of host memory");
     std::vector<HistGradSlot> slots((size_t)num_inst);
     size_t nl = 0;
     for (int i = 0; i < num_inst; ++i) {
@@ -62,18 +65,19 @@ int run_hist_grad(int num_inst, const int32_t *n_host, const int32_t *m_host, co
     const size_t o_db = o_psol + al256(8 * I), o_dg = o_db + al256(ang), o_end = o_dg + ang;
     char *base = reinterpret_cast<char *>(ws);
     const bool packed = o_end <= kPackBytes;
-    std::vector<char> pack(packed ? o_end : 0);
+    const std::unique_ptr<char[]> pack(packed ? new (std::nothrow) char[o_end] : nullptr);
+    if (packed && !pack) return fail(GQAOA_EINVAL, "out of host memory");
     const struct {
         size_t at;
         const void *src;
         size_t bytes;
-    } parts[] = {{0, slots.data(), sizeof(HistGradSlot) * I}, {o_lev, lev.data(), 4 * nl}, {o_w, w.data(), 8 * nl},
+    } parts[] = {{0, slots.data(), sizeof(HistGradSlot) * I}, {o_lev, lev.get(), 4 * nl}, {o_w, w.get(), 8 * nl},
                  {o_beta, beta, ang}, {o_gamma, gamma, ang}};
     for (const auto &q : parts) {
-        if (packed) memcpy(pack.data() + q.at, q.src, q.bytes);
+        if (packed) memcpy(pack.get() + q.at, q.src, q.bytes);
         else if (q.bytes) GQ_HIP(hipMemcpyAsync(base + q.at, q.src, q.bytes, hipMemcpyHostToDevice, st));
     }
-    if (packed) GQ_HIP(hipMemcpyAsync(base, pack.data(), o_psol, hipMemcpyHostToDevice, st));
+    if (packed) GQ_HIP(hipMemcpyAsync(base, pack.get(), o_psol, hipMemcpyHostToDevice, st));
 
     LevelGrad g{};
     g.num_inst = num_inst;
@@ -90,11 +94,11 @@ int run_hist_grad(int num_inst, const int32_t *n_host, const int32_t *m_host, co
     if (s) return s;
 
     if (packed) {
-        GQ_HIP(hipMemcpyAsync(pack.data() + o_psol, base + o_psol, o_end - o_psol, hipMemcpyDeviceToHost, st));
+        GQ_HIP(hipMemcpyAsync(pack.get() + o_psol, base + o_psol, o_end - o_psol, hipMemcpyDeviceToHost, st));
         GQ_HIP(hipStreamSynchronize(st));
-        if (psol) memcpy(psol, pack.data() + o_psol, 8 * I);
-        if (dbeta) memcpy(dbeta, pack.data() + o_db, ang);
-        if (dgamma) memcpy(dgamma, pack.data() + o_dg, ang);
+        if (psol) memcpy(psol, pack.get() + o_psol, 8 * I);
+        if (dbeta) memcpy(dbeta, pack.get() + o_db, ang);
+        if (dgamma) memcpy(dgamma, pack.get() + o_dg, ang);
         return GQAOA_OK;
     }
     if (psol) GQ_HIP(hipMemcpyAsync(psol, g.psol, 8 * I, hipMemcpyDeviceToHost, st));

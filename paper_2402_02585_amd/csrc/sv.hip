@@ -28,6 +28,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -1212,12 +1213,14 @@ static int run_grad_level(int num_inst, int n, const int32_t *m_of, const uint8_
     char *w = reinterpret_cast<char *>(ws);
     const size_t I = (size_t)num_inst, ang = I * p * 8;
     // angles | targets | m: consecutive regions, one upload
-    std::vector<char> up(L.counter - L.angles + I * 4);
-    memcpy(up.data(), beta, ang);
-    memcpy(up.data() + ang, gamma, ang);
-    memcpy(up.data() + (L.target - L.angles), targets, I * 4);
-    memcpy(up.data() + (L.counter - L.angles), m_of, I * 4);
-    GQ_HIP(hipMemcpyAsync(w + L.angles, up.data(), up.size(), hipMemcpyHostToDevice, st));
+    const size_t up_bytes = L.counter - L.angles + I * 4, down_bytes = L.dgamma - L.T + ang;
+    const std::unique_ptr<char[]> up(new (std::nothrow) char[up_bytes]), down(new (std::nothrow) char[down_bytes]);
+    if (!up || !down) return fail(GQAOA_EINVAL, "out of host memory");
+    memcpy(up.get(), beta, ang);
+    memcpy(up.get() + ang, gamma, ang);
+    memcpy(up.get() + (L.target - L.angles), targets, I * 4);
+    memcpy(up.get() + (L.counter - L.angles), m_of, I * 4);
+    GQ_HIP(hipMemcpyAsync(w + L.angles, up.get(), up_bytes, hipMemcpyHostToDevice, st));
     LevelGrad g{};
     g.num_inst = num_inst;
     g.pstride = p;
@@ -1242,13 +1245,12 @@ static int run_grad_level(int num_inst, int n, const int32_t *m_of, const uint8_
         if ((s = level_grad(g, st))) return s;
         ps.end();
     }
-    std::vector<char> down(L.dgamma - L.T + ang);
-    GQ_HIP(hipMemcpyAsync(down.data(), w + L.T, down.size(), hipMemcpyDeviceToHost, st));
+    GQ_HIP(hipMemcpyAsync(down.get(), w + L.T, down_bytes, hipMemcpyDeviceToHost, st));
     GQ_HIP(hipStreamSynchronize(st));
     if (prof_on()) prof_collect();
-    if (psol) memcpy(psol, down.data(), I * 8);
-    if (dbeta) memcpy(dbeta, down.data() + (L.dbeta - L.T), ang);
-    if (dgamma) memcpy(dgamma, down.data() + (L.dgamma - L.T), ang);
+    if (psol) memcpy(psol, down.get(), I * 8);
+    if (dbeta) memcpy(dbeta, down.get() + (L.dbeta - L.T), ang);
+    if (dgamma) memcpy(dgamma, down.get() + (L.dgamma - L.T), ang);
     return GQAOA_OK;
 }
 
