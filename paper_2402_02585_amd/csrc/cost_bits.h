@@ -8,12 +8,18 @@
 // the byte-packed costs of z = 32w + 4r .. 32w + 4r + 3, ready to store.
 //
 // Within a wave of 64 lanes, lane l handles word 64*W + l, so z bits 5..10
-// are the lane index and z bits >= 11 are the same for the whole wave.
-// A clause's unsatisfied-mask on a word is
+// are the lane index and z bits >= 11, the tile index W, are the same for the
+// whole wave. A clause's unsatisfied-mask on a word is
 //     P  (the AND of the false-masks of its literals on bits 0..4)
 //   & L[lane]   (its literals on bits 5..10 are all false for this lane)
-//   & H(wave)   (its literals on bits >= 11 are all false for this wave).
-// P and L depend only on the clause and are packed once on the host.
+//   & H(tile)   (its literals on bits >= 11 are all false for this tile).
+// P and L depend only on the clause and are packed once.
+//
+// Clauses are kept in four classes by what their mask depends on inside a
+// tile: A, word bit and lane (literals on bits 0..4 and on 5..10); B, word bit
+// alone; C, lane alone; D, neither. The sums over B, C and D are the same for
+// every lane, for every word bit, or for both, so they need not be formed 64
+// lanes wide in every tile.
 #pragma once
 
 #include <cstdint>
@@ -29,19 +35,17 @@ constexpr int kLowBits = 5;    // z bits inside a word
 constexpr int kLaneBits = 6;   // z bits across the 64 lanes of a wave
 constexpr int kHighBit0 = kLowBits + kLaneBits;  // first wave-uniform bit (11)
 constexpr int kGroup = 16;     // clauses per carry-save-adder block
+constexpr int kHalfGroup = 8;
 
-struct alignas(32) ClauseRec {
+struct alignas(8) ClauseRec {
     uint32_t P;       // false-mask over the 32 word bits of the low literals
+    uint32_t hv;      // variables >= 11 of the clause (bit v - 11)
+    uint32_t hn;      // their neg flags (bit v - 11)
     uint32_t pad;
     uint64_t L;       // bit l set iff the literals on bits 5..10 are false in lane l
-    uint64_t hivar;   // variables >= 11 of the clause (bit v)
-    uint64_t hineg;   // their neg flags (bit v)
 };
 
-struct alignas(16) UniformRec {  // clause with all variables >= 11
-    uint64_t hivar;
-    uint64_t hineg;
-};
+enum ClauseClass { kClassA = 0, kClassB = 1, kClassC = 2, kClassD = 3, kClasses = 4 };
 
 // z offset (bits 0..4) held by word bit j.
 GQ_HD uint32_t word_bit_to_zlow(int j) { return 4u * (uint32_t)(j & 7) + (uint32_t)(j >> 3); }
@@ -62,35 +66,48 @@ constexpr uint64_t kLaneBitPattern[kLaneBits] = {
     0xAAAAAAAAAAAAAAAAull, 0xCCCCCCCCCCCCCCCCull, 0xF0F0F0F0F0F0F0F0ull,
     0xFF00FF00FF00FF00ull, 0xFFFF0000FFFF0000ull, 0xFFFFFFFF00000000ull};
 
-// Record of one clause (validated literals: lit = 2*var + neg, distinct vars).
-// Sets *uniform when every variable sits at z bits >= 11.
-GQ_HD ClauseRec make_record(int32_t l0, int32_t l1, int32_t l2, bool *uniform) {
-    ClauseRec r{0xFFFFFFFFu, 0u, ~0ull, 0ull, 0ull};
-    bool uni = true;
+// Record of one clause (validated literals: lit = 2*var + neg, distinct vars)
+// and its class.
+GQ_HD ClauseRec make_record(int32_t l0, int32_t l1, int32_t l2, int *cls) {
+    ClauseRec r{0xFFFFFFFFu, 0u, 0u, 0u, ~0ull};
+    bool low = false, lane = false;
     const int32_t lits[3] = {l0, l1, l2};
     for (int j = 0; j < 3; ++j) {
         const int v = lits[j] >> 1, neg = lits[j] & 1;
         if (v < kLowBits) {
             const uint32_t pat = kLowVarPattern[v];
             r.P &= neg ? pat : ~pat;     // false iff bit v == neg
-            uni = false;
+            low = true;
         } else if (v < kHighBit0) {
             const uint64_t ones = kLaneBitPattern[v - kLowBits];
             r.L &= neg ? ones : ~ones;   // false iff the lane's bit equals neg
-            uni = false;
+            lane = true;
         } else {
-            r.hivar |= 1ull << v;
-            r.hineg |= (uint64_t)neg << v;
+            r.hv |= 1u << (v - kHighBit0);
+            r.hn |= (uint32_t)neg << (v - kHighBit0);
         }
     }
-    if (uniform) *uniform = uni;
+    *cls = low ? (lane ? kClassA : kClassB) : (lane ? kClassC : kClassD);
     return r;
 }
 
-// A clause is active for a wave when its high literals are all false there.
-GQ_HD bool high_literals_false(uint64_t zwave, uint64_t hivar, uint64_t hineg) {
-    return ((zwave ^ hineg) & hivar) == 0;
+// A clause is active in a tile when its high literals are all false there.
+GQ_HD bool high_literals_false(uint32_t tile, uint32_t hv, uint32_t hn) { return ((tile ^ hn) & hv) == 0; }
+
+// Records per class of one instance, in class order, B and C padded to
+// kHalfGroup with empty records (P = L = 0: never part of a sum).
+struct ClauseCounts {
+    int n[kClasses];     // clauses
+    int first[kClasses]; // first record of the class
+};
+
+GQ_HD ClauseCounts clause_layout(int nA, int nB, int nC, int nD) {
+    ClauseCounts c{{nA, nB, nC, nD}, {0, nA, 0, 0}};
+    c.first[kClassC] = nA + (nB + kHalfGroup - 1) / kHalfGroup * kHalfGroup;
+    c.first[kClassD] = c.first[kClassC] + (nC + kHalfGroup - 1) / kHalfGroup * kHalfGroup;
+    return c;
 }
+constexpr int kMaxRecs = 272;  // 255 clauses and the padding of two classes
 
 // Carry-save adder: a + b + c = 2*hi + lo, bitwise. On the device each output
 // is one v_bitop3_b32 (truth tables 0x96 = three-input XOR, 0xE8 = majority).
@@ -137,6 +154,23 @@ struct SlicedCounter {
             c = t;
         }
     }
+    // Add 8 one-bit inputs per word bit.
+    GQ_HD void add8(const uint32_t (&f)[kHalfGroup]) {
+        uint32_t twosA, twosB, foursA, foursB, eights;
+        csa(twosA, p[0], p[0], f[0], f[1]);
+        csa(twosB, p[0], p[0], f[2], f[3]);
+        csa(foursA, p[1], p[1], twosA, twosB);
+        csa(twosA, p[0], p[0], f[4], f[5]);
+        csa(twosB, p[0], p[0], f[6], f[7]);
+        csa(foursB, p[1], p[1], twosA, twosB);
+        csa(eights, p[2], p[2], foursA, foursB);
+        uint32_t c = eights;
+        for (int b = 3; b < 8; ++b) {  // counts never exceed 255
+            const uint32_t t = p[b] & c;
+            p[b] ^= c;
+            c = t;
+        }
+    }
     // Add the same value u (< 256) to every word bit's count, bit-sliced:
     // plane b gets p_b ^ u_b ^ carry and the carry becomes maj(p_b, u_b, carry).
     GQ_HD void add_scalar(uint32_t u) {
@@ -172,37 +206,23 @@ struct SlicedCounter {
 
 }  // namespace gqaoa
 
-#include <vector>
-
 namespace gqaoa {
 
-// Pack validated clauses (lit = 2*var + neg, 3 distinct vars) into the records
-// above. Clauses with all three variables at bits >= 11 go to `uni`; the rest
-// go to `vec`, padded with empty records to a multiple of kGroup. Fixed-capacity
-// form: for m clauses vec needs room for m rounded up to kGroup records, uni for m.
-inline void pack_clauses(int m, const int32_t *lits, ClauseRec *vec, int *nvec, UniformRec *uni, int *nuni) {
-    int nv = 0, nu = 0;
+// Pack validated clauses (lit = 2*var + neg, 3 distinct vars) into rec
+// [kMaxRecs], by class.
+inline ClauseCounts pack_clauses(int m, const int32_t *lits, ClauseRec *rec) {
+    ClauseRec r[255];
+    int cls[255], n[kClasses] = {0, 0, 0, 0};
     for (int i = 0; i < m; ++i) {
-        bool uniform = false;
-        const ClauseRec r = make_record(lits[3 * i], lits[3 * i + 1], lits[3 * i + 2], &uniform);
-        if (uniform)
-            uni[nu++] = UniformRec{r.hivar, r.hineg};
-        else
-            vec[nv++] = r;
+        r[i] = make_record(lits[3 * i], lits[3 * i + 1], lits[3 * i + 2], &cls[i]);
+        ++n[cls[i]];
     }
-    while (nv % kGroup) vec[nv++] = ClauseRec{0u, 0u, 0ull, 0ull, 0ull};
-    *nvec = nv;
-    *nuni = nu;
-}
-
-inline void pack_clauses(int m, const int32_t *lits, std::vector<ClauseRec> &vec,
-                         std::vector<UniformRec> &uni) {
-    vec.resize((size_t)(m + kGroup - 1) / kGroup * kGroup);
-    uni.resize((size_t)m);
-    int nv = 0, nu = 0;
-    pack_clauses(m, lits, vec.data(), &nv, uni.data(), &nu);
-    vec.resize((size_t)nv);
-    uni.resize((size_t)nu);
+    const ClauseCounts c = clause_layout(n[0], n[1], n[2], n[3]);
+    for (int i = 0; i < kMaxRecs; ++i) rec[i] = ClauseRec{0u, 0u, 0u, 0u, 0ull};
+    int at[kClasses];
+    for (int k = 0; k < kClasses; ++k) at[k] = c.first[k];
+    for (int i = 0; i < m; ++i) rec[at[cls[i]]++] = r[i];
+    return c;
 }
 
 }  // namespace gqaoa

@@ -5,16 +5,17 @@
 // N_k = #{z : C(z) = k} is the per-level state count of App. C. The word
 // layout and clause records are described in cost_bits.h.
 //
-// Each lane evaluates one 32-assignment word per loop trip. Per wave tile the
-// lanes first test the wave-uniform (high) literals of 64 clauses at a time and
-// leave each clause's effective lane mask in wave-private LDS; then, per
-// clause, one LDS broadcast read and a sign-extended bit extract select the
-// low-literal pattern P for this lane, and a carry-save adder tree folds 16
-// clauses at a time into eight bit-planes; 8x8 bit transposes turn the planes
-// into byte costs. Clauses whose variables all sit in wave-uniform bits add a
-// count found by a ballot.
-// The histogram is tallied in LDS (one copy per wave) and written as per-block
-// rows, which a second kernel sums in a fixed order.
+// Each lane evaluates one 32-assignment word per tile. The clauses whose mask
+// varies over word bits and lanes (class A) are tested against the tile's high
+// bits 64 at a time; the active ones are compacted into wave-private LDS and
+// folded, 16 at a time, into bit planes by a carry-save adder tree (one LDS
+// broadcast, a bit extract and an AND per clause). The other classes' sums are
+// the same along lanes or word bits: a wave forms them for up to 64 tiles at
+// once, one tile per lane, and each tile reads its own back as scalars (the
+// starting planes of the adder tree, and lane masks added at its end).
+// Three 8x8 bit transposes turn the planes into byte costs. The histogram is
+// counted from the planes and written as per-block rows, which a second kernel
+// sums in a fixed order.
 #include "internal.h"
 #include "cost_bits.h"
 
@@ -29,7 +30,6 @@ namespace gqaoa {
 
 constexpr int kCostThreads = 256;
 constexpr int kCostWaves = kCostThreads / kWave;
-constexpr int kMaxVec = 256;  // padded clause records per instance (m <= 255)
 // LDS histogram copies per block: four per wave (by lane & 3). Copies are
 // kHistStride = 257 words apart, so one level in different copies falls in
 // different LDS banks: lanes of different copies tallying the same level
@@ -37,74 +37,141 @@ constexpr int kMaxVec = 256;  // padded clause records per instance (m <= 255)
 constexpr int kHistCopies = kCostWaves * 4;
 constexpr int kHistStride = 257;
 
-// A clause's effective masks for one wave-tile, as each half-wave reads them:
-// entry [c][h] = {P, bits 32h..32h+31 of L_eff} with L_eff = L if the clause's
-// high literals are all false in this tile, else 0.
+// A clause's masks as each half-wave reads them: entry [c][h] = {P, bits
+// 32h..32h+31 of L}.
 struct EffEntry {
     uint32_t P, Lhalf;
 };
 
-// Dynamic LDS of a cost block, sized by the padded clause count nvec:
-// clause records [nvec], per-wave effective masks [waves][nvec][2], and the
-// histogram copies [copies][kHistStride].
+// Dynamic LDS of a cost block: clause records, per-wave entries of the active
+// clauses [waves][neff][2], and the histogram copies [copies][kHistStride].
 struct CostLds {
-    ClauseRec *rec;
     EffEntry *eff;
+    ClauseRec *rec;
     uint32_t *hist;
-    __device__ CostLds(unsigned char *smem, int nvec)
-        : rec(reinterpret_cast<ClauseRec *>(smem)),
-          eff(reinterpret_cast<EffEntry *>(smem + sizeof(ClauseRec) * nvec)),
-          hist(reinterpret_cast<uint32_t *>(smem + sizeof(ClauseRec) * nvec +
-                                            sizeof(EffEntry) * 2 * kCostWaves * nvec)) {}
-    __device__ EffEntry (*wave_eff(int nvec))[2] {
-        return reinterpret_cast<EffEntry(*)[2]>(eff + (size_t)2 * nvec * (threadIdx.x / kWave));
+    __device__ CostLds(unsigned char *smem, int neff)
+        : eff(reinterpret_cast<EffEntry *>(smem)),
+          rec(reinterpret_cast<ClauseRec *>(smem + sizeof(EffEntry) * 2 * kCostWaves * neff)),
+          hist(reinterpret_cast<uint32_t *>(smem + sizeof(EffEntry) * 2 * kCostWaves * neff +
+                                            sizeof(ClauseRec) * kMaxRecs)) {}
+    __device__ EffEntry (*wave_eff(int neff))[2] {
+        return reinterpret_cast<EffEntry(*)[2]>(eff + (size_t)2 * neff * (threadIdx.x / kWave));
     }
 };
 
-size_t cost_lds_bytes(int nvec) {
-    return sizeof(ClauseRec) * nvec + sizeof(EffEntry) * 2 * kCostWaves * nvec +
-           sizeof(uint32_t) * kHistCopies * kHistStride;
-}
+// Entries a wave may hold: every clause of the classes it evaluates per tile.
+static inline int eff_entries(int m) { return (m + kHalfGroup - 1) / kHalfGroup * kHalfGroup; }
 
-// Zero the histogram copies and stage the clause records in LDS.
-__device__ __forceinline__ void stage(CostLds &s, const ClauseRec *__restrict__ vec, int nvec) {
-    for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kCostThreads) s.hist[i] = 0;
-    for (int i = threadIdx.x; i < nvec; i += kCostThreads) s.rec[i] = vec[i];
-    __syncthreads();
+size_t cost_lds_bytes(int m) {
+    return sizeof(EffEntry) * 2 * kCostWaves * eff_entries(m) + sizeof(ClauseRec) * kMaxRecs +
+           sizeof(uint32_t) * kHistCopies * kHistStride;
 }
 
 __device__ __forceinline__ uint32_t *hist_copy(CostLds &s) {
     return s.hist + ((threadIdx.x / kWave) * 4 + (threadIdx.x & 3)) * kHistStride;
 }
 
-// Costs of the 32 assignments of word w = tile*64 + lane as bit planes: bit j
-// of v[b] is bit b of C(z) for the assignment at word bit j. Every lane of the
-// wave must call this with the same tile.
-__device__ __forceinline__ void eval_planes(const ClauseRec *vec, int nvec, const UniformRec *uni, int nuni,
-                                            uint64_t tile, EffEntry (*eff)[2], uint32_t (&v)[8]) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t zwave = (tile * kWave) << kLowBits;   // z of lane 0, bit 0
-    // 1) high-literal test of 64 clauses at a time, one per lane
-    for (int c = lane; c < nvec; c += kWave) {
-        const ClauseRec r = vec[c];
-        const uint64_t L = high_literals_false(zwave, r.hivar, r.hineg) ? r.L : 0ull;
-        eff[c][0] = EffEntry{r.P, (uint32_t)L};
-        eff[c][1] = EffEntry{r.P, (uint32_t)(L >> 32)};
+// Sums of classes B, C and D for up to 64 tiles, lane t holding tile tile0 + t:
+// b: bit planes over the word bits of B's sum plus D's count; c[0], c[1]: bit
+// planes over lanes 0..31 and 32..63 of C's sum.
+struct TileSums {
+    uint32_t b[8], c[2][8];
+};
+
+__device__ __forceinline__ void tile_sums(const ClauseRec *rec, const ClauseCounts &n, uint32_t tile0, TileSums &s) {
+    const uint32_t tile = tile0 + (threadIdx.x & (kWave - 1));
+    SlicedCounter sb;
+    sb.clear();
+    for (int g = 0; g < n.n[kClassB]; g += kHalfGroup) {
+        uint32_t f[kHalfGroup];
+#pragma unroll
+        for (int i = 0; i < kHalfGroup; ++i) {
+            const ClauseRec &r = rec[n.first[kClassB] + g + i];
+            f[i] = high_literals_false(tile, r.hv, r.hn) ? r.P : 0u;
+        }
+        sb.add8(f);
     }
     uint32_t u = 0;
-    for (int c0 = 0; c0 < nuni; c0 += kWave) {
+    for (int g = 0; g < n.n[kClassD]; ++g) {
+        const ClauseRec &r = rec[n.first[kClassD] + g];
+        u += high_literals_false(tile, r.hv, r.hn) ? 1u : 0u;
+    }
+    sb.add_scalar(u);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) s.b[b] = sb.p[b];
+    SlicedCounter lo, hi;
+    lo.clear();
+    hi.clear();
+    for (int g = 0; g < n.n[kClassC]; g += kHalfGroup) {
+        uint32_t fl[kHalfGroup], fh[kHalfGroup];
+#pragma unroll
+        for (int i = 0; i < kHalfGroup; ++i) {
+            const ClauseRec &r = rec[n.first[kClassC] + g + i];
+            const uint64_t L = high_literals_false(tile, r.hv, r.hn) ? r.L : 0ull;
+            fl[i] = (uint32_t)L;
+            fh[i] = (uint32_t)(L >> 32);
+        }
+        lo.add8(fl);
+        hi.add8(fh);
+    }
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        s.c[0][b] = lo.p[b];
+        s.c[1][b] = hi.p[b];
+    }
+}
+
+// Costs of the 32 assignments of word w = tile*64 + lane as bit planes: bit j
+// of v[b] is bit b of C(z) for the assignment at word bit j. Every lane of the
+// wave must call this with the same tile. SUMS: the sums of classes B, C and D
+// come from s (lane `slot`); otherwise their clauses are evaluated with class
+// A's (they follow it in rec).
+template <bool SUMS>
+__device__ __forceinline__ void eval_planes(const ClauseRec *rec, const ClauseCounts &n, uint32_t tile,
+                                            const TileSums &s, int slot, EffEntry (*eff)[2], uint32_t (&v)[8]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int ncand = SUMS ? n.n[kClassA] : n.first[kClassD];
+    // 1) the active clauses, compacted
+    int active = 0;
+    for (int c0 = 0; c0 < ncand; c0 += kWave) {
         const int c = c0 + lane;
-        const bool f = c < nuni && high_literals_false(zwave, uni[c].hivar, uni[c].hineg);
-        u += (uint32_t)__popcll(__ballot(f));
+        ClauseRec r{0u, 0u, 0u, 0u, 0ull};
+        if (c < ncand) r = rec[c];
+        const bool on = r.P != 0u && r.L != 0ull && high_literals_false(tile, r.hv, r.hn);
+        const uint64_t mask = __ballot(on);
+        if (on) {
+            const int at = active + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            eff[at][0] = EffEntry{r.P, (uint32_t)r.L};
+            eff[at][1] = EffEntry{r.P, (uint32_t)(r.L >> 32)};
+        }
+        active += __popcll(mask);
+    }
+    const int padded = (active + kHalfGroup - 1) & ~(kHalfGroup - 1);
+    if (lane < padded - active) {
+        eff[active + lane][0] = EffEntry{0u, 0u};
+        eff[active + lane][1] = EffEntry{0u, 0u};
+    }
+    SlicedCounter cnt;
+    uint32_t u = 0;
+    if constexpr (SUMS) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) cnt.p[b] = __builtin_amdgcn_readlane(s.b[b], slot);
+    } else {
+        cnt.clear();
+        for (int c0 = 0; c0 < n.n[kClassD]; c0 += kWave) {
+            const int c = n.first[kClassD] + c0 + lane;
+            const bool f = c0 + lane < n.n[kClassD] && high_literals_false(tile, rec[c].hv, rec[c].hn);
+            u += (uint32_t)__popcll(__ballot(f));
+        }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // 2) per clause: the lane's bit of L_eff selects P; 16 clauses per adder tree
+    // 2) per active clause: the lane's bit of L selects P; 16 (then 8) clauses per adder tree
     const int half = lane >> 5, bit = lane & 31;
-    SlicedCounter cnt;
-    cnt.clear();
-    for (int g = 0; g < nvec; g += kGroup) {
+    int g = 0;
+    for (; g + kGroup <= padded; g += kGroup) {
         uint32_t f[kGroup];
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
@@ -113,9 +180,32 @@ __device__ __forceinline__ void eval_planes(const ClauseRec *vec, int nvec, cons
         }
         cnt.add16(f);
     }
-    cnt.add_scalar(u);  // no overflow: every count <= m <= 255
+    if (g < padded) {
+        uint32_t f[kHalfGroup];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) v[b] = cnt.p[b];
+        for (int i = 0; i < kHalfGroup; ++i) {
+            const EffEntry e = eff[g + i][half];
+            f[i] = e.P & (uint32_t)__builtin_amdgcn_sbfe((int)e.Lhalf, bit, 1);
+        }
+        cnt.add8(f);
+    }
+    // 3) no overflow: every count <= m <= 255
+    if constexpr (SUMS) {
+        uint32_t carry = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint64_t lanes = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(s.c[1][b], slot) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readlane(s.c[0][b], slot);
+            const uint32_t add = __builtin_amdgcn_inverse_ballot_w64(lanes) ? 0xFFFFFFFFu : 0u;
+            uint32_t c;
+            csa(c, v[b], cnt.p[b], add, carry);
+            carry = c;
+        }
+    } else {
+        cnt.add_scalar(u);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) v[b] = cnt.p[b];
+    }
     // the next tile rewrites eff: every lane's reads of this one come first
     __builtin_amdgcn_wave_barrier();
 }
@@ -206,42 +296,62 @@ __device__ __forceinline__ void tally_word(uint32_t *h, const uint32_t (&t)[8], 
     }
 }
 
-template <int NB>
-__global__ void __launch_bounds__(kCostThreads)
-cost_table_kernel(const ClauseRec *__restrict__ vec, int nvec, const UniformRec *__restrict__ uni,
-                  int nuni, int n, uint8_t *__restrict__ cost, uint32_t *__restrict__ block_hist,
-                  int hist_len, int win_a0) {
-    extern __shared__ unsigned char smem[];
-    CostLds lds(smem, nvec);
-    stage(lds, vec, nvec);
-    uint32_t *h = hist_copy(lds);
-    EffEntry(*eff)[2] = lds.wave_eff(nvec);
-    const uint64_t N = 1ull << n;
-    const uint64_t nwords = n >= kLowBits ? (N >> kLowBits) : 1;
-    const uint64_t ntiles = (nwords + kWave - 1) / kWave;
-    const uint64_t nwaves = (uint64_t)gridDim.x * kCostWaves;
+// Tiles tile0 .. tile0 + ntiles of one instance by one wave: cost bytes to
+// `cost` (when not null), levels to win and, outside its window, to h.
+template <int NB, bool SUMS>
+__device__ __forceinline__ void wave_tiles(const ClauseRec *rec, const ClauseCounts &n, EffEntry (*eff)[2],
+                                           uint32_t tile0, uint32_t ntiles, int nvars, uint8_t *cost,
+                                           LevelWindow<NB> &win, uint32_t *h) {
     const int lane = threadIdx.x & (kWave - 1);
-    LevelWindow<NB> win;
-    win.clear(win_a0);
-    for (uint64_t tile = (uint64_t)blockIdx.x * kCostWaves + threadIdx.x / kWave; tile < ntiles; tile += nwaves) {
+    const uint64_t nwords = nvars >= kLowBits ? (1ull << (nvars - kLowBits)) : 1;
+    TileSums s;
+    if constexpr (SUMS) tile_sums(rec, n, tile0, s);
+    for (uint32_t t0 = 0; t0 < ntiles; ++t0) {
+        const uint32_t tile = tile0 + t0;
         uint32_t v[8], t[8];
-        eval_planes(lds.rec, nvec, uni, nuni, tile, eff, v);
-        const uint64_t w = tile * kWave + lane;
+        eval_planes<SUMS>(rec, n, tile, s, (int)t0, eff, v);
+        const uint64_t w = (uint64_t)tile * kWave + lane;
         if (w >= nwords) continue;
-        if (n >= kLowBits) {
+        if (nvars >= kLowBits) {
             const uint32_t outside = win.add(v);
-            planes_to_bytes(v, t);
-            typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-            u32x4 *dst = reinterpret_cast<u32x4 *>(cost + (w << kLowBits));
-            dst[0] = u32x4{t[0], t[1], t[2], t[3]};
-            dst[1] = u32x4{t[4], t[5], t[6], t[7]};
+            if (outside || cost) planes_to_bytes(v, t);
+            if (cost) {
+                typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+                u32x4 *dst = reinterpret_cast<u32x4 *>(cost + (w << kLowBits));
+                dst[0] = u32x4{t[0], t[1], t[2], t[3]};
+                dst[1] = u32x4{t[4], t[5], t[6], t[7]};
+            }
             if (outside) tally_bits(h, t, outside);
         } else {
+            const uint32_t N = 1u << nvars;
             planes_to_bytes(v, t);
-            for (uint32_t z = 0; z < (uint32_t)N; ++z) cost[z] = (uint8_t)((t[z >> 2] >> (8 * (z & 3))) & 0xFFu);
-            tally_word(h, t, (uint32_t)N);
+            if (cost)
+                for (uint32_t z = 0; z < N; ++z) cost[z] = (uint8_t)((t[z >> 2] >> (8 * (z & 3))) & 0xFFu);
+            tally_word(h, t, N);
         }
     }
+}
+
+// A wave takes runs of `run` tiles (at most 64). SUMS pays for itself from a
+// run of 8 on: the sums of a run cost about two tiles' work and save half of
+// every tile's.
+template <int NB, bool SUMS>
+__global__ void __launch_bounds__(kCostThreads)
+cost_table_kernel(const ClauseRec *__restrict__ recs, ClauseCounts cc, int neff, int n, uint32_t run,
+                  uint8_t *__restrict__ cost, uint32_t *__restrict__ block_hist, int hist_len, int win_a0) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    CostLds lds(smem, neff);
+    for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kCostThreads) lds.hist[i] = 0;
+    for (int i = threadIdx.x; i < kMaxRecs; i += kCostThreads) lds.rec[i] = recs[i];
+    __syncthreads();
+    uint32_t *h = hist_copy(lds);
+    EffEntry(*eff)[2] = lds.wave_eff(neff);
+    const uint32_t ntiles = n > kHighBit0 ? 1u << (n - kHighBit0) : 1u;
+    const uint32_t step = gridDim.x * kCostWaves * run;
+    LevelWindow<NB> win;
+    win.clear(win_a0);
+    for (uint32_t t0 = (blockIdx.x * kCostWaves + threadIdx.x / kWave) * run; t0 < ntiles; t0 += step)
+        wave_tiles<NB, SUMS>(lds.rec, cc, eff, t0, min(run, ntiles - t0), n, cost, win, h);
     win.flush(h);
     __syncthreads();
     for (int k = threadIdx.x; k < hist_len; k += kCostThreads) {
@@ -281,61 +391,69 @@ struct HistInst {
     uint64_t cost_off;  // byte offset of the instance's cost table (when costs are written)
 };
 struct HistUnit {
-    uint32_t inst, word0, nwords, pad;
+    uint32_t inst, tile0, ntiles, pad;
 };
+
+constexpr uint32_t kSumsRun = 8;  // shortest run of tiles per wave that takes the class sums
 
 __global__ void __launch_bounds__(kCostThreads)
 hist_batched_kernel(const HistInst *__restrict__ insts, const HistUnit *__restrict__ units,
-                    const int32_t *__restrict__ lits, unsigned long long *__restrict__ hists, int hist_stride,
-                    uint8_t *__restrict__ costs) {
-    extern __shared__ unsigned char smem[];
+                    const int32_t *__restrict__ lits, int neff, unsigned long long *__restrict__ hists,
+                    int hist_stride, uint8_t *__restrict__ costs) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ int cls_n[kCostWaves][kClasses];
     const HistUnit unit = units[blockIdx.x];
     const HistInst in = insts[unit.inst];
-    const int nvec = (in.m + kGroup - 1) / kGroup * kGroup;
-    CostLds lds(smem, nvec);
+    CostLds lds(smem, neff);
     const int32_t *L = lits + 3 * (size_t)in.lit_off;
-    for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kCostThreads) lds.hist[i] = 0;
-    for (int c = threadIdx.x; c < nvec; c += kCostThreads)
-        lds.rec[c] = c < in.m ? make_record(L[3 * c], L[3 * c + 1], L[3 * c + 2], nullptr)
-                              : ClauseRec{0u, 0u, 0ull, 0ull, 0ull};
+    const int c = threadIdx.x, wave = threadIdx.x / kWave;
+    for (int i = c; i < kHistCopies * kHistStride; i += kCostThreads) lds.hist[i] = 0;
+    for (int i = c; i < kMaxRecs; i += kCostThreads) lds.rec[i] = ClauseRec{0u, 0u, 0u, 0u, 0ull};
+    // thread c ingests clause c (m <= 255): its record goes behind those of its
+    // class with a lower index
+    int cls = -1, below = 0;
+    ClauseRec r;
+    if (c < in.m) r = make_record(L[3 * c], L[3 * c + 1], L[3 * c + 2], &cls);
+#pragma unroll
+    for (int k = 0; k < kClasses; ++k) {
+        const uint64_t mask = __ballot(cls == k);
+        if (cls == k) below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        if ((c & (kWave - 1)) == 0) cls_n[wave][k] = __popcll(mask);
+    }
+    __syncthreads();
+    int tot[kClasses];
+#pragma unroll
+    for (int k = 0; k < kClasses; ++k) {
+        tot[k] = 0;
+#pragma unroll
+        for (int w = 0; w < kCostWaves; ++w) {
+            if (cls == k && w < wave) below += cls_n[w][k];
+            tot[k] += cls_n[w][k];
+        }
+        tot[k] = __builtin_amdgcn_readfirstlane(tot[k]);
+    }
+    const ClauseCounts cc = clause_layout(tot[0], tot[1], tot[2], tot[3]);
+    if (cls >= 0) lds.rec[cc.first[cls] + below] = r;
     __syncthreads();
     uint32_t *h = hist_copy(lds);
-    EffEntry(*eff)[2] = lds.wave_eff(nvec);
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t nbits = in.n >= kLowBits ? 32u : (1u << in.n);
-    const uint32_t ntiles = (unit.nwords + kWave - 1) / kWave;
+    EffEntry(*eff)[2] = lds.wave_eff(neff);
     LevelWindow<2> win;
     win.clear(in.win_a0);
-    for (uint32_t t0 = threadIdx.x / kWave; t0 < ntiles; t0 += kCostWaves) {
-        // word0 is a multiple of 64, so tile (word0 / 64 + t0) starts at word0 + 64 t0
-        const uint64_t tile = (uint64_t)unit.word0 / kWave + t0;
-        uint32_t v[8], t[8];
-        eval_planes(lds.rec, nvec, nullptr, 0, tile, eff, v);
-        if (t0 * kWave + lane >= unit.nwords) continue;
-        if (nbits == 32u) {
-            const uint32_t outside = win.add(v);
-            if (outside || costs) planes_to_bytes(v, t);
-            if (outside) tally_bits(h, t, outside);
-            if (costs) {
-                typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-                const uint64_t w = (uint64_t)unit.word0 + t0 * kWave + lane;
-                u32x4 *dst = reinterpret_cast<u32x4 *>(costs + in.cost_off + (w << kLowBits));
-                dst[0] = u32x4{t[0], t[1], t[2], t[3]};
-                dst[1] = u32x4{t[4], t[5], t[6], t[7]};
-            }
-        } else {
-            planes_to_bytes(v, t);
-            tally_word(h, t, nbits);
-            if (costs)
-                for (uint32_t z = 0; z < nbits; ++z)
-                    costs[in.cost_off + z] = (uint8_t)((t[z >> 2] >> (8 * (z & 3))) & 0xFFu);
-        }
+    // the unit's tiles in equal runs, one per wave
+    const uint32_t run = (unit.ntiles + kCostWaves - 1) / kCostWaves;
+    const uint32_t t0 = wave * run;
+    uint8_t *cost = costs ? costs + in.cost_off : nullptr;
+    if (t0 < unit.ntiles) {
+        const uint32_t nt = min(run, unit.ntiles - t0);
+        if (run >= kSumsRun) wave_tiles<2, true>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
+        else wave_tiles<2, false>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
     }
     win.flush(h);
     __syncthreads();
     for (int k = threadIdx.x; k <= in.m; k += kCostThreads) {
         uint32_t s = 0;
-        for (int c = 0; c < kHistCopies; ++c) s += lds.hist[c * kHistStride + k];
+        for (int q = 0; q < kHistCopies; ++q) s += lds.hist[q * kHistStride + k];
         if (s && hists) atomicAdd(hists + (size_t)unit.inst * hist_stride + k, (unsigned long long)s);
     }
 }
@@ -354,75 +472,84 @@ static void level_window(int m, int *a0, int *nb) {
     *nb = std::min(2, hi / 32 - *a0 + 1);
 }
 
+// Runs of tiles per wave and blocks of a cost table: the longest run (at most
+// 64) that still gives 4096 waves, and single tiles where that leaves runs
+// shorter than kSumsRun.
+struct CostGrid {
+    uint32_t run;
+    int blocks;
+};
+static CostGrid cost_grid(int n, const DeviceInfo &dev, int cap) {
+    const uint32_t ntiles = n > kHighBit0 ? 1u << (n - kHighBit0) : 1u;
+    CostGrid g{1, 0};
+    if (ntiles / 4096 >= kSumsRun) g.run = std::min(64u, ntiles / 4096);
+    const uint32_t want = (ntiles / g.run + kCostWaves - 1) / kCostWaves;
+    g.blocks = (int)std::min<uint32_t>(want, (uint32_t)std::min(dev.num_cus * 8, cap));
+    return g;
+}
+
+template <int NB>
+static void launch_cost_kernel(bool sums, int m, const CostGrid &g, const ClauseRec *recs, const ClauseCounts &cc,
+                               int n, uint8_t *cost, uint32_t *d_bh, int a0, hipStream_t stream) {
+    const dim3 grid(g.blocks), block(kCostThreads);
+    if (sums)
+        hipLaunchKernelGGL((cost_table_kernel<NB, true>), grid, block, cost_lds_bytes(m), stream, recs, cc,
+                           eff_entries(m), n, g.run, cost, d_bh, m + 1, a0);
+    else
+        hipLaunchKernelGGL((cost_table_kernel<NB, false>), grid, block, cost_lds_bytes(m), stream, recs, cc,
+                           eff_entries(m), n, g.run, cost, d_bh, m + 1, a0);
+}
+
 // Cost kernel and histogram reduce on records already on the device.
-static int enqueue_cost_kernels(int n, int m, int nblocks, int nvec, int nuni, const ClauseRec *d_vec,
-                                const UniformRec *d_uni, uint32_t *d_bh, uint8_t *cost, uint64_t *hist,
-                                hipStream_t stream) {
+static int enqueue_cost_kernels(int n, int m, const CostGrid &g, const ClauseCounts &cc, const ClauseRec *d_rec,
+                                uint32_t *d_bh, uint8_t *cost, uint64_t *hist, hipStream_t stream) {
     const int hist_len = m + 1;
     int a0 = 0, nb = 1;
     level_window(m, &a0, &nb);
     ProfScope ps("cost_table", stream);
-    if (nb == 1)
-        hipLaunchKernelGGL(cost_table_kernel<1>, dim3(nblocks), dim3(kCostThreads), cost_lds_bytes(nvec), stream,
-                           d_vec, nvec, d_uni, nuni, n, cost, d_bh, hist_len, a0);
-    else
-        hipLaunchKernelGGL(cost_table_kernel<2>, dim3(nblocks), dim3(kCostThreads), cost_lds_bytes(nvec), stream,
-                           d_vec, nvec, d_uni, nuni, n, cost, d_bh, hist_len, a0);
+    if (nb == 1) launch_cost_kernel<1>(g.run >= kSumsRun, m, g, d_rec, cc, n, cost, d_bh, a0, stream);
+    else launch_cost_kernel<2>(g.run >= kSumsRun, m, g, d_rec, cc, n, cost, d_bh, a0, stream);
     ps.end();
     GQ_LAUNCH_CHECK();
     if (hist) {
-        hipLaunchKernelGGL(hist_reduce_kernel, dim3(hist_len), dim3(256), 0, stream, d_bh, nblocks, hist_len,
+        hipLaunchKernelGGL(hist_reduce_kernel, dim3(hist_len), dim3(256), 0, stream, d_bh, g.blocks, hist_len,
                            reinterpret_cast<unsigned long long *>(hist));
         GQ_LAUNCH_CHECK();
     }
     return GQAOA_OK;
 }
 
-static int cost_grid(int n, const DeviceInfo &dev, int cap) {
-    const uint64_t nwords = n >= kLowBits ? (1ull << (n - kLowBits)) : 1;
-    const uint64_t want = (nwords + kCostThreads - 1) / kCostThreads;
-    return (int)std::min<uint64_t>(want, (uint64_t)std::min(dev.num_cus * 8, cap));
-}
+constexpr size_t kRecBytes = sizeof(ClauseRec) * kMaxRecs;
 
 int launch_cost_table(int n, int m, const int32_t *lits, uint8_t *cost, uint64_t *hist,
                       hipStream_t stream) {
     DeviceInfo dev;
     int st = device_info(&dev);
     if (st) return st;
-    std::vector<ClauseRec> vec;
-    std::vector<UniformRec> uni;
-    pack_clauses(m, lits, vec, uni);
-    const int nblocks = cost_grid(n, dev, 1 << 30);
-    const int hist_len = m + 1;
-    const size_t rec_bytes = sizeof(ClauseRec) * vec.size() + sizeof(UniformRec) * (uni.size() + 1);
-    const size_t bh_bytes = sizeof(uint32_t) * (size_t)nblocks * hist_len;
+    ClauseRec rec[kMaxRecs];
+    const ClauseCounts cc = pack_clauses(m, lits, rec);
+    const CostGrid g = cost_grid(n, dev, 1 << 30);
+    const size_t rec_bytes = (kRecBytes + 255) & ~size_t(255);
     AsyncScratch guard(stream);
-    GQ_HIP(guard.alloc(rec_bytes + bh_bytes + 256));
-    void *scratch = guard.ptr;
-    ClauseRec *d_vec = reinterpret_cast<ClauseRec *>(scratch);
-    UniformRec *d_uni = reinterpret_cast<UniformRec *>(d_vec + vec.size());
-    uint32_t *d_bh = reinterpret_cast<uint32_t *>(
-        (reinterpret_cast<uintptr_t>(d_uni + uni.size() + 1) + 255) & ~uintptr_t(255));
-    std::vector<char> staging(rec_bytes);
-    memcpy(staging.data(), vec.data(), sizeof(ClauseRec) * vec.size());
-    if (!uni.empty()) memcpy(staging.data() + sizeof(ClauseRec) * vec.size(), uni.data(), sizeof(UniformRec) * uni.size());
-    GQ_HIP(hipMemcpyAsync(scratch, staging.data(), rec_bytes, hipMemcpyHostToDevice, stream));
-    GQ_HIP(hipStreamSynchronize(stream));  // staging is host pageable memory owned here
-    return enqueue_cost_kernels(n, m, nblocks, (int)vec.size(), (int)uni.size(), d_vec, d_uni, d_bh, cost, hist,
-                                stream);
+    GQ_HIP(guard.alloc(rec_bytes + sizeof(uint32_t) * (size_t)g.blocks * (m + 1)));
+    char *scratch = reinterpret_cast<char *>(guard.ptr);
+    GQ_HIP(hipMemcpyAsync(scratch, rec, kRecBytes, hipMemcpyHostToDevice, stream));
+    GQ_HIP(hipStreamSynchronize(stream));  // the records are host stack memory of this call
+    return enqueue_cost_kernels(n, m, g, cc, reinterpret_cast<const ClauseRec *>(scratch),
+                                reinterpret_cast<uint32_t *>(scratch + rec_bytes), cost, hist, stream);
 }
 
 // ---- allocation-free form: scratch in a static device array --------------------------------
 // The clause records and the per-block histogram rows of gqaoa_cost_table,
 // for callers that cannot allocate device memory. The grid is capped at
 // kStaticBlocks blocks (the kernel's loop over tiles covers any n), so every
-// valid (n, m) fits: 12 KiB of records and at most 2 MiB of rows. Each GPU
+// valid (n, m) fits: 8 KiB of records and at most 2 MiB of rows. Each GPU
 // holds its own copy of the array until the process ends; host code reaches it
 // only through the address hipGetSymbolAddress returns on that device.
 constexpr int kStaticBlocks = 2048;
-constexpr size_t kStaticRecBytes =
-    (sizeof(ClauseRec) * kMaxVec + sizeof(UniformRec) * kMaxVec + 255) & ~size_t(255);
-constexpr size_t kStaticRowBytes = sizeof(uint32_t) * (size_t)kStaticBlocks * kMaxVec;
+constexpr size_t kStaticRecBytes = 8192;
+static_assert(kRecBytes <= kStaticRecBytes, "records");
+constexpr size_t kStaticRowBytes = sizeof(uint32_t) * (size_t)kStaticBlocks * 256;
 constexpr size_t kStaticScratchBytes = kStaticRecBytes + kStaticRowBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -452,24 +579,18 @@ int launch_cost_table_noalloc(int n, int m, const int32_t *lits, uint8_t *cost, 
     if (st) return st;
     unsigned char *base = nullptr;
     if ((st = static_scratch(&base))) return st;
-    ClauseRec vec[kMaxVec];
-    UniformRec uni[kMaxVec];
-    int nvec = 0, nuni = 0;
-    pack_clauses(m, lits, vec, &nvec, uni, &nuni);
-    const int nblocks = cost_grid(n, dev, kStaticBlocks);
-    const size_t vec_bytes = sizeof(ClauseRec) * (size_t)nvec, uni_bytes = sizeof(UniformRec) * (size_t)nuni;
-    const size_t row_bytes = sizeof(uint32_t) * (size_t)nblocks * (size_t)(m + 1);
-    if (vec_bytes + uni_bytes > kStaticRecBytes || row_bytes > kStaticRowBytes)
-        return fail(GQAOA_ERANGE, "cost table n=%d m=%d needs %zu + %zu scratch bytes, more than the static %zu + %zu",
-                    n, m, vec_bytes + uni_bytes, row_bytes, kStaticRecBytes, kStaticRowBytes);
-    ClauseRec *d_vec = reinterpret_cast<ClauseRec *>(base);
-    UniformRec *d_uni = reinterpret_cast<UniformRec *>(base + vec_bytes);
-    uint32_t *d_bh = reinterpret_cast<uint32_t *>(base + kStaticRecBytes);
-    if (nvec) GQ_HIP(hipMemcpyAsync(d_vec, vec, vec_bytes, hipMemcpyHostToDevice, stream));
-    if (nuni) GQ_HIP(hipMemcpyAsync(d_uni, uni, uni_bytes, hipMemcpyHostToDevice, stream));
+    ClauseRec rec[kMaxRecs];
+    const ClauseCounts cc = pack_clauses(m, lits, rec);
+    const CostGrid g = cost_grid(n, dev, kStaticBlocks);
+    const size_t row_bytes = sizeof(uint32_t) * (size_t)g.blocks * (size_t)(m + 1);
+    if (row_bytes > kStaticRowBytes)
+        return fail(GQAOA_ERANGE, "cost table n=%d m=%d needs %zu scratch bytes, more than the static %zu", n, m,
+                    row_bytes, kStaticRowBytes);
+    GQ_HIP(hipMemcpyAsync(base, rec, kRecBytes, hipMemcpyHostToDevice, stream));
     GQ_HIP(hipStreamSynchronize(stream));  // the records are host stack memory of this call
     // every block writes its whole row of hist_len counts, so no row needs clearing
-    return enqueue_cost_kernels(n, m, nblocks, nvec, nuni, d_vec, d_uni, d_bh, cost, hist, stream);
+    return enqueue_cost_kernels(n, m, g, cc, reinterpret_cast<const ClauseRec *>(base),
+                                reinterpret_cast<uint32_t *>(base + kStaticRecBytes), cost, hist, stream);
 }
 
 // Byte offset of each instance's cost table in the concatenated output: the
@@ -485,11 +606,15 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
                         const int32_t *lits, uint64_t *hists, int hist_stride, uint8_t *costs, hipStream_t stream) {
     std::vector<HistInst> insts(num_inst);
     std::vector<HistUnit> units;
-    constexpr uint32_t kUnitWords = kCostThreads * 4;
+    // tiles of a unit: runs of up to 32 per wave while the batch still gives
+    // 4096 of them
+    uint64_t all_tiles = 0;
+    for (int i = 0; i < num_inst; ++i) all_tiles += n_host[i] > kHighBit0 ? 1ull << (n_host[i] - kHighBit0) : 1;
+    uint32_t unit_tiles = 4 * kCostWaves;
+    while (unit_tiles < 32 * kCostWaves && all_tiles / (unit_tiles * 2) * kCostWaves >= 4096) unit_tiles *= 2;
     size_t off = 0;
     int max_m = 1;
     for (int i = 0; i < num_inst; ++i) max_m = std::max(max_m, m_host[i]);
-    const size_t smem_bytes = cost_lds_bytes((max_m + kGroup - 1) / kGroup * kGroup);
     uint64_t cost_off = 0;
     for (int i = 0; i < num_inst; ++i) {
         int a0 = 0, nb = 1;
@@ -497,10 +622,9 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
         insts[i] = HistInst{(uint32_t)off, n_host[i], m_host[i], a0, cost_off};
         cost_off += ((1ull << n_host[i]) + 63) & ~63ull;
         off += (size_t)m_host[i];
-        const uint64_t nwords = n_host[i] >= kLowBits ? (1ull << (n_host[i] - kLowBits)) : 1;
-        for (uint64_t w0 = 0; w0 < nwords; w0 += kUnitWords)
-            units.push_back(HistUnit{(uint32_t)i, (uint32_t)w0,
-                                     (uint32_t)std::min<uint64_t>(kUnitWords, nwords - w0), 0u});
+        const uint32_t ntiles = n_host[i] > kHighBit0 ? 1u << (n_host[i] - kHighBit0) : 1u;
+        for (uint32_t t0 = 0; t0 < ntiles; t0 += unit_tiles)
+            units.push_back(HistUnit{(uint32_t)i, t0, std::min(unit_tiles, ntiles - t0), 0u});
     }
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t b_inst = sizeof(HistInst) * insts.size();
@@ -515,9 +639,10 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
     GQ_HIP(hipMemcpyAsync(base + o_unit, units.data(), b_unit, hipMemcpyHostToDevice, stream));
     GQ_HIP(hipMemcpyAsync(base + o_lits, lits, b_lits, hipMemcpyHostToDevice, stream));
     if (hists) GQ_HIP(hipMemsetAsync(hists, 0, sizeof(uint64_t) * (size_t)num_inst * hist_stride, stream));
-    hipLaunchKernelGGL(hist_batched_kernel, dim3((unsigned)units.size()), dim3(kCostThreads), smem_bytes, stream,
+    hipLaunchKernelGGL(hist_batched_kernel, dim3((unsigned)units.size()), dim3(kCostThreads), cost_lds_bytes(max_m),
+                       stream,
                        reinterpret_cast<const HistInst *>(base), reinterpret_cast<const HistUnit *>(base + o_unit),
-                       reinterpret_cast<const int32_t *>(base + o_lits),
+                       reinterpret_cast<const int32_t *>(base + o_lits), eff_entries(max_m),
                        reinterpret_cast<unsigned long long *>(hists), hist_stride, costs);
     GQ_LAUNCH_CHECK();
     GQ_HIP(hipStreamSynchronize(stream));  // the host tables above end with this call
