@@ -67,9 +67,10 @@ size_t cost_lds_bytes(int m) {
            sizeof(uint32_t) * kHistCopies * kHistStride;
 }
 
-__device__ __forceinline__ uint32_t *hist_copy(CostLds &s) {
-    return s.hist + ((threadIdx.x / kWave) * 4 + (threadIdx.x & 3)) * kHistStride;
+__device__ __forceinline__ uint32_t *wave_copies(CostLds &s) {
+    return s.hist + (threadIdx.x / kWave) * 4 * kHistStride;
 }
+__device__ __forceinline__ uint32_t *hist_copy(CostLds &s) { return wave_copies(s) + (threadIdx.x & 3) * kHistStride; }
 
 // Sums of classes B, C and D for up to 64 tiles, lane t holding tile tile0 + t:
 // b: bit planes over the word bits of B's sum plus D's count; c[0], c[1]: bit
@@ -260,13 +261,24 @@ struct LevelWindow {
         }
         return ~in;
     }
-    // add the counters into an LDS histogram (levels < 256)
+    // Add the counters into an LDS histogram (levels < 256): summed over each
+    // row of 16 lanes first (DPP shifts), so a level costs four LDS adds to four
+    // copies instead of 64 to 4. Every lane of the wave calls this.
     __device__ __forceinline__ void flush(uint32_t *h) const {
+        const int lane = threadIdx.x & (kWave - 1);
+        uint32_t *copy = h + (lane >> 4) * kHistStride;  // h: the wave's first copy
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int k = 0; k < 32; ++k)
-                if (cnt[i][k] && a0 + i < 8) atomicAdd(h + 32 * (a0 + i) + k, cnt[i][k]);
+            for (int k = 0; k < 32; ++k) {
+                if (a0 + i >= 8 || __ballot(cnt[i][k] != 0u) == 0) continue;
+                int s = (int)cnt[i][k];
+                s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, true);  // row_shr:1
+                s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, true);  // row_shr:2
+                s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, true);  // row_shr:4
+                s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, true);  // row_shr:8
+                if ((lane & 15) == 15) atomicAdd(copy + 32 * (a0 + i) + k, (uint32_t)s);
+            }
     }
 };
 
@@ -352,7 +364,7 @@ cost_table_kernel(const ClauseRec *__restrict__ recs, ClauseCounts cc, int neff,
     win.clear(win_a0);
     for (uint32_t t0 = (blockIdx.x * kCostWaves + threadIdx.x / kWave) * run; t0 < ntiles; t0 += step)
         wave_tiles<NB, SUMS>(lds.rec, cc, eff, t0, min(run, ntiles - t0), n, cost, win, h);
-    win.flush(h);
+    win.flush(wave_copies(lds));
     __syncthreads();
     for (int k = threadIdx.x; k < hist_len; k += kCostThreads) {
         uint32_t s = 0;
@@ -381,9 +393,8 @@ __global__ void __launch_bounds__(256) hist_reduce_kernel(const uint32_t *__rest
 
 // ---- many instances, histograms only ---------------------------------------
 // Clause ingest runs on the device here: each block builds its instance's
-// records from the raw literals straight into LDS (every clause as a vector
-// record, padded to the adder-tree group), so the host uploads 12 bytes per
-// clause and packs nothing.
+// records from the raw literals straight into LDS, so the host uploads 12
+// bytes per clause and packs nothing.
 struct HistInst {
     uint32_t lit_off;   // first clause of the instance in the literal array
     int32_t n, m;
@@ -449,7 +460,7 @@ hist_batched_kernel(const HistInst *__restrict__ insts, const HistUnit *__restri
         if (run >= kSumsRun) wave_tiles<2, true>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
         else wave_tiles<2, false>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
     }
-    win.flush(h);
+    win.flush(wave_copies(lds));
     __syncthreads();
     for (int k = threadIdx.x; k <= in.m; k += kCostThreads) {
         uint32_t s = 0;
