@@ -627,9 +627,12 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
     int max_m = 1;
     for (int i = 0; i < num_inst; ++i) max_m = std::max(max_m, m_host[i]);
     uint64_t cost_off = 0;
+    int win_a0[256];  // by m, filled as they occur
+    std::fill(win_a0, win_a0 + 256, -1);
+    units.reserve((size_t)num_inst + all_tiles / unit_tiles);
     for (int i = 0; i < num_inst; ++i) {
-        int a0 = 0, nb = 1;
-        level_window(m_host[i], &a0, &nb);
+        int &a0 = win_a0[m_host[i]], nb = 1;
+        if (a0 < 0) level_window(m_host[i], &a0, &nb);
         insts[i] = HistInst{(uint32_t)off, n_host[i], m_host[i], a0, cost_off};
         cost_off += ((1ull << n_host[i]) + 63) & ~63ull;
         off += (size_t)m_host[i];

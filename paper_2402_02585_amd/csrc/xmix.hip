@@ -21,9 +21,8 @@
 //     high-group tile) and applies the butterflies of the register-resident
 //     bits there; the tile is re-distributed through LDS to bring the next
 //     bits into registers (one to four exchanges per pass, never a butterfly
-//     in LDS). For group 0 and the full groups the chunk plan is a template
-//     parameter, so the exchanges use fixed LDS offsets and the stages run
-//     without branches;
+//     in LDS). The chunk plan is a template parameter, so the exchanges use
+//     fixed LDS offsets and the stages run without branches;
 //   * the group order alternates between rounds (o_0..o_{g-1}, then back),
 //     so the last pass of a round and the first of the next touch the same
 //     group and are fused: mixers of round j, readout of the state after
@@ -200,10 +199,7 @@ struct XPassArgs {
     const uint8_t *cost;   // C of tile t at (t << T), in the order after the group's forward mixers
     const uint8_t *cost_z; // the cost table (z order), for the readout-only pass
     int n, mlo, q0;        // tile bits [0, mlo) = z bits [0, mlo); [mlo, T) = z bits [q0, ...)
-    int contig;            // tile bits that are consecutive in z (T for group 0, else mlo)
     uint64_t ntiles;
-    XPlan plan;
-    int ops;
     int init_uniform;
     double init_amp;
     int target;
@@ -312,34 +308,9 @@ __device__ __forceinline__ XF<T> x_factors(T c, T s) {
     return XF<T>{cv, sv, nsv};
 }
 
-template <typename T, int R>
-__device__ __forceinline__ void x_stages(XC<T> (&v)[1 << R], int mask, const XF<T> &f) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (!((mask >> r) & 1)) continue;  // uniform across the block
-#pragma unroll
-        for (int i = 0; i < (1 << R); ++i)
-            if (!((i >> r) & 1)) xrot2(v[i], v[i | (1 << r)], f.c, f.s, f.ns);
-    }
-}
-
-// Mixers of one group, chunk by chunk, forward (from rb[0]) or backward (from
-// the last chunk); rb is the register layout on entry and on exit.
-template <typename T, int R>
-__device__ __forceinline__ void x_mix(XC<T> (&v)[1 << R], XC<T> *lds, const XPlan &pl, bool forward, int &rb,
-                                      const XF<T> &f) {
-    for (int k = 0; k < pl.nchunks; ++k) {
-        const int kk = forward ? k : pl.nchunks - 1 - k;
-        if (pl.rb[kk] != rb) {
-            x_exchange<T, R>(v, lds, rb, pl.rb[kk]);
-            rb = pl.rb[kk];
-        }
-        x_stages<T, R>(v, pl.mask[kk], f);
-    }
-}
-
-// The same with the group's plan fixed at compile time (group on tile bits
-// [MLO, TB)): exchanges at fixed layouts, no branches between stages.
+// Mixers of one group (tile bits [MLO, TB)), chunk by chunk, forward (from the
+// load layout) or backward (to it). The plan is fixed at compile time:
+// exchanges at fixed layouts, no branches between stages.
 template <typename T, int R, int MASK>
 __device__ __forceinline__ void x_stages_c(XC<T> (&v)[1 << R], const XF<T> &f) {
 #pragma unroll
@@ -365,14 +336,18 @@ __device__ __forceinline__ void x_mix_c(XC<T> (&v)[1 << R], XC<T> *lds, const XF
 }
 
 // Readouts of one tile's register values: sums in the state precision within
-// the tile, float64 across tiles.
-template <typename T, int R>
+// the tile, float64 across tiles. RE_FMA fixes which product of |v|^2 is
+// rounded first (im^2), so that a last group of any size gives the bits it
+// always gave; otherwise the compiler's choice stands.
+template <typename T, int R, bool RE_FMA>
 __device__ __forceinline__ void x_readout(const XC<T> (&v)[1 << R], const uint32_t (&cz)[1 << R], double &aP,
                                           double &aE, double &aN, int target) {
     T sP = 0, sE = 0, sN = 0;
 #pragma unroll
     for (int i = 0; i < (1 << R); ++i) {
-        const T pr = v[i].re * v[i].re + v[i].im * v[i].im;
+        T pr;
+        if constexpr (RE_FMA) pr = x_fma(v[i].re, v[i].re, v[i].im * v[i].im);
+        else pr = v[i].re * v[i].re + v[i].im * v[i].im;
         sN += pr;
         sE += (T)cz[i] * pr;
         sP += cz[i] == (uint32_t)target ? pr : T(0);
@@ -403,9 +378,10 @@ __device__ __forceinline__ void x_unpack_costs(const typename XCostVec<R>::type 
 // OPS: the XOP_* flags of the pass, fixed at compile time so that a pass
 // that only mixes carries no readout, cost or phase state. TB: the tile bits
 // (group 0's tiles or the high groups' twice larger ones), one tile per
-// 2^(TB - R) threads. MLO >= 0: the group is on tile bits [MLO, TB) and its
-// plan is fixed at compile time (group 0 and the full groups of 8 qubits);
-// MLO = -1: any group, from the plan in the arguments.
+// 2^(TB - R) threads. The group is on tile bits [MLO, TB) and its plan is
+// fixed at compile time (a last group of 6 qubits took 318 us per fused pass
+// with the plan as an argument, against 195 us of a full group of 8: n = 26,
+// complex64; with its own plan 195-205 us).
 template <typename T, int OPS, int MLO, int TB>
 __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArgs a) {
     constexpr int R = XCfg<T>::R, E = 1 << R, kThreads = 1 << (TB - R);
@@ -416,7 +392,8 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
     // while this tile is mixed and stored.
     constexpr bool kStream = (OPS & XOP_MIX_A) != 0 && (OPS & XOP_PRE) == 0;
     constexpr bool kReadout = (OPS & (XOP_PRE | XOP_MID | XOP_POST)) != 0;
-    constexpr int kPlan = OPS == XOP_MIX_A && MLO == 0 ? kXPlanMix0 : MLO >= 0 ? MLO : 0;
+    constexpr bool kRagged = MLO > TB - kXGroupBits;
+    constexpr int kPlan = OPS == XOP_MIX_A && MLO == 0 ? kXPlanMix0 : MLO;
     constexpr XPlan kP = x_plan_id(TB, R, kPlan);
     extern __shared__ __align__(16) unsigned char smem[];
     XC<T> *lds = reinterpret_cast<XC<T> *>(smem);
@@ -431,11 +408,11 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
     constexpr int rb0 = TB - R;
     constexpr bool store = (OPS & (XOP_MIX_A | XOP_MID)) != 0;
     XC<T> *psi = reinterpret_cast<XC<T> *>(a.psi);
-    const int mlo = MLO >= 0 ? MLO : a.mlo;
-    const int contig = MLO == 0 ? TB : MLO > 0 ? MLO : a.contig;
+    constexpr int mlo = MLO;
+    constexpr int contig = MLO == 0 ? TB : MLO;  // tile bits that are consecutive in z
     const int lowbits = a.q0 - mlo;         // z bits mlo..q0-1 come from the tile index
     const int hishift = a.q0 + TB - mlo;    // z bits above the group
-    const uint32_t cmask = (1u << mlo) - 1u;
+    constexpr uint32_t cmask = (1u << mlo) - 1u;
     double aP = 0.0, aE = 0.0, aN = 0.0;
     // z of tile element e is base | zmap(e); zmap is a bit placement, so for
     // e = (thread part) | (register part) it splits into a per-thread offset
@@ -462,16 +439,12 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
     };
     // mixers forward from rb0 or backward to it; rb: the layout on exit
     auto mix = [&](XC<T>(&w)[E], bool forward, int &rb, const XF<T> &f) {
-        if constexpr (MLO >= 0) {
-            if (forward) {
-                x_mix_c<T, R, TB, kPlan, true>(w, lds, f);
-                rb = kP.rb[kP.nchunks - 1];
-            } else {
-                x_mix_c<T, R, TB, kPlan, false>(w, lds, f);
-                rb = rb0;
-            }
+        if (forward) {
+            x_mix_c<T, R, TB, kPlan, true>(w, lds, f);
+            rb = kP.rb[kP.nchunks - 1];
         } else {
-            x_mix<T, R>(w, lds, a.plan, forward, rb, f);
+            x_mix_c<T, R, TB, kPlan, false>(w, lds, f);
+            rb = rb0;
         }
     };
     XC<T> v[E];
@@ -498,7 +471,7 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
             mix(v, true, rb, x_factors((T)a.ca, (T)a.sa));
             if constexpr (kCosts) {
                 x_unpack_costs<R>(cw, cz);
-                x_readout<T, R>(v, cz, aP, aE, aN, a.target);
+                x_readout<T, R, kRagged>(v, cz, aP, aE, aN, a.target);
             }
             if constexpr ((OPS & XOP_MID) != 0) {
 #pragma unroll
@@ -514,7 +487,7 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
         // mixed backward into the load layout. The readout-only pass (p = 0)
         // gathers its costs from the cost table.
         static_assert((OPS & XOP_PRE) == 0 || (OPS & XOP_MID) == 0, "the first pass is no boundary pass");
-        const int rb_end = MLO >= 0 ? kP.rb[kP.nchunks - 1] : a.plan.rb[a.plan.nchunks - 1];
+        constexpr int rb_end = kP.rb[kP.nchunks - 1];
         for (uint64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
             auto load_cost = [&](int rb) {
                 const uint8_t *cc = a.cost_z + tile_base(tile) + zmap((uint32_t)x_elem(t, 0, rb, R));
@@ -533,7 +506,7 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
                 }
                 rb = rb_end;
                 x_unpack_costs<R>(cw, cz);
-                x_readout<T, R>(v, cz, aP, aE, aN, a.target);
+                x_readout<T, R, kRagged>(v, cz, aP, aE, aN, a.target);
 #pragma unroll
                 for (int i = 0; i < E; ++i) v[i] = xmul(lut_s[0][cz[i]], v[i]);
                 if constexpr ((OPS & XOP_MIX_A) != 0) mix(v, false, rb, x_factors((T)a.ca, (T)a.sa));
@@ -543,7 +516,7 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
             }
             if constexpr ((OPS & XOP_POST) != 0) {
                 load_cost(rb);
-                x_readout<T, R>(v, cz, aP, aE, aN, a.target);
+                x_readout<T, R, kRagged>(v, cz, aP, aE, aN, a.target);
             }
             if constexpr (store) store_tile(tile, v, rb);
         }
@@ -673,36 +646,35 @@ static XLayout x_layout(void *ws, int n, int p, int dtype) {
 
 size_t x_workspace_bytes(int n, int p, int dtype) { return x_layout(nullptr, n, p, dtype).bytes; }
 
-// Group 0 (mlo = 0) on its own tiles; the high groups on the larger ones,
-// a full group of 8 qubits with its compile-time plan.
-template <typename T, int OPS>
-static void launch_group(int mlo, int blocks, size_t smem, hipStream_t st, const XPassArgs &a) {
+// Group 0 (mlo = 0) on its own tiles; the high groups of KB qubits on the
+// larger ones. A group of fewer than 8 qubits is the last of its call, so it
+// takes only the fused boundary passes and the last pass.
+template <typename T, int OPS, int KB = kXGroupBits>
+static int launch_group(int blocks, size_t smem, hipStream_t st, const XPassArgs &a) {
     constexpr int TB = XCfg<T>::TB, TBW = XCfg<T>::TBW, R = XCfg<T>::R;
-    constexpr int kFull = TBW - kXGroupBits;  // high-group tile bits below a full group
-    if (mlo == 0)
+    constexpr bool kRagged = OPS == (XOP_MIX_A | XOP_MID) || OPS == (XOP_MIX_A | XOP_POST);
+    if (a.mlo == 0) {
         hipLaunchKernelGGL((x_pass_kernel<T, OPS, 0, TB>), dim3(blocks), dim3(1 << (TB - R)), smem, st, a);
-    else if (mlo == kFull)
-        hipLaunchKernelGGL((x_pass_kernel<T, OPS, kFull, TBW>), dim3(blocks), dim3(1 << (TBW - R)), smem, st, a);
-    else
-        hipLaunchKernelGGL((x_pass_kernel<T, OPS, -1, TBW>), dim3(blocks), dim3(1 << (TBW - R)), smem, st, a);
+    } else if (a.mlo == TBW - KB) {
+        hipLaunchKernelGGL((x_pass_kernel<T, OPS, TBW - KB, TBW>), dim3(blocks), dim3(1 << (TBW - R)), smem, st, a);
+    } else {
+        if constexpr (kRagged && KB > 1) return launch_group<T, OPS, KB - 1>(blocks, smem, st, a);
+        return fail(GQAOA_EINVAL, "internal: X pass operations %d on tile bits from %d", OPS, a.mlo);
+    }
+    GQ_LAUNCH_CHECK();
+    return GQAOA_OK;
 }
 
 template <typename T>
 static int launch_pass(int ops, int blocks, size_t smem, hipStream_t st, const XPassArgs &a) {
     switch (ops) {
-        case XOP_MIX_A: launch_group<T, XOP_MIX_A>(a.mlo, blocks, smem, st, a); break;
-        case XOP_PRE | XOP_MIX_A: launch_group<T, XOP_PRE | XOP_MIX_A>(a.mlo, blocks, smem, st, a); break;
-        case XOP_MIX_A | XOP_MID: launch_group<T, XOP_MIX_A | XOP_MID>(a.mlo, blocks, smem, st, a); break;
-        case XOP_MIX_A | XOP_POST: launch_group<T, XOP_MIX_A | XOP_POST>(a.mlo, blocks, smem, st, a); break;
-        case XOP_POST: launch_group<T, XOP_POST>(a.mlo, blocks, smem, st, a); break;
-        case XOP_PRE | XOP_MIX_A | XOP_POST:
-            launch_group<T, XOP_PRE | XOP_MIX_A | XOP_POST>(a.mlo, blocks, smem, st, a);
-            break;
-        default:
-            return fail(GQAOA_EINVAL, "internal: X pass operations %d", ops);
+        case XOP_MIX_A: return launch_group<T, XOP_MIX_A>(blocks, smem, st, a);
+        case XOP_PRE | XOP_MIX_A: return launch_group<T, XOP_PRE | XOP_MIX_A>(blocks, smem, st, a);
+        case XOP_MIX_A | XOP_MID: return launch_group<T, XOP_MIX_A | XOP_MID>(blocks, smem, st, a);
+        case XOP_MIX_A | XOP_POST: return launch_group<T, XOP_MIX_A | XOP_POST>(blocks, smem, st, a);
+        case XOP_POST: return launch_group<T, XOP_POST>(blocks, smem, st, a);
+        default: return fail(GQAOA_EINVAL, "internal: X pass operations %d", ops);
     }
-    GQ_LAUNCH_CHECK();
-    return GQAOA_OK;
 }
 
 // One group of qubits for the streaming passes (n > T).
@@ -860,10 +832,7 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
             a.n = n;
             a.mlo = gr.mlo;
             a.q0 = gr.q0;
-            a.contig = gi == 0 ? TB : gr.mlo;
             a.ntiles = ntiles_of(gr);
-            a.plan = gr.plan;
-            a.ops = ops;
             a.init_uniform = uniform ? 1 : 0;
             a.init_amp = amp0;
             a.target = target;

@@ -161,3 +161,27 @@ def test_bit_flip_closed_form_complex128_n30():
     assert np.abs(norm - 1).max() < 1e-12
     del psi, cost
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dt,t", [(g.C64, 12), (g.C128, 11)])
+def test_every_size_of_the_last_group(dt, t):
+    """A last group of 1 to 7 qubits beside group 0 alone (n = T + 1 .. T + 7)
+    and behind a full group of 8 (T + 9, T + 13): each has its own compiled
+    passes (fused boundary pass and last pass). Bars of the statevector tests."""
+    need_gpu()
+    for n in [t + k for k in range(1, 8)] + [t + 9, t + 13]:
+        if n > 22:
+            continue
+        m = int(round(4.2 * n))
+        lits = rand_lits(n, m, 300 + n)
+        cost, _ = g.gqaoa_cost_table(n, lits)
+        ref_cost = cost_table(n, lits)
+        b, gm = inst.uniform_angles(301 + n, 3)
+        target = int(ref_cost.min())
+        log(f"x last group n={n} dtype={dt}")
+        psi, ps, en, no = g.gqaoa_evolve_x(n, m, cost, b, gm, dtype=dt, target_level=target)
+        rpsi, rp, re, rn = evolve_x(n, ref_cost, b, gm, target=target)
+        tol = 1e-5 if dt == g.C64 else 1e-12
+        assert np.abs(ps - rp).max() < tol and np.abs(no - rn).max() < tol, n
+        assert np.abs(en - re).max() < tol * m, n
+        assert np.abs(psi.cpu().numpy() - rpsi).max() < tol, n
