@@ -11,15 +11,17 @@
 // backward products. Pre-activations z1, z2, outputs and all gradients of
 // parameters are float32; the float32 master weights are updated by Adam.
 //
-// GEMM: 256 threads compute a 64x64 tile of C = A B; each wave owns a 32x32
-// quarter as 2x2 MFMA tiles. A and B tiles of 64x32 are staged in LDS with k
-// contiguous so a lane fetches its 8 consecutive k values with one 16-byte
-// LDS read. Transposed operands (the backward products) are handled by the
-// staging loads.
+// A training step's products are small (a batch of 512 against 256 units), so
+// its launches and the latency of each are what it costs. The forward pass is
+// one launch and the backward pass two: a block takes ROWS rows of the batch
+// through all layers with a whole weight matrix in LDS at a time; the weight
+// gradients, sums over the batch, take 32x32 tiles of all matrices (and the
+// bias sums) in one launch.
 #include "internal.h"
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace gqaoa {
 
@@ -37,11 +39,13 @@ constexpr size_t kOffB3 = kOffW3 + (size_t)kDH * kDOut;
 constexpr size_t kNParams = kOffB3 + kDOut;
 static_assert(kNParams == GQAOA_MLP_NPARAMS, "parameter packing");
 
-// Round a float to bfloat16, nearest with ties to even (finite inputs).
-__device__ __forceinline__ uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+// Round a float to bfloat16, nearest with ties to even (one v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+// Two of them, the first in the low half.
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -74,200 +78,380 @@ static ActLayout act_layout(int batch) {
 }
 size_t mlp_act_bytes(int batch) { return act_layout(batch).total; }
 
-// ---- MFMA GEMM -------------------------------------------------------------------
-enum Epi { kEpiBiasGelu = 0, kEpiStoreF32 = 1, kEpiGeluGrad = 2 };
+// ---- training forward and backward --------------------------------------------
+// MFMA operands (16x16x32): lane l holds row (column) l % 16 and the 8
+// consecutive k values from 8 (l / 16); C's lane holds rows 4 (l / 16) .. + 3
+// of column l % 16. Every product accumulates its k steps in one ascending
+// chain, so a product's bits do not depend on the tiling.
+constexpr int kPad = 8;                                    // row padding of the LDS images
+constexpr int kW1Ld = kDInPad + kPad, kW2Ld = kDH + kPad, kXLd = kDInPad + kPad;
+constexpr int kTrThreads = 1024;                           // 16 waves, 16 units each
 
-struct GemmArgs {
-    const uint16_t *A;  // bf16
-    const uint16_t *B;  // bf16
-    int M, N, K, lda, ldb;
-    // epilogue
-    const float *bias;  // [N]            (kEpiBiasGelu)
-    float *Cf;          // [M][ldc] float (z for kEpiBiasGelu, C for kEpiStoreF32)
-    uint16_t *Cb;       // [M][ldc] bf16  (gelu(z) or dz)
-    const float *Zin;   // [M][ldc] float pre-activation (kEpiGeluGrad)
-    int ldc;
+__device__ __forceinline__ f32x4 mfma_bf16(const uint16_t *a, const uint16_t *b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+        __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(a)),
+        __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(b)), c, 0, 0, 0);
+}
+
+// A [64 Q or fewer rows][256] float matrix in registers: wave w's lane l holds,
+// for q < Q, the 4x4 block at rows 64 q + 4 w, columns 4 l. Whole rows per load
+// instruction: with lanes over rows 4 KiB apart the same loads took three
+// times as long (16,000 against 5,500 clocks per 256 KiB).
+template <int ROWS, int Q = (ROWS + 63) / 64>
+__device__ __forceinline__ void load_blocks(const float *__restrict__ w, f32x4 (&v)[Q][4]) {
+    const int k = 4 * (threadIdx.x >> 6), n = 4 * (threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (64 * q + k < ROWS)  // whole waves
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[q][r] = *reinterpret_cast<const f32x4 *>(w + (size_t)(64 * q + k + r) * kDH + n);
+}
+// LDS image of a transposed weight matrix: column n's bfloat16 k values in a
+// row of 512 bytes, its 16-byte chunk c (k = 8 c ..) at chunk c ^ (n's bits 3,
+// 2, 5, 4). So the transposing writes (lanes 4 columns apart, one k) and the
+// operand reads (16 consecutive columns, 4 chunks) both spread over all banks.
+constexpr int kWLd = kDH;
+__device__ __forceinline__ int w_at(int n, int chunk) {
+    return n * kWLd + ((chunk ^ ((n & 12) | (n >> 4 & 3))) << 3);
+}
+template <int ROWS, int Q = (ROWS + 63) / 64>
+__device__ __forceinline__ void put_transposed(const f32x4 (&v)[Q][4], uint16_t *dst) {
+    const int k = 4 * (threadIdx.x >> 6), n = 4 * (threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (64 * q + k < ROWS) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<uint2 *>(dst + w_at(n + i, (64 * q + k) >> 3) + (k & 4)) =
+                    make_uint2(f2bf2(v[q][0][i], v[q][1][i]), f2bf2(v[q][2][i], v[q][3][i]));
+        }
+}
+
+// The bfloat16 copy of W2 for the backward pass, from the blocks in registers:
+// row i by block i mod P, P the largest power of two up to the grid and 32.
+__device__ __forceinline__ void keep_w2(const f32x4 (&v)[kDH / 64][4], uint16_t *__restrict__ wb) {
+    const uint32_t P = 1u << (31 - __clz((int)min(gridDim.x, 32u)));
+    if (blockIdx.x >= P) return;
+    const int k = 4 * (threadIdx.x >> 6), n = 4 * (threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < kDH / 64; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (((uint32_t)(k + r) & (P - 1)) == blockIdx.x)  // 64 q is a multiple of P
+                *reinterpret_cast<uint2 *>(wb + (size_t)(64 * q + k + r) * kDH + n) =
+                    make_uint2(f2bf2(v[q][r][0], v[q][r][1]), f2bf2(v[q][r][2], v[q][r][3]));
+}
+
+// acc = A B over KS k steps: A rows [ROWS] and B columns (this wave's 16) in
+// LDS; B in the w_at layout or, with SWZ false, in rows of kW2Ld.
+template <int ROWS, int KS, bool SWZ>
+__device__ __forceinline__ void wave_product(const uint16_t *a, int lda, const uint16_t *b,
+                                             f32x4 (&acc)[ROWS / 16]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, kg = (lane >> 4) * 8;
+#pragma unroll
+    for (int i = 0; i < ROWS / 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < ROWS / 16; ++i)
+            acc[i] = mfma_bf16(a + (i * 16 + r16) * lda + ks * 32 + kg,
+                               b + (SWZ ? w_at(wave * 16 + r16, ks * 4 + (lane >> 4))
+                                        : (wave * 16 + r16) * kW2Ld + ks * 32 + kg),
+                               acc[i]);
+}
+
+struct ActPtrs {
+    uint16_t *xb, *h1, *h2, *dz2, *dz1, *wb;
+    float *z1, *z2;
 };
 
-constexpr int kBM = 64, kBN = 64, kBK = 32, kPad = 8;
+// z = acc + bias and h = bf16(gelu(z)) of this block's rows, to the cache and to LDS.
+template <int ROWS>
+__device__ __forceinline__ void hidden_epilogue(const f32x4 (&acc)[ROWS / 16], float bn, int row0, int batch, float *__restrict__ z, uint16_t *__restrict__ h,
+                                                uint16_t *s) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = wave * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < ROWS / 16; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = i * 16 + 4 * (lane >> 4) + r;
+            const float v = acc[i][r] + bn;
+            const uint16_t b = f2bf(gelu(v));
+            s[m * kW2Ld + n] = b;
+            if (row0 + m < batch) {
+                z[(size_t)(row0 + m) * kDH + n] = v;
+                h[(size_t)(row0 + m) * kDH + n] = b;
+            }
+        }
+}
 
-template <bool TA, bool TB, int EPI>
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
-    __shared__ uint16_t As[kBM][kBK + kPad];
-    __shared__ uint16_t Bs[kBN][kBK + kPad];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * kBM, n0 = blockIdx.x * kBN;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
+// Forward pass of ROWS batch rows: x -> z1, h1 -> z2, h2 -> out, keeping what
+// the backward pass reads (and bfloat16 copies of W2 and W3 as they are now).
+// Bound by latency and by what one CU can load (0.43 MB of float weights per
+// block): two weight matrices through LDS, the second one loaded while the
+// first product runs. A batch of 512: 12 us in one launch, where packing
+// launches, two 64x64-tile products with 2-byte loads and the output layer took
+// 45 us in five.
+template <int ROWS>
+__global__ void __launch_bounds__(kTrThreads) mlp_forward_kernel(const float *__restrict__ prm,
+                                                                 const float *__restrict__ x, int batch,
+                                                                 float *__restrict__ out, ActPtrs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t w[kDH * kWLd];
+    __shared__ __attribute__((aligned(16))) uint16_t s[ROWS * kW2Ld];  // the rows' x, then h1, then h2
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row0 = blockIdx.x * ROWS, rows = min(ROWS, batch - row0);
+    // what the later stages need, asked for before the first wait
+    const float bn1 = prm[kOffB1 + wave * 16 + (lane & 15)], bn2 = prm[kOffB2 + wave * 16 + (lane & 15)];
+    const float b30 = prm[kOffB3], b31 = prm[kOffB3 + 1];
+    const uint16_t w3v = f2bf(prm[kOffW3 + tid % (kDH * kDOut)]);
+    float w30[kDH / 64], w31[kDH / 64];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    for (int k0 = 0; k0 < g.K; k0 += kBK) {
-        // stage A (64 x 32) and B (32 x 64), k contiguous in LDS
-        if constexpr (!TA) {
-            const int r = tid >> 2, kc = (tid & 3) * 8;
-            const int m = m0 + r;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = k0 + kc + e;
-                As[r][kc + e] = (m < g.M && k < g.K) ? g.A[(size_t)m * g.lda + k] : (uint16_t)0;
-            }
-        } else {
-            const int kk = tid >> 3, mc = (tid & 7) * 8;
-            const int k = k0 + kk;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int m = m0 + mc + e;
-                As[mc + e][kk] = (m < g.M && k < g.K) ? g.A[(size_t)k * g.lda + m] : (uint16_t)0;
-            }
-        }
-        if constexpr (TB) {
-            const int r = tid >> 2, kc = (tid & 3) * 8;
-            const int n = n0 + r;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = k0 + kc + e;
-                Bs[r][kc + e] = (n < g.N && k < g.K) ? g.B[(size_t)n * g.ldb + k] : (uint16_t)0;
-            }
-        } else {
-            const int kk = tid >> 3, nc = (tid & 7) * 8;
-            const int k = k0 + kk;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int n = n0 + nc + e;
-                Bs[nc + e][kk] = (n < g.N && k < g.K) ? g.B[(size_t)k * g.ldb + n] : (uint16_t)0;
-            }
-        }
-        __syncthreads();
-        const int r16 = lane & 15, kg = (lane >> 4) * 8;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const u16x8 av = *reinterpret_cast<const u16x8 *>(&As[wm + i * 16 + r16][kg]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const u16x8 bv = *reinterpret_cast<const u16x8 *>(&Bs[wn + j * 16 + r16][kg]);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc[i][j], 0, 0, 0);
-            }
-        }
-        __syncthreads();
+    for (int q = 0; q < kDH / 64; ++q) {
+        w30[q] = bf2f(f2bf(prm[kOffW3 + 2 * (lane + 64 * q)]));
+        w31[q] = bf2f(f2bf(prm[kOffW3 + 2 * (lane + 64 * q) + 1]));
     }
-    // lane holds C[4*(lane/16) + r][lane % 16] of each 16x16 tile
+    {
+        f32x4 v[(kDInPad + 63) / 64][4];
+        load_blocks<kDInPad>(prm + kOffW1, v);
+        constexpr int kX = (ROWS * kXLd + kTrThreads - 1) / kTrThreads;
+        float xv[kX];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int q = 0; q < kX; ++q) {
+            // clamped, not skipped: all loads go out together
+            const int i = tid + kTrThreads * q, r = i / kXLd, k = i % kXLd;
+            const float e = x[(size_t)(row0 + min(r, rows - 1)) * kDIn + min(k, kDIn - 1)];
+            xv[q] = r < rows && k < kDIn ? e : 0.f;
+        }
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int q = 0; q < kX; ++q)
+            if (tid + kTrThreads * q < ROWS * kXLd) s[tid + kTrThreads * q] = f2bf(xv[q]);
+        put_transposed<kDInPad>(v, w);
+    }
+    __syncthreads();
+    f32x4 v2[kDH / 64][4];
+    load_blocks<kDH>(prm + kOffW2, v2);
+    for (int i = tid; i < rows * (kDInPad / 8); i += kTrThreads) {
+        const int r = i / (kDInPad / 8), c = i % (kDInPad / 8) * 8;
+        *reinterpret_cast<u16x8 *>(a.xb + (size_t)(row0 + r) * kDInPad + c) =
+            *reinterpret_cast<const u16x8 *>(s + r * kXLd + c);
+    }
+    f32x4 acc[ROWS / 16];
+    wave_product<ROWS, kDInPad / 32, true>(s, kXLd, w, acc);
+    __syncthreads();  // x and W1 are read
+    put_transposed<kDH>(v2, w);
+    keep_w2(v2, a.wb + kOffW2);
+    if (blockIdx.x == 0 && tid < kDH * kDOut) a.wb[kOffW3 + tid] = w3v;
+    hidden_epilogue<ROWS>(acc, bn1, row0, batch, a.z1, a.h1, s);
+    __syncthreads();
+    wave_product<ROWS, kDH / 32, true>(s, kW2Ld, w, acc);
+    __syncthreads();  // h1 is read
+    hidden_epilogue<ROWS>(acc, bn2, row0, batch, a.z2, a.h2, s);
+    __syncthreads();
+    // o[b][c] = sum_j h2[b][j] W3[j][c] + b3[c]; one wave per row
+    for (int r = wave; r < rows; r += kTrThreads / 64) {
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int q = 0; q < kDH / 64; ++q) {
+            const float h = bf2f(s[r * kW2Ld + lane + 64 * q]);
+            s0 += h * w30[q];
+            s1 += h * w31[q];
+        }
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        if (lane == 0) {
+            out[(size_t)(row0 + r) * 2] = s0 + b30;
+            out[(size_t)(row0 + r) * 2 + 1] = s1 + b31;
+        }
+    }
+}
+
+// Backward pass of ROWS batch rows: dz2 = bf16((dout W3^T) gelu'(z2)) and
+// dz1 = bf16((dz2 W2^T) gelu'(z1)); W2's rows are k-contiguous as they are. A
+// batch of 512: 7 us (25 us in two launches before).
+template <int ROWS>
+__global__ void __launch_bounds__(kTrThreads) mlp_back_rows_kernel(const float *__restrict__ dout, int batch,
+                                                                   ActPtrs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t w[kDH * kW2Ld];
+    __shared__ __attribute__((aligned(16))) uint16_t s[ROWS * kW2Ld];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row0 = blockIdx.x * ROWS;
+    constexpr int kCopies = kDH * kDH / 8 / kTrThreads;
+    u16x8 c[kCopies];
+#pragma unroll
+    for (int q = 0; q < kCopies; ++q)
+        c[q] = *reinterpret_cast<const u16x8 *>(a.wb + kOffW2 + (size_t)(tid + kTrThreads * q) * 8);
+    // every load of the block before its first use: this thread's z2 (unit j of
+    // rows tid / 256 + 4 q) and the z1 of its rows of the product
+    const int j = tid % kDH, n = wave * 16 + (lane & 15);
+    const float w30 = bf2f(a.wb[kOffW3 + 2 * j]), w31 = bf2f(a.wb[kOffW3 + 2 * j + 1]);
+    float z2[ROWS / 4], d0[ROWS / 4], d1[ROWS / 4], z1[ROWS / 16][4];
+#pragma unroll
+    for (int q = 0; q < ROWS / 4; ++q) {
+        const int b = min(row0 + tid / kDH + 4 * q, batch - 1);
+        z2[q] = a.z2[(size_t)b * kDH + j];
+        d0[q] = dout[(size_t)b * 2];
+        d1[q] = dout[(size_t)b * 2 + 1];
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS / 16; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            z1[i][r] = a.z1[(size_t)min(row0 + i * 16 + 4 * (lane >> 4) + r, batch - 1) * kDH + n];
+#pragma unroll
+    for (int q = 0; q < ROWS / 4; ++q) {
+        const int r = tid / kDH + 4 * q, b = row0 + r;
+        const float dh = d0[q] * w30 + d1[q] * w31;
+        const uint16_t d = b < batch ? f2bf(dh * gelu_grad(z2[q])) : (uint16_t)0;
+        if (b < batch) a.dz2[(size_t)b * kDH + j] = d;
+        s[r * kW2Ld + j] = d;
+    }
+#pragma unroll
+    for (int q = 0; q < kCopies; ++q) {
+        const int i = (tid + kTrThreads * q) * 8;
+        *reinterpret_cast<u16x8 *>(w + (i / kDH) * kW2Ld + i % kDH) = c[q];
+    }
+    __syncthreads();
+    f32x4 acc[ROWS / 16];
+    wave_product<ROWS, kDH / 32, false>(s, kW2Ld, w, acc);
+#pragma unroll
+    for (int i = 0; i < ROWS / 16; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int b = row0 + i * 16 + 4 * (lane >> 4) + r;
+            if (b < batch) a.dz1[(size_t)b * kDH + n] = f2bf(acc[i][r] * gelu_grad(z1[i][r]));
+        }
+}
+
+// Sums over the batch, one launch. Blocks [0, 64): 32x32 tiles of gW2 = h1^T
+// dz2; [64, 104): of gW1 = xb^T dz1; [104, 112): gb2, [112, 120): gb1, 32
+// columns each; [120, 128): 32 rows of gW3 = h2^T dout (the first also gb3). A
+// batch of 512: 6.5 us (64 us in four launches before, on 28 blocks of 64x64).
+constexpr int kGwTile = 32, kGwK = 256, kGwLd = kGwK + kPad;
+constexpr int kGwBlocks2 = (kDH / kGwTile) * (kDH / kGwTile), kGwBlocks1 = (kDInPad / kGwTile) * (kDH / kGwTile);
+constexpr int kSumBlocks = kDH / 32;
+
+// The part of one operand [k][cols] for a tile: thread t (of 128) takes 8 of
+// the tile's 32 columns and, per step, 4 consecutive k.
+struct GwOperand {
+    const uint16_t *p;
+    int ld;
+    __device__ __forceinline__ void load(int k0, int batch, u16x8 (&v)[kGwK / 128][4]) const {
+        const int t = threadIdx.x & 127, c = (t & 3) * 8, kr = (t >> 2) * 4;
+#pragma unroll
+        for (int q = 0; q < kGwK / 128; ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-                const int n = n0 + wn + j * 16 + (lane & 15);
-                if (m >= g.M || n >= g.N) continue;
-                const float v = acc[i][j][r];
-                const size_t o = (size_t)m * g.ldc + n;
-                if constexpr (EPI == kEpiBiasGelu) {
-                    const float z = v + g.bias[n];
-                    g.Cf[o] = z;
-                    g.Cb[o] = f2bf(gelu(z));
-                } else if constexpr (EPI == kEpiStoreF32) {
-                    g.Cf[o] = v;
-                } else {
-                    g.Cb[o] = f2bf(v * gelu_grad(g.Zin[o]));
-                }
+                const int k = k0 + 128 * q + kr + r;
+                v[q][r] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                if (k < batch) v[q][r] = *reinterpret_cast<const u16x8 *>(p + (size_t)k * ld + c);
             }
-}
-
-template <bool TA, bool TB, int EPI>
-static int gemm(const GemmArgs &g, hipStream_t st) {
-    const dim3 grid((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM);
-    hipLaunchKernelGGL((gemm_bf16_kernel<TA, TB, EPI>), grid, dim3(256), 0, st, g);
-    GQ_LAUNCH_CHECK();
-    return GQAOA_OK;
-}
-
-// ---- small kernels -----------------------------------------------------------------
-// x (float [B][131]) -> bf16 [B][160] zero padded.
-__global__ void pack_inputs_kernel(const float *__restrict__ x, int batch, uint16_t *__restrict__ xb) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)batch * kDInPad) return;
-    const int b = (int)(i / kDInPad), c = (int)(i % kDInPad);
-    xb[i] = c < kDIn ? f2bf(x[(size_t)b * kDIn + c]) : (uint16_t)0;
-}
-
-// bf16 copies of W1, W2, W3 (rows 131..159 of W1 are zero in the master copy).
-__global__ void pack_weights_kernel(const float *__restrict__ prm, uint16_t *__restrict__ wb) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kNParams) wb[i] = f2bf(prm[i]);
-}
-
-// o[b][c] = sum_j h2[b][j] W3[j][c] + b3[c]; one wave per row.
-__global__ void out_layer_kernel(const uint16_t *__restrict__ h2, const uint16_t *__restrict__ w3b,
-                                 const float *__restrict__ b3, int batch, float *__restrict__ out) {
-    const int row = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= batch) return;
-    float s0 = 0.f, s1 = 0.f;
-    for (int j = lane; j < kDH; j += 64) {
-        const float h = bf2f(h2[(size_t)row * kDH + j]);
-        s0 += h * bf2f(w3b[j * 2]);
-        s1 += h * bf2f(w3b[j * 2 + 1]);
     }
-    s0 = wave_sum(s0);
-    s1 = wave_sum(s1);
-    if (lane == 0) {
-        out[(size_t)row * 2] = s0 + b3[0];
-        out[(size_t)row * 2 + 1] = s1 + b3[1];
+    __device__ __forceinline__ void put(const u16x8 (&v)[kGwK / 128][4], uint16_t *dst) const {
+        const int t = threadIdx.x & 127, c = (t & 3) * 8, kr = (t >> 2) * 4;
+#pragma unroll
+        for (int q = 0; q < kGwK / 128; ++q)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                *reinterpret_cast<uint2 *>(dst + (c + e) * kGwLd + 128 * q + kr) =
+                    make_uint2(v[q][0][e] | (uint32_t)v[q][1][e] << 16, v[q][2][e] | (uint32_t)v[q][3][e] << 16);
     }
-}
+};
 
-// dz2[b][j] = bf16((sum_c dout[b][c] W3[j][c]) * gelu'(z2[b][j])).
-__global__ void out_backward_kernel(const float *__restrict__ dout, const uint16_t *__restrict__ w3b,
-                                    const float *__restrict__ z2, int batch, uint16_t *__restrict__ dz2) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)batch * kDH) return;
-    const int b = (int)(i / kDH), j = (int)(i % kDH);
-    const float dh = dout[(size_t)b * 2] * bf2f(w3b[j * 2]) + dout[(size_t)b * 2 + 1] * bf2f(w3b[j * 2 + 1]);
-    dz2[i] = f2bf(dh * gelu_grad(z2[i]));
-}
-
-// Column sums over the batch, fixed order: one block per column group.
-//   mode 0: g[c] = sum_b bf16 dz[b][c]                 (bias gradients)
-//   mode 1: gW3[j][c] = sum_b h2[b][j] dout[b][c], gb3 (output layer)
-__global__ void __launch_bounds__(256) colsum_bf16_kernel(const uint16_t *__restrict__ dz, int batch,
-                                                         int ncol, float *__restrict__ g) {
-    __shared__ double red[4];
-    const int c = blockIdx.x;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < batch; b += 256) s += bf2f(dz[(size_t)b * ncol + c]);
-    double v[1] = {s};
-    block_sum<1, 256>(v, red);
-    if (threadIdx.x == 0) g[c] = (float)v[0];
-}
-
-__global__ void __launch_bounds__(256) out_grad_kernel(const uint16_t *__restrict__ h2,
-                                                       const float *__restrict__ dout, int batch,
-                                                       float *__restrict__ gW3, float *__restrict__ gb3) {
-    __shared__ double red[8];
-    const int j = blockIdx.x;  // 0..255 -> W3 row; 256 -> bias
-    double s0 = 0.0, s1 = 0.0;
-    for (int b = threadIdx.x; b < batch; b += 256) {
-        const double h = j < kDH ? (double)bf2f(h2[(size_t)b * kDH + j]) : 1.0;
-        s0 += h * dout[(size_t)b * 2];
-        s1 += h * dout[(size_t)b * 2 + 1];
+// g[c] (and, with dout, both outputs) of 32 columns: 64 row groups of 4
+// threads, 8 columns each; double sums in a fixed order.
+template <bool OUT>
+__device__ __forceinline__ void column_sums(const uint16_t *__restrict__ src, const float *__restrict__ dout,
+                                            int batch, int c0, float *__restrict__ g, double *red) {
+    const int tid = threadIdx.x, c = c0 + (tid & 3) * 8, rg = tid >> 2;
+    constexpr int NO = OUT ? 2 : 1;
+    double s[8][NO];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int o = 0; o < NO; ++o) s[e][o] = 0.0;
+    for (int b = rg; b < batch; b += 64) {
+        const u16x8 v = *reinterpret_cast<const u16x8 *>(src + (size_t)b * kDH + c);
+        double d[NO];
+#pragma unroll
+        for (int o = 0; o < NO; ++o) d[o] = OUT ? (double)dout[(size_t)b * 2 + o] : 1.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int o = 0; o < NO; ++o) s[e][o] += (double)bf2f(v[e]) * d[o];
     }
-    double v[2] = {s0, s1};
-    block_sum<2, 256>(v, red);
-    if (threadIdx.x == 0) {
-        if (j < kDH) {
-            gW3[j * 2] = (float)v[0];
-            gW3[j * 2 + 1] = (float)v[1];
-        } else {
-            gb3[0] = (float)v[0];
-            gb3[1] = (float)v[1];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[rg * 33 + (tid & 3) * 8 + e] = s[e][o];
+        __syncthreads();
+        if (tid < 32) {
+            double t = 0.0;
+            for (int r = 0; r < 64; ++r) t += red[r * 33 + tid];
+            g[(c0 + tid) * NO + o] = (float)t;
         }
     }
+}
+
+__global__ void __launch_bounds__(256) mlp_back_weights_kernel(const float *__restrict__ dout, int batch, ActPtrs a,
+                                                               float *__restrict__ grads) {
+    __shared__ __attribute__((aligned(16))) uint16_t As[kGwTile * kGwLd];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[kGwTile * kGwLd];
+    __shared__ double red[64 * 33];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int blk = blockIdx.x;
+    if (blk >= kGwBlocks2 + kGwBlocks1) {
+        blk -= kGwBlocks2 + kGwBlocks1;
+        const int c0 = blk % kSumBlocks * 32;
+        if (blk < kSumBlocks) {
+            column_sums<false>(a.dz2, nullptr, batch, c0, grads + kOffB2, red);
+        } else if (blk < 2 * kSumBlocks) {
+            column_sums<false>(a.dz1, nullptr, batch, c0, grads + kOffB1, red);
+        } else {
+            column_sums<true>(a.h2, dout, batch, c0, grads + kOffW3, red);
+            if (c0 == 0) {
+                double v[2] = {0.0, 0.0};
+                for (int b = tid; b < batch; b += 256) {
+                    v[0] += dout[(size_t)b * 2];
+                    v[1] += dout[(size_t)b * 2 + 1];
+                }
+                __syncthreads();
+                block_sum<2, 256>(v, red);
+                if (tid == 0) {
+                    grads[kOffB3] = (float)v[0];
+                    grads[kOffB3 + 1] = (float)v[1];
+                }
+            }
+        }
+        return;
+    }
+    const bool second = blk < kGwBlocks2;
+    if (!second) blk -= kGwBlocks2;
+    const int m0 = blk / (kDH / kGwTile) * kGwTile, n0 = blk % (kDH / kGwTile) * kGwTile;
+    // threads 0..127 stage A, 128..255 B
+    const bool isA = tid < 128;
+    const GwOperand op = isA ? (second ? GwOperand{a.h1 + m0, kDH} : GwOperand{a.xb + m0, kDInPad})
+                             : GwOperand{(second ? a.dz2 : a.dz1) + n0, kDH};
+    uint16_t *dst = isA ? As : Bs;
+    u16x8 v[kGwK / 128][4];
+    op.load(0, batch, v);
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    const int r16 = lane & 15, kg = (lane >> 4) * 8;
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+    for (int k0 = 0; k0 < batch; k0 += kGwK) {
+        op.put(v, dst);
+        __syncthreads();
+        if (k0 + kGwK < batch) op.load(k0 + kGwK, batch, v);
+        const int steps = min(kGwK / 32, (batch - k0 + 31) / 32);
+        for (int ks = 0; ks < steps; ++ks)
+            acc = mfma_bf16(As + (wm + r16) * kGwLd + ks * 32 + kg, Bs + (wn + r16) * kGwLd + ks * 32 + kg, acc);
+        __syncthreads();
+    }
+    float *out = grads + (second ? kOffW2 : kOffW1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(size_t)(m0 + wm + 4 * (lane >> 4) + r) * kDH + n0 + wn + r16] = acc[r];
 }
 
 // Loss of the angle regression and its gradient with respect to the raw outputs:
@@ -323,83 +507,49 @@ __global__ void features_kernel(const unsigned long long *__restrict__ hists, in
 }
 
 // ---- host entry points ---------------------------------------------------------------
-int run_mlp_forward(const float *prm, int batch, const float *x, float *out, void *act, hipStream_t st) {
+static ActPtrs act_ptrs(void *act, int batch) {
     const ActLayout L = act_layout(batch);
     char *a = reinterpret_cast<char *>(act);
-    uint16_t *xb = reinterpret_cast<uint16_t *>(a + L.xb);
-    uint16_t *wb = reinterpret_cast<uint16_t *>(a + L.wb);
-    const size_t nx = (size_t)batch * kDInPad;
-    hipLaunchKernelGGL(pack_inputs_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, x, batch, xb);
-    GQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)((kNParams + 255) / 256)), dim3(256), 0, st, prm, wb);
-    GQ_LAUNCH_CHECK();
-    GemmArgs g{};
-    g.A = xb; g.lda = kDInPad;
-    g.B = wb + kOffW1; g.ldb = kDH;
-    g.M = batch; g.N = kDH; g.K = kDInPad;
-    g.bias = prm + kOffB1;
-    g.Cf = reinterpret_cast<float *>(a + L.z1);
-    g.Cb = reinterpret_cast<uint16_t *>(a + L.h1);
-    g.ldc = kDH;
-    int s = gemm<false, false, kEpiBiasGelu>(g, st);
+    auto u16 = [&](size_t o) { return reinterpret_cast<uint16_t *>(a + o); };
+    return ActPtrs{u16(L.xb),  u16(L.h1), u16(L.h2), u16(L.dz), u16(L.dz1), u16(L.wb),
+                   reinterpret_cast<float *>(a + L.z1), reinterpret_cast<float *>(a + L.z2)};
+}
+
+// Rows per block: 16 until that gives every CU a block, then 32, which halves
+// the reads of the weights (L2) per row.
+template <typename F>
+static void by_rows(int batch, const DeviceInfo &dev, F f) {
+    if (batch <= 16 * dev.num_cus) f(std::integral_constant<int, 16>{}, (batch + 15) / 16);
+    else f(std::integral_constant<int, 32>{}, (batch + 31) / 32);
+}
+
+int run_mlp_forward(const float *prm, int batch, const float *x, float *out, void *act, hipStream_t st) {
+    DeviceInfo dev;
+    int s = device_info(&dev);
     if (s) return s;
-    g.A = reinterpret_cast<uint16_t *>(a + L.h1); g.lda = kDH;
-    g.B = wb + kOffW2; g.ldb = kDH;
-    g.K = kDH;
-    g.bias = prm + kOffB2;
-    g.Cf = reinterpret_cast<float *>(a + L.z2);
-    g.Cb = reinterpret_cast<uint16_t *>(a + L.h2);
-    if ((s = gemm<false, false, kEpiBiasGelu>(g, st))) return s;
-    hipLaunchKernelGGL(out_layer_kernel, dim3((unsigned)((batch + 3) / 4)), dim3(256), 0, st,
-                       reinterpret_cast<uint16_t *>(a + L.h2), wb + kOffW3, prm + kOffB3, batch, out);
+    const ActPtrs a = act_ptrs(act, batch);
+    by_rows(batch, dev, [&](auto rows, int blocks) {
+        hipLaunchKernelGGL(mlp_forward_kernel<decltype(rows)::value>, dim3(blocks), dim3(kTrThreads), 0, st, prm, x,
+                           batch, out, a);
+    });
     GQ_LAUNCH_CHECK();
     return GQAOA_OK;
 }
 
 int run_mlp_backward(const float *prm, int batch, const void *act, const float *dout, float *grads,
                      hipStream_t st) {
-    (void)prm;
-    const ActLayout L = act_layout(batch);
-    char *a = const_cast<char *>(reinterpret_cast<const char *>(act));
-    const uint16_t *wb = reinterpret_cast<uint16_t *>(a + L.wb);
-    const uint16_t *h1 = reinterpret_cast<uint16_t *>(a + L.h1);
-    const uint16_t *h2 = reinterpret_cast<uint16_t *>(a + L.h2);
-    uint16_t *dz2 = reinterpret_cast<uint16_t *>(a + L.dz);
-    uint16_t *dz1 = reinterpret_cast<uint16_t *>(a + L.dz1);
-    const uint16_t *xb = reinterpret_cast<uint16_t *>(a + L.xb);
-    // output layer: gW3, gb3, then dz2
-    hipLaunchKernelGGL(out_grad_kernel, dim3(kDH + 1), dim3(256), 0, st, h2, dout, batch, grads + kOffW3, grads + kOffB3);
-    GQ_LAUNCH_CHECK();
-    const size_t nh = (size_t)batch * kDH;
-    hipLaunchKernelGGL(out_backward_kernel, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, st, dout,
-                       wb + kOffW3, reinterpret_cast<const float *>(a + L.z2), batch, dz2);
-    GQ_LAUNCH_CHECK();
-    // gW2 = h1^T dz2  (M = 256, N = 256, K = batch)
-    GemmArgs g{};
-    g.A = h1; g.lda = kDH;
-    g.B = dz2; g.ldb = kDH;
-    g.M = kDH; g.N = kDH; g.K = batch;
-    g.Cf = grads + kOffW2; g.ldc = kDH;
-    int s = gemm<true, false, kEpiStoreF32>(g, st);
+    (void)prm;  // the weights of the forward pass, kept in act
+    DeviceInfo dev;
+    int s = device_info(&dev);
     if (s) return s;
-    hipLaunchKernelGGL(colsum_bf16_kernel, dim3(kDH), dim3(256), 0, st, dz2, batch, kDH, grads + kOffB2);
+    const ActPtrs a = act_ptrs(const_cast<void *>(act), batch);
+    by_rows(batch, dev, [&](auto rows, int blocks) {
+        hipLaunchKernelGGL(mlp_back_rows_kernel<decltype(rows)::value>, dim3(blocks), dim3(kTrThreads), 0, st, dout,
+                           batch, a);
+    });
     GQ_LAUNCH_CHECK();
-    // dz1 = bf16((dz2 W2^T) * gelu'(z1))  (M = batch, N = 256, K = 256)
-    GemmArgs d{};
-    d.A = dz2; d.lda = kDH;
-    d.B = wb + kOffW2; d.ldb = kDH;   // W2[i][j] read as B(k=j, n=i)
-    d.M = batch; d.N = kDH; d.K = kDH;
-    d.Zin = reinterpret_cast<const float *>(a + L.z1);
-    d.Cb = dz1; d.ldc = kDH;
-    if ((s = gemm<false, true, kEpiGeluGrad>(d, st))) return s;
-    // gW1 = xb^T dz1 (M = 160, N = 256, K = batch)
-    GemmArgs w{};
-    w.A = xb; w.lda = kDInPad;
-    w.B = dz1; w.ldb = kDH;
-    w.M = kDInPad; w.N = kDH; w.K = batch;
-    w.Cf = grads + kOffW1; w.ldc = kDH;
-    if ((s = gemm<true, false, kEpiStoreF32>(w, st))) return s;
-    hipLaunchKernelGGL(colsum_bf16_kernel, dim3(kDH), dim3(256), 0, st, dz1, batch, kDH, grads + kOffB1);
+    hipLaunchKernelGGL(mlp_back_weights_kernel, dim3(kGwBlocks2 + kGwBlocks1 + 3 * kSumBlocks), dim3(256), 0, st, dout,
+                       batch, a, grads);
     GQ_LAUNCH_CHECK();
     return GQAOA_OK;
 }
@@ -440,8 +590,7 @@ int run_mlp_features(int batch, const uint64_t *hists, int hist_stride, const in
 // leaves registers. The MFMA k-order equals the training GEMM's, so h1 and
 // h2 are bit-identical to the training forward; only the output layer's
 // 256-term sum is taken in another order.
-constexpr int kInfThreads = 512, kInfRows = 128, kWPad = 8;
-constexpr int kW1Ld = kDInPad + kWPad, kW2Ld = kDH + kWPad, kXLd = kDInPad + kWPad;
+constexpr int kInfThreads = 512, kInfRows = 128;
 
 constexpr size_t kW1Image = (size_t)kDH * kW1Ld * 2, kW2Image = (size_t)kDH * kW2Ld * 2;  // bytes
 

@@ -167,3 +167,26 @@ def test_features_match_oracle():
     for i in range(2):
         xr = ref.features(hist[i, :ms[i] + 1], int(ns[i]), ms[i] / ns[i], int(ps[i]))
         np.testing.assert_allclose(x[i], xr, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("B", [15, 16, 17, 255, 257, 513, 4100])
+def test_forward_backward_at_block_edges(B):
+    """Batches around the 16-row blocks and the 256-row steps of the weight
+    gradients, and one on 32-row blocks (more than 16 rows per CU): the
+    oracle's bars, as above."""
+    log(f"mlp training B={B}")
+    test_forward_backward_vs_oracle(B)
+
+
+def test_training_forward_independent_of_the_split():
+    """Every product accumulates its k steps in one order, so a row's outputs
+    have the same bits on 32-row blocks (8200 rows), on 16-row blocks and in a
+    batch of its own."""
+    torch = need_gpu()
+    prm = torch.tensor(_pack(_params32(3)), device="cuda")
+    rng = np.random.Generator(np.random.PCG64(77))
+    x = torch.tensor((np.abs(rng.normal(size=(8200, 131))) * 0.2).astype(np.float32), device="cuda")
+    whole, _ = g.gqaoa_mlp_forward(prm, x)
+    for a, b in ((0, 1), (0, 500), (3, 20), (8191, 8200)):
+        part, _ = g.gqaoa_mlp_forward(prm, x[a:b].contiguous())
+        assert torch.equal(part, whole[a:b]), (a, b)
