@@ -467,25 +467,20 @@ int scan_launch_bucket(int bucket, const TileChoice &tc, const DeviceInfo &dev, 
 
 static int tune_bucket(int bucket, const DeviceInfo &dev, const ScanArgs &a, unsigned int *counter,
                        hipStream_t st, TileChoice *out) {
-    const std::string plain_key = std::string(dev.arch) + ":k" + std::to_string(kBuckets[bucket]) + ":t" +
-                                  std::to_string(a.ntiles) + ":p" +
-                                  std::to_string(a.p_list[a.num_p - 1] > 16 ? 64 : 16);
-    const std::string key = plain_key + (a.first_p ? ":x" : "");
+    const std::string key = std::string(dev.arch) + ":k" + std::to_string(kBuckets[bucket]) + ":t" +
+                            std::to_string(a.ntiles) + ":p" + std::to_string(a.p_list[a.num_p - 1] > 16 ? 64 : 16);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load_locked();
         auto it = g_tune.find(key);
-        if (it == g_tune.end() && a.first_p) it = g_tune.find(plain_key);  // same loop, plus a readout
         if (it != g_tune.end()) {
             *out = it->second;
             return GQAOA_OK;
         }
     }
-    // time a prefix of the queue that fills the device a few times over; the
-    // crossing form's items can run thousands of rounds, so its prefix is a
-    // single fill of the device
+    // time a prefix of the items that fills the device a few times over
     ScanArgs t = a;
-    t.total_items = std::min<unsigned>(a.total_items, (unsigned)dev.num_cus * (a.first_p ? 8 : 64));
+    t.total_items = std::min<unsigned>(a.total_items, (unsigned)dev.num_cus * 64);
     const int waves_c[] = {1, 2, 4};
     const int bpc_c[] = {2, 4, 8, 16};
     hipEvent_t e0, e1;
@@ -601,6 +596,17 @@ int scan_choose_tile(int bucket, const DeviceInfo &dev, const ScanArgs &a, unsig
                      const int32_t *tile, hipStream_t st, TileChoice *out) {
     if (tile) {
         *out = TileChoice{tile[0], tile[1]};
+        return GQAOA_OK;
+    }
+    if (a.first_p) {
+        // The crossing form takes its items from a queue, so the more waves the
+        // better as long as they are resident (the rest find the queue empty):
+        // at 2 or more waves per SIMD every shape is within 2% (128 unsatisfiable
+        // instances, 360 x 181 pairs: 12.5 ms), at one wave 22 ms. Timing a
+        // prefix of it cannot tell: items run from one round to their cap, and
+        // a prefix of one fill chose one wave per SIMD. Few items go out as
+        // blocks of one wave, which spread over all CUs.
+        *out = a.total_items < 8u * (unsigned)dev.num_cus ? TileChoice{1, 32} : TileChoice{4, 8};
         return GQAOA_OK;
     }
     return tune_bucket(bucket, dev, a, counter, st, out);
