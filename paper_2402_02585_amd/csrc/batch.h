@@ -19,7 +19,8 @@ struct ScanSlot {          // one instance inside a bucket, in queue order
     int32_t K;             // occupied levels
     int32_t t_idx;         // 0 when the target level is occupied (it comes first among them), else -1
     int32_t pmax;          // rounds to run for this instance
-    int32_t pad[3];
+    int32_t unit;          // the histogram's counts sum to 2^n
+    int32_t pad[2];
 };
 
 struct ScanArgs {

@@ -228,6 +228,29 @@ __device__ __forceinline__ void scan_table(const ScanArgs &a, const ScanSlot &sl
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// How far a round can bring a state to the target level. With x^2 = P = <psi|Pi_t|psi>
+// and theta = asin x, the phase leaves theta as it is, and the mixer, a unitary
+// M, moves the angle between psi and the target state |t> by at most the angle
+// between |t> and M^dagger |t>: cos d = |<t|M|t>| = |1 + (e^{-i beta} - 1) w_t|, so
+// sin d = |e^{-i beta} - 1| sqrt(w_t (1 - w_t)). A lane whose theta + r d stays
+// below asin sqrt(S) with r rounds left cannot cross any more. The margins
+// (1% and 1e-6 per round of P, 1e-4) are wide of what float32 rounding moves.
+constexpr int kReachEvery = 16;  // rounds between the checks (under 1% of their arithmetic)
+struct ScanReach {
+    float th, d, rel;
+    __device__ __forceinline__ ScanReach(const ScanSlot &sl, float S, float w0, float mr, float mi) {
+        th = sl.unit ? asinf(sqrtf(fminf(fmaxf(S, 0.f), 1.f))) : 0.f;  // th = 0: always within reach
+        d = asinf(fminf(sqrtf(w0 * (1.f - w0) * (mr * mr + mi * mi)), 1.f));
+        rel = 0.99f - 1e-6f * (float)sl.pmax;
+    }
+    // P after a round with r more to come
+    __device__ __forceinline__ bool out_of_reach(float P, int r) const {
+        const float t = th - (float)r * d;
+        const float s = sinf(t);
+        return t > 0.f && P < rel * s * s - 1e-4f;
+    }
+};
+
 // The rounds of one item for this lane's beta (mixer e^{-i beta} - 1 = mr + i mi).
 template <int KMAX, bool CROSS>
 __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &sl, const ScanItem &it, int lane,
@@ -258,8 +281,11 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
     float cr = 0.f, ci = 0.f;
     int q = 0;
     int found = 0;
-    const int pmax = sl.pmax;
+    int pmax = sl.pmax;
     int next_p = CROSS ? 0 : a.p_list[0];   // next readout round, kept in a register
+    const ScanReach reach(sl, CROSS ? a.threshold : 0.f, w0, mr, mi);
+    if constexpr (CROSS)
+        if (__ballot(active && !reach.out_of_reach(w0, pmax)) == 0) pmax = 0;  // wave-uniform
     for (int j = 1; j <= pmax; ++j) {
         // Small tables stay in registers across rounds; larger ones are
         // re-read from LDS (broadcast) each round to bound register use.
@@ -286,7 +312,9 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
             const float b0r = pr[0] + cr, b0i = pi[0] + ci;
             const float P = w0 * (b0r * b0r + b0i * b0i);
             if (found == 0 && P >= a.threshold) found = j;
-            if (__ballot(active && found == 0) == 0) break;  // wave-uniform
+            bool live = active && found == 0;
+            if (j % kReachEvery == 0) live = live && !reach.out_of_reach(P, pmax - j);
+            if (__ballot(live) == 0) break;  // wave-uniform
         } else if (j == next_p) {
             float E = 0.f;
 #pragma unroll
@@ -549,7 +577,7 @@ int scan_host_tables(int num_inst, const int32_t *n_host, const int32_t *m_host,
                      int hist_stride, const int32_t *target_host, const int32_t *pmax_host, int pmax_all,
                      ScanHost *out) {
     // compact the occupied levels of every instance
-    std::vector<int32_t> K(num_inst), tidx(num_inst), off(num_inst);
+    std::vector<int32_t> K(num_inst), tidx(num_inst), off(num_inst), unit(num_inst);
     out->lev.clear();
     out->w.clear();
     for (int i = 0; i < num_inst; ++i) {
@@ -558,18 +586,22 @@ int scan_host_tables(int num_inst, const int32_t *n_host, const int32_t *m_host,
         off[i] = (int32_t)out->lev.size();
         tidx[i] = -1;
         const double invN = std::ldexp(1.0, -n_host[i]);
+        uint64_t total = 0;
         // the target level (when occupied) first, then the others in level order
         if (t <= m_host[i] && h[t]) {
             tidx[i] = 0;
+            total += h[t];
             out->lev.push_back(t);
             out->w.push_back((float)((double)h[t] * invN));
         }
         for (int k = 0; k <= m_host[i]; ++k)
             if (h[k] && k != t) {
+                total += h[k];
                 out->lev.push_back(k);
                 out->w.push_back((float)((double)h[k] * invN));
             }
         K[i] = (int32_t)out->lev.size() - off[i];
+        unit[i] = n_host[i] < 64 && total == 1ull << n_host[i];
         if (K[i] > kScanMaxK) return fail(GQAOA_ERANGE, "instance %d has %d occupied levels (max %d)", i, K[i], kScanMaxK);
     }
     // buckets, each ordered by K descending
@@ -586,7 +618,8 @@ int scan_host_tables(int num_inst, const int32_t *n_host, const int32_t *m_host,
         std::stable_sort(mb.begin(), mb.end(), [&](int x, int y) { return K[x] > K[y]; });
         out->bucket_first[bk] = (int)out->slots.size();
         for (int i : mb)
-            out->slots.push_back(ScanSlot{i, off[i], K[i], tidx[i], pmax_host ? pmax_host[i] : pmax_all, {0, 0, 0}});
+            out->slots.push_back(
+                ScanSlot{i, off[i], K[i], tidx[i], pmax_host ? pmax_host[i] : pmax_all, unit[i], {0, 0}});
     }
     out->bucket_first[kNumBuckets] = (int)out->slots.size();
     return GQAOA_OK;

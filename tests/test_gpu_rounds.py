@@ -196,3 +196,33 @@ def test_per_instance_caps():
     capped = g.gqaoa_scan_crossing(ns, ms, hd, gb, gg, caps, 0.5).cpu().numpy()
     for k in range(len(ns)):
         assert (capped[k] == np.where(full[k] <= caps[k], full[k], 0)).all()
+
+
+@pytest.mark.parametrize("S", [1e-3, 0.25, 0.5, 0.75, 0.95, 1.0])
+@pytest.mark.parametrize("unit", [True, False])
+def test_crossing_caps_only_cut(S, unit):
+    """A smaller round cap gives the larger cap's crossings up to it and 0
+    elsewhere, whatever the wave skips because the target is out of reach in
+    the rounds left (caps from a fraction of that reach to several times it;
+    with counts that do not sum to 2^n nothing is skipped). Exact: the rounds
+    are the same arithmetic."""
+    need_gpu()
+    rng = np.random.Generator(np.random.PCG64(71))
+    I, L = 12, 40
+    ns = rng.integers(8, 17, I).astype(np.int32)
+    h = np.zeros((I, L), dtype=np.int64)
+    for i in range(I):
+        N, K = 1 << int(ns[i]), int(rng.integers(2, L))
+        h[i, :K] = np.maximum(rng.multinomial(N - 4 * K, rng.dirichlet(np.ones(K))), 0)
+        h[i, 0] = 1 + i % 3
+        h[i, 1] += N - h[i].sum() + (0 if unit else 5)
+    ms = np.full(I, L - 1, dtype=np.int32)
+    b, gm = np.linspace(0, 2 * np.pi, 70, endpoint=False), np.linspace(0.0, np.pi, 24)
+    P = h[:, 0] / np.exp2(ns.astype(float))
+    full = g.gqaoa_scan_crossing(ns, ms, h, b, gm, np.ceil(6 / np.sqrt(P)).astype(np.int32), S).cpu().numpy()
+    for f in (0.1, 0.5, 1.0, 2.0, 4.0):
+        cap = np.ceil(f / np.sqrt(P)).astype(np.int32)
+        got = g.gqaoa_scan_crossing(ns, ms, h, b, gm, cap, S).cpu().numpy()
+        want = np.where(full <= cap[:, None, None], full, 0)
+        assert np.array_equal(got, want), (S, f)
+    log(f"crossing caps S={S} unit={unit}: {(full > 0).mean():.4f} of the cells cross")
