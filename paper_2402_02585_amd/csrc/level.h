@@ -12,12 +12,13 @@ constexpr int kLevelInlineRounds = 112;  // rounds whose angles travel as kernel
 
 struct LevelEvolve {
     int n, m, p, target;
+    int init_uniform;
     const uint8_t *cost;
-    void *psi;              // [2^n] complex128, written
+    void *psi;              // [2^n] complex128: the initial state unless init_uniform, the final one
     const double *beta_host, *gamma_host;  // eager calls: p host angles each
     double *angles_dev;     // beta[p], gamma[p]: read by captured calls, scratch of long eager ones
-    uint32_t *rows;         // [kLevelMaxRows][256] counts (n > kLevelFusedMaxN)
-    void *table;            // [256] complex128 (n > kLevelFusedMaxN)
+    void *rows;             // [kLevelMaxRows + 1][256][4] doubles: counts or level sums of the blocks
+    void *table;            // [512] complex128: the final level table
     double *readout;        // [p+1][3]
 };
 

@@ -357,9 +357,9 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
 }
 
 // ---- resident evolution of small states ------------------------------------------
-// A state of at most 2^14 (complex64) or 2^13 (complex128) amplitudes fits the
-// registers of one block, so all p rounds of one instance run in a single
-// launch: each thread owns the PER consecutive amplitudes z = tid PER + i in
+// A complex64 state of at most 2^14 amplitudes fits the registers of one
+// block, so all p rounds of one instance run in a single launch: each thread
+// owns the PER consecutive amplitudes z = tid PER + i in
 // every round, with their costs packed four to a register. Round j: add
 // delta_{j-1} (the previous mixer, applied lazily), read out psi_{j-1},
 // apply the phase from the round's table (staged in LDS, the next round's
@@ -476,45 +476,44 @@ __global__ void __launch_bounds__(THREADS) sv_resident_kernel(ResArgs a) {
     }
 }
 
-// Largest n of the resident form: the state's registers in one block.
-static int resident_max_n(int dtype) { return dtype == GQAOA_C64 ? 14 : 13; }
+// complex64 only (complex128 takes the level form at these sizes); the largest
+// n is what the registers of one block hold.
+constexpr int kResidentMaxN = 14;
 
 static bool resident_ok(int n, int dtype, int p) {
-    if (p < 1 || n > resident_max_n(dtype)) return false;
+    if (dtype != GQAOA_C64 || p < 1 || n > kResidentMaxN) return false;
     const char *e = getenv("GQAOA_SV_RESIDENT");  // "0": always stream (for comparisons)
     return !(e && e[0] == '0');
 }
 
 typedef void (*ResFn)(ResArgs);
-template <typename T>
 static ResFn resident_fn(int n, int *threads) {
-    // one wave of 2^n / 64 amplitudes per lane while that is at most the run
-    // length, then 2^n / run threads (complex64: runs of 16, complex128: 8)
-    constexpr int kRun = sizeof(T) == 4 ? 16 : 8;
+    // one wave of 2^n / 64 amplitudes per lane while that is at most 16, then
+    // 2^n / 16 threads
+    constexpr int kRun = 16;
     const int N = 1 << n;
     *threads = std::max(kWave, N / kRun);
     if (*threads == kWave) {
         switch (std::max(1, N / kWave)) {
-            case 1: return sv_resident_kernel<T, 64, 1>;
-            case 2: return sv_resident_kernel<T, 64, 2>;
-            case 4: return sv_resident_kernel<T, 64, 4>;
-            case 8: return sv_resident_kernel<T, 64, 8>;
-            default: break;
+            case 1: return sv_resident_kernel<float, 64, 1>;
+            case 2: return sv_resident_kernel<float, 64, 2>;
+            case 4: return sv_resident_kernel<float, 64, 4>;
+            case 8: return sv_resident_kernel<float, 64, 8>;
+            default: return sv_resident_kernel<float, 64, 16>;
         }
-        if constexpr (kRun == 16) return sv_resident_kernel<T, 64, 16>;
     }
     switch (*threads) {
-        case 128: return sv_resident_kernel<T, 128, kRun>;
-        case 256: return sv_resident_kernel<T, 256, kRun>;
-        case 512: return sv_resident_kernel<T, 512, kRun>;
-        default: return sv_resident_kernel<T, 1024, kRun>;
+        case 128: return sv_resident_kernel<float, 128, kRun>;
+        case 256: return sv_resident_kernel<float, 256, kRun>;
+        case 512: return sv_resident_kernel<float, 512, kRun>;
+        default: return sv_resident_kernel<float, 1024, kRun>;
     }
 }
 
-static int launch_resident(int dtype, const ResArgs &a, hipStream_t st) {
+static int launch_resident(const ResArgs &a, hipStream_t st) {
     int threads = 0;
-    const ResFn fn = dtype == GQAOA_C64 ? resident_fn<float>(a.n, &threads) : resident_fn<double>(a.n, &threads);
-    ProfScope ps(dtype == GQAOA_C64 ? "sv_resident_c64" : "sv_resident_c128", st);
+    const ResFn fn = resident_fn(a.n, &threads);
+    ProfScope ps("sv_resident_c64", st);
     hipLaunchKernelGGL(fn, dim3(1), dim3(threads), 0, st, a);
     ps.end();
     GQ_LAUNCH_CHECK();
@@ -1106,36 +1105,41 @@ static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, co
 }
 
 // ---- entry points (validated by the ABI layer) ---------------------------------------------
-// complex128 evolutions from |s> take the level form (level.hip): two passes
-// over the cost table, one write of the state and O(pK) level operations
-// instead of p passes over the state. It is the faster one at every n and p
-// (n = 10, p = 20: 40 us against 138 us of the resident rounds; n = 18, p = 32:
-// 49 against 409 us of streamed rounds; n = 28, p = 64: 0.91 against 94 ms,
-// p = 1: 0.89 against 2.5 ms).
+// complex128 evolutions take the level form (level.hip): two passes over the
+// cost table (and, for a given state, two reads of it), one write of the state
+// and O(pK) level operations instead of p passes over the state. It is the
+// faster one at every n and p (from |s>: n = 10, p = 20: 40 us against 138 us of
+// the resident rounds; n = 18, p = 32: 49 against 409 us of streamed rounds;
+// n = 28, p = 64: 0.91 against 94 ms, p = 1: 0.89 against 2.5 ms; from a given
+// state: n = 10, p = 20: 50 against 206 us; n = 22, p = 16: 89 against 615 us;
+// n = 28, p = 64: 2.9 against 95 ms, p = 1: 2.8 against 3.0 ms).
 // Round passes stay for complex64, whose float32 rounding in every round is
-// part of its results, for states that are given, and for the tuning hooks,
-// which ask for a form of them (GQAOA_SV_RESIDENT=0, GQAOA_SV_SHAPE,
-// GQAOA_SV_FUSE=1).
-static bool level_form(int dtype, int init_uniform) {
-    if (dtype != GQAOA_C128 || !init_uniform) return false;
+// part of its results, and for the tuning hooks, which ask for a form of them
+// (GQAOA_SV_RESIDENT=0, GQAOA_SV_SHAPE, GQAOA_SV_FUSE=1). p = 0 leaves a given
+// state alone: one readout pass.
+static bool level_form(int dtype, int init_uniform, int p) {
+    if (dtype != GQAOA_C128 || (!init_uniform && p == 0)) return false;
     const char *r = getenv("GQAOA_SV_RESIDENT");
     return !(r && r[0] == '0') && !getenv("GQAOA_SV_SHAPE") && !fuse_requested();
 }
 
-static LevelEvolve level_args(int n, int m, const uint8_t *cost, int p, void *psi, int target, void *ws) {
+static LevelEvolve level_args(int n, int m, const uint8_t *cost, int p, int init_uniform, void *psi, int target,
+                              void *ws) {
     const SvLayout L = sv_layout(1, n, p, GQAOA_C128, 0, false);
     char *w = reinterpret_cast<char *>(ws);
-    static_assert((size_t)kLevelMaxRows * 256 * 4 <= (size_t)kMaxPassBlocks * kFwdR * 8, "count rows in the partials");
+    constexpr size_t kRowsBytes = (size_t)(kLevelMaxRows + 1) * 256 * 32, kTableBytes = 512 * 16;
+    static_assert(kRowsBytes + kTableBytes <= (size_t)kMaxPassBlocks * kFwdR * 8, "rows and table in the partials");
     LevelEvolve e{};
     e.n = n;
     e.m = m;
     e.p = p;
     e.target = target;
+    e.init_uniform = init_uniform;
     e.cost = cost;
     e.psi = psi;
     e.angles_dev = reinterpret_cast<double *>(w + L.angles);
-    e.rows = reinterpret_cast<uint32_t *>(w + L.partials);
-    e.table = w + L.lut;  // 256 entries of one round's table
+    e.rows = w + L.partials;
+    e.table = w + L.partials + kRowsBytes;
     e.readout = reinterpret_cast<double *>(w + L.readout);
     return e;
 }
@@ -1149,8 +1153,8 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
     std::vector<int32_t> t;
     int s;
     const double *readout;
-    if (level_form(dtype, init_uniform)) {
-        LevelEvolve le = level_args(n, m, cost, p, psi, target, ws);
+    if (level_form(dtype, init_uniform, p)) {
+        LevelEvolve le = level_args(n, m, cost, p, init_uniform, psi, target, ws);
         le.beta_host = beta;
         le.gamma_host = gamma;
         if ((s = level_evolve(le, false, st))) return s;
@@ -1164,7 +1168,7 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
         if (resident_ok(n, dtype, p)) {
             ResArgs r{cost, psi, P.ws + P.L.lut, reinterpret_cast<const double *>(P.ws + P.L.mixf),
                       reinterpret_cast<double *>(P.ws + P.L.readout), n, p, init_uniform ? 1 : 0, target};
-            if ((s = launch_resident(dtype, r, st))) return s;
+            if ((s = launch_resident(r, st))) return s;
         } else {
             for (int j = 1; j <= p; ++j)
                 if ((s = forward_round(P, j, psi, psi, init_uniform && j == 1, true, st))) return s;
@@ -1257,7 +1261,7 @@ static int run_grad_level(int num_inst, int n, const int32_t *m_of, const uint8_
 int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int p,
              const double *beta, const double *gamma, int dtype, const int32_t *targets,
              int ckpt_every, double *psol, double *dbeta, double *dgamma, void *ws, hipStream_t st) {
-    if (level_form(dtype, 1))
+    if (level_form(dtype, 1, p))
         return run_grad_level(num_inst, n, m_of, cost, p, beta, gamma, targets, psol, dbeta, dgamma, ws, st);
     FwdPlan P;
     std::vector<char> lut;
@@ -1449,8 +1453,8 @@ struct EvolvePlanGuard {
 
 static int enqueue_evolve(EvolvePlan *E, int init_uniform, void *psi, hipStream_t st) {
     FwdPlan &P = E->P;
-    if (level_form(P.dtype, init_uniform))
-        return level_evolve(level_args(P.n, E->m, P.cost, P.p, psi, *E->target_host, P.ws), true, st);
+    if (level_form(P.dtype, init_uniform, P.p))
+        return level_evolve(level_args(P.n, E->m, P.cost, P.p, init_uniform, psi, *E->target_host, P.ws), true, st);
     const double *ang = reinterpret_cast<const double *>(P.ws + P.L.angles);
     double *mixf = reinterpret_cast<double *>(P.ws + P.L.mixf);
     if (P.dtype == GQAOA_C64)
@@ -1463,7 +1467,7 @@ static int enqueue_evolve(EvolvePlan *E, int init_uniform, void *psi, hipStream_
     if (resident_ok(P.n, P.dtype, P.p)) {
         ResArgs r{P.cost, psi, P.ws + P.L.lut, mixf, reinterpret_cast<double *>(P.ws + P.L.readout), P.n, P.p,
                   init_uniform, *E->target_host};
-        return launch_resident(P.dtype, r, st);
+        return launch_resident(r, st);
     }
     int s;
     for (int j = 1; j <= P.p; ++j)

@@ -80,3 +80,43 @@ def test_level_gradient_matches_statevector_oracle(n, I, levels, p, odd):
         rP, rb, rg = grad_sv(n, cost[i], b[i], gm[i], target=int(tg[i]))
         assert abs(P[i] - rP) < 1e-12 and np.abs(db[i] - rb).max() < 1e-12, i
         assert np.abs(dg[i] - rg).max() < 1e-12 * levels, i
+
+
+@pytest.mark.parametrize("n,m,p,odd", [
+    (3, 2, 1, False), (5, 7, 3, True), (8, 97, 16, False), (9, 98, 17, False), (9, 188, 5, False), (10, 189, 4, True),
+    (11, 254, 6, False), (13, 50, 113, False), (16, 40, 15, True), (17, 67, 9, False), (20, 84, 3, False)])
+def test_given_state_in_level_form(n, m, p, odd):
+    """From a random state that is not constant on the levels: the level sums'
+    column counts (16, 8 and 4 columns: up to 98, 189 and 255 levels), blocks of
+    a few amplitudes and of several tiles, a plan's runs chained from psi's own
+    contents, and reruns with the same bits."""
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(800 + 7 * n + m))
+    cost = rng.integers(0, m + 1, 2 ** n).astype(np.uint8)
+    v = rng.normal(size=2 ** n) + 1j * rng.normal(size=2 ** n)
+    v /= np.linalg.norm(v)
+    buf = torch.zeros(2 ** n + 16, dtype=torch.uint8, device="cuda")
+    dev = buf[1:2 ** n + 1] if odd else buf[:2 ** n]
+    dev.copy_(torch.from_numpy(cost))
+    b, gm = rng.uniform(0, 2 * np.pi, p), rng.uniform(0, np.pi, p)
+    target = int(cost[0])
+    log(f"given state n={n} m={m} p={p} odd={odd}")
+    runs = [g.gqaoa_evolve(n, m, dev, b, gm, dtype=g.C128, psi=torch.tensor(v, device="cuda"), init_uniform=False,
+                           target_level=target) for _ in range(3)]
+    psi, ps, en, no = runs[0]
+    for r in runs[1:]:
+        assert torch.equal(r[0], psi) and all(np.array_equal(x, y) for x, y in zip(r[1:], runs[0][1:]))
+    rpsi, rp, re, rn = evolve_sv(n, cost, b, gm, psi0=v, target=target)
+    assert np.abs(ps - rp).max() < 1e-12 and np.abs(no - rn).max() < 1e-12
+    assert np.abs(en - re).max() < 1e-12 * m
+    assert np.abs(psi.cpu().numpy() - rpsi).max() < 1e-12
+    plan = g.EvolvePlan(n, m, dev, p, dtype=g.C128, init_uniform=False, target_level=target,
+                        psi=torch.tensor(v, device="cuda"))
+    try:
+        got = plan.run(b, gm)
+        assert all(np.array_equal(x, y) for x, y in zip(got, (ps, en, no))) and torch.equal(plan.psi, psi)
+        got = plan.run(b, gm)
+        rpsi, rp, _, _ = evolve_sv(n, cost, b, gm, psi0=rpsi, target=target)
+        assert np.abs(got[0] - rp).max() < 1e-12 and np.abs(plan.psi.cpu().numpy() - rpsi).max() < 1e-12
+    finally:
+        plan.close()
