@@ -169,6 +169,14 @@ struct FinArgs {
     int grad_stride;         // doubles per instance in dbeta (p)
 };
 
+// delta_j = (e^{-i beta_j} - 1) S_j / N
+__device__ __forceinline__ void mixer_delta(double mr, double mi, double inv_N, double Sr, double Si, double &dr,
+                                            double &di) {
+    const double sr = Sr * inv_N, si = Si * inv_N;
+    dr = mr * sr - mi * si;
+    di = mr * si + mi * sr;
+}
+
 // Turn the summed partials of one instance into its readouts and delta_j.
 __device__ __forceinline__ void finalize_apply(const FinArgs &a, int inst, const double (&r)[kFwdR]) {
     if (a.readout_out) {
@@ -179,10 +187,8 @@ __device__ __forceinline__ void finalize_apply(const FinArgs &a, int inst, const
     }
     if (a.mixf) {
         const double *mf = a.mixf + (size_t)inst * a.mixf_stride;
-        const double sr = r[0] * a.inv_N, si = r[1] * a.inv_N;
         double *d = a.delta_out + (size_t)inst * a.stride;
-        d[0] = mf[0] * sr - mf[1] * si;
-        d[1] = mf[0] * si + mf[1] * sr;
+        mixer_delta(mf[0], mf[1], a.inv_N, r[0], r[1], d[0], d[1]);
         if (a.S_out) {
             double *s = a.S_out + (size_t)inst * a.stride;
             s[0] = r[0];
@@ -232,6 +238,61 @@ __device__ __forceinline__ void reduce_rows(const double *p, int nrows, double (
     block_sum<R, kThreads>(r, lds);
 }
 
+// block_sum of a kSvThreads block, entry k added over the waves and stored to
+// out[k] by thread k: the R serial sums of one thread side by side.
+template <int R>
+__device__ __forceinline__ void block_sum_row(double (&v)[R], double *lds, double *out) {
+    constexpr int kWaves = kSvThreads / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] = wave_sum_dpp(v[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) lds[wave * R + k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < R) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += lds[w * R + threadIdx.x];
+        out[threadIdx.x] = s;
+    }
+}
+
+// Sums of the first R entries of nrows <= kChainRows partial rows, in every
+// thread of a kSvThreads block: row 64 w + l by lane l of wave w (mod the
+// block's waves), then the waves' sums in order, as the finalize of one row per
+// thread adds them. Ends behind a barrier; lds is free again after the next.
+constexpr int kChainRows = 512;
+
+template <int R>
+__device__ __forceinline__ void sum_rows(const double *p, int nrows, double (&r)[R], double *lds) {
+    constexpr int kWaves = kSvThreads / kWave, kPer = kChainRows / kSvThreads;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    double v[kPer][R];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int b = (i * kWaves + wave) * kWave + lane;
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[i][k] = b < nrows ? p[(size_t)b * kFwdR + k] : 0.0;
+    }
+    const int nw = (nrows + kWave - 1) / kWave;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        if (i * kWaves + wave < nw)
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                v[i][k] = wave_sum_dpp(v[i][k]);
+                if (lane == 0) lds[(i * kWaves + wave) * R + k] = v[i][k];
+            }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < R; ++k) r[k] = 0.0;
+    for (int w = 0; w < nw; ++w)
+#pragma unroll
+        for (int k = 0; k < R; ++k) r[k] += lds[w * R + k];
+}
+
 // ---- forward pass ---------------------------------------------------------------
 struct FwdArgs {
     const uint8_t *cost;     // [inst][N]
@@ -248,29 +309,37 @@ struct FwdArgs {
     const int32_t *target;   // [inst]
     double *partials;        // [inst][gridDim.x][kFwdR]
     unsigned int *counter;   // [inst] blocks finished (fused finalize only; zero between launches)
-    FinArgs fin;             // finalize of this round (fused finalize only)
+    FinArgs fin;             // finalize of this round (fused), or of the pass before (chained)
+    int chain;               // finalize the pass before (complex64, one tile of 2 x 4 per lane and block)
 };
 
+// CHAIN: the pass finalizes the pass before it. Every block sums that pass's
+// partial rows (a.fin, at most kChainRows, in the finalize's order, so delta is
+// the same bits) while its own tile is on its way from memory; one more block of
+// each instance writes the readouts, S and delta. One tile per block.
 // FUSED: the last block of each instance to finish (counted with a device-scope
 // atomic after a release fence) sums all partial rows in the fixed row order
 // and applies the finalize itself, so a round is a single launch.
-template <typename T, bool PHASE, bool WRITE, int AMP, int UNROLL, int NT = 1, bool FUSED = false>
+template <typename T, bool PHASE, bool WRITE, int AMP, int UNROLL, int NT = 1, bool FUSED = false, bool CHAIN = false>
 __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
     __shared__ Cx<T> lut_s[256];
-    __shared__ double red_s[kFwdR * kSvThreads / kWave];
+    __shared__ double red_s[kFwdR * (CHAIN ? kChainRows : kSvThreads) / kWave];
     const int inst = blockIdx.y;
     const uint64_t ioff = (uint64_t)inst * a.N;
-    if constexpr (PHASE) {
-        const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
-        for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
-        __syncthreads();
+    const double *rows = nullptr;
+    int nblocks = gridDim.x;
+    if constexpr (CHAIN) {
+        rows = a.fin.partials + (size_t)inst * a.fin.nblocks * kFwdR;
+        nblocks = a.fin.nblocks;
+        if ((int)blockIdx.x == nblocks) {
+            double r[kFwdR];
+            sum_rows<kFwdR>(rows, nblocks, r, red_s);
+            if (threadIdx.x == 0) finalize_apply(a.fin, inst, r);
+            return;
+        }
     }
     const uint32_t target = (uint32_t)a.target[inst];
     Cx<T> dl{T(0), T(0)};
-    if (a.delta) {
-        const double *d = a.delta + (size_t)inst * a.delta_stride;
-        dl = {T(d[0]), T(d[1])};
-    }
     const uint8_t *cost = a.cost + ioff;
     const Cx<T> *src = reinterpret_cast<const Cx<T> *>(a.psi_in) + ioff;
     Cx<T> *dst = reinterpret_cast<Cx<T> *>(a.psi_out) + ioff;
@@ -279,11 +348,11 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
     double accSr = 0, accSi = 0, accP = 0, accE = 0, accN = 0, accTr = 0, accTi = 0;
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t wave = ((uint64_t)blockIdx.x * kSvThreads + threadIdx.x) / kWave;
-    const uint64_t nwaves = (uint64_t)gridDim.x * kSvThreads / kWave;
+    const uint64_t nwaves = (uint64_t)nblocks * kSvThreads / kWave;
     constexpr uint64_t kTile = (uint64_t)kWave * AMP * UNROLL;
-    for (uint64_t base = wave * kTile; base < a.N; base += nwaves * kTile) {
-        uint32_t c[UNROLL][AMP];
-        Cx<T> v[UNROLL][AMP];
+    uint32_t c[UNROLL][AMP];
+    Cx<T> v[UNROLL][AMP];
+    auto load_tile = [&](uint64_t base) {
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const uint64_t idx = base + (uint64_t)u * kWave * AMP + (uint64_t)lane * AMP;
@@ -295,6 +364,28 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
                 for (int i = 0; i < AMP; ++i) c[u][i] = 0xFFFFu;  // never a target level
             }
         }
+    };
+    if constexpr (CHAIN) load_tile(wave * kTile);  // in flight during the sums below
+    if constexpr (PHASE) {
+        const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
+        for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
+    }
+    if constexpr (CHAIN) {
+        const double *mf = a.fin.mixf + (size_t)inst * a.fin.mixf_stride;
+        const double mr = mf[0], mi = mf[1];
+        double S[2], dr, di;
+        sum_rows<2>(rows, a.fin.nblocks, S, red_s);
+        mixer_delta(mr, mi, a.fin.inv_N, S[0], S[1], dr, di);
+        dl = {T(dr), T(di)};
+    } else {
+        if constexpr (PHASE) __syncthreads();
+        if (a.delta) {
+            const double *d = a.delta + (size_t)inst * a.delta_stride;
+            dl = {T(d[0]), T(d[1])};
+        }
+    }
+    for (uint64_t base = wave * kTile; base < a.N; base += nwaves * kTile) {
+        if constexpr (!CHAIN) load_tile(base);
         typename Acc<T>::t sSr = 0, sSi = 0, sP = 0, sE = 0, sN = 0, sTr = 0, sTi = 0;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
@@ -329,14 +420,11 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
             }
         }
     }
+    if constexpr (CHAIN) __syncthreads();  // red_s: read above, written below
     double r[kFwdR] = {accSr, accSi, accP, accE, accN, accTr, accTi};
-    block_sum<kFwdR, kSvThreads>(r, red_s);
-    if (threadIdx.x == 0) {
-        double *out = a.partials + ((size_t)inst * gridDim.x + blockIdx.x) * kFwdR;
-#pragma unroll
-        for (int k = 0; k < kFwdR; ++k) out[k] = r[k];
-    }
+    block_sum_row<kFwdR>(r, red_s, a.partials + ((size_t)inst * nblocks + blockIdx.x) * kFwdR);
     if constexpr (FUSED) {
+        __syncthreads();
         __shared__ int last_s;
         if (threadIdx.x == 0) {
             __threadfence();
@@ -615,12 +703,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
         }
     }
     double r[kRevR] = {accLr, accLi, accGr, accGi};
-    block_sum<kRevR, kSvThreads>(r, red_s);
-    if (threadIdx.x == 0) {
-        double *out = a.partials + ((size_t)inst * gridDim.x + blockIdx.x) * kRevR;
-#pragma unroll
-        for (int k = 0; k < kRevR; ++k) out[k] = r[k];
-    }
+    block_sum_row<kRevR>(r, red_s, a.partials + ((size_t)inst * gridDim.x + blockIdx.x) * kRevR);
 }
 
 // ---- finalizers (fixed-order sums of the per-block partial rows) -----------------
@@ -770,6 +853,11 @@ template <typename T, bool PHASE, bool WRITE>
 static void launch_fwd_t(const PassShape &s, int num_inst, const FwdArgs &a, hipStream_t st) {
     const dim3 grid(s.blocks_x, num_inst), block(kSvThreads);
     if constexpr (sizeof(T) == 4) {
+        if (a.chain) {
+            const dim3 g1(s.blocks_x + 1, num_inst);
+            hipLaunchKernelGGL((sv_forward_kernel<T, PHASE, WRITE, 2, 4, 1, false, true>), g1, block, 0, st, a);
+            return;
+        }
         if constexpr (PHASE && WRITE) {  // the round pass: every compiled tuning shape
             if (a.counter && s.amp == 2 && s.unroll == 8 && s.nt == 1) {
                 hipLaunchKernelGGL((sv_forward_kernel<T, true, true, 2, 8, 1, true>), grid, block, 0, st, a);
@@ -946,6 +1034,8 @@ struct FwdPlan {
     SvLayout L;
     PassShape shape;
     const uint8_t *cost;
+    bool chain = false;     // passes finalize the one before them
+    FinArgs pending{};      // finalize of the last chained pass, due in the next one
     int fuse_mode = 0;  // 0: the GQAOA_SV_FUSE switch decides, 1: fused when the shape allows, -1: never
 };
 
@@ -1025,10 +1115,38 @@ static bool fused_round(const FwdPlan &P) {
     return s.unroll == 8 && s.nt == 1 && s.amp == (P.dtype == GQAOA_C64 ? 2 : 1);
 }
 
+// A round of a small streamed state is launches and latency: a pass of 4.3 us and
+// a finalize of 2 to 3 us at n = 16 .. 18, with a gap of 1.1 us after each. Chained
+// passes drop the second launch (per round, complex64, replayed: n = 16 7.2 -> 5.7
+// us, n = 18 7.7 -> 6.0, n = 20 10.5 -> 7.5). Every block pays for the rows, so
+// with more of them it turns: at n = 21 (1024 rows) 13.0 -> 13.2 us, and a batch
+// of 64 gradients of n = 20 (512 rows, 32,768 blocks) loses 6%; at 2,048 blocks in
+// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing.
+constexpr int kChainBlocks = 2048;
+
+static bool chain_rule(const FwdPlan &P) {
+    const PassShape &s = P.shape;
+    return P.dtype == GQAOA_C64 && P.p > 0 && s.amp == 2 && s.unroll == 4 && s.nt == 1 &&
+           s.blocks_x <= kChainRows && (uint64_t)s.blocks_x * kSvThreads * 8 == P.N &&
+           (int64_t)P.num_inst * s.blocks_x <= kChainBlocks && !fused_round(P);
+}
+
+// Pass j of a chain (1-based; j = p + 1: the final pass): its rows go to one of
+// two regions in turn, and it finalizes the rows of pass j - 1 from the other.
+static void chain_pass(FwdPlan &P, int j, FwdArgs &a, FinArgs &f) {
+    a.partials += (size_t)(j & 1) * P.num_inst * P.shape.blocks_x * kFwdR;
+    f.partials = a.partials;
+    if (j > 1) {
+        a.chain = 1;
+        a.fin = P.pending;
+    }
+    P.pending = f;
+}
+
 // One forward round j (1-based): psi_in holds phi_{j-1} (or |s> if j == 1 and
 // uniform), psi_out receives phi_j. With finalize, writes delta_j, S_j and the
 // readout of round j-1.
-static int forward_round(const FwdPlan &P, int j, const void *psi_in, void *psi_out, bool uniform,
+static int forward_round(FwdPlan &P, int j, const void *psi_in, void *psi_out, bool uniform,
                          bool finalize, hipStream_t st) {
     const size_t cs = P.dtype == GQAOA_C64 ? 8 : 16;
     FwdArgs a = base_fwd_args(P);
@@ -1042,7 +1160,8 @@ static int forward_round(const FwdPlan &P, int j, const void *psi_in, void *psi_
     f.delta_out = reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * j;
     f.S_out = reinterpret_cast<double *>(P.ws + P.L.S) + 2 * j;
     f.readout_out = reinterpret_cast<double *>(P.ws + P.L.readout) + 3 * (j - 1);
-    const bool fused = finalize && fused_round(P);
+    if (finalize && P.chain) chain_pass(P, j, a, f);
+    const bool fused = finalize && !P.chain && fused_round(P);
     if (fused) {
         a.counter = reinterpret_cast<unsigned int *>(P.ws + P.L.counter);
         a.fin = f;
@@ -1051,12 +1170,12 @@ static int forward_round(const FwdPlan &P, int j, const void *psi_in, void *psi_
     launch_fwd(P.dtype, true, true, P.shape, P.num_inst, a, st);
     ps.end();
     GQ_LAUNCH_CHECK();
-    if (finalize && !fused) return launch_finalize(P, f, st);
+    if (finalize && !fused && !P.chain) return launch_finalize(P, f, st);
     return GQAOA_OK;
 }
 
 // Final pass: psi_out = phi_p + delta_p (if write), readout of round p.
-static int final_pass(const FwdPlan &P, const void *psi_in, void *psi_out, bool uniform, bool write,
+static int final_pass(FwdPlan &P, const void *psi_in, void *psi_out, bool uniform, bool write,
                       hipStream_t st) {
     FwdArgs a = base_fwd_args(P);
     a.psi_in = psi_in;
@@ -1064,9 +1183,10 @@ static int final_pass(const FwdPlan &P, const void *psi_in, void *psi_out, bool 
     a.lut = nullptr;
     a.delta = P.p > 0 ? reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * P.p : nullptr;
     a.init_uniform = uniform ? 1 : 0;
+    FinArgs f = base_fin_args(P);
+    if (P.chain) chain_pass(P, P.p + 1, a, f);
     launch_fwd(P.dtype, false, write, P.shape, P.num_inst, a, st);
     GQ_LAUNCH_CHECK();
-    FinArgs f = base_fin_args(P);
     f.readout_out = reinterpret_cast<double *>(P.ws + P.L.readout) + 3 * P.p;
     return launch_finalize(P, f, st);
 }
@@ -1088,6 +1208,7 @@ static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, co
     P.ws = reinterpret_cast<char *>(ws);
     P.L = sv_layout(num_inst, n, p, dtype, ckpt_every, grad);
     P.shape = pass_shape(P.N, num_inst, dtype, dev, fuse_requested());
+    P.chain = chain_rule(P);
     P.cost = cost;
     if (p > 0) {
         build_tables(num_inst, m_of, p, beta, gamma, dtype, keep_lut, keep_f, keep_b, keep_e);
@@ -1299,9 +1420,10 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
         a.psi_out = nullptr;
         a.lut = nullptr;
         a.delta = reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * p;
+        FinArgs fa = base_fin_args(P);
+        if (P.chain) chain_pass(P, p + 1, a, fa);
         launch_fwd(P.dtype, false, false, P.shape, P.num_inst, a, st);
         GQ_LAUNCH_CHECK();
-        FinArgs fa = base_fin_args(P);
         fa.readout_out = reinterpret_cast<double *>(P.ws + P.L.readout) + 3 * p;
         fa.mixb = reinterpret_cast<double *>(P.ws + P.L.mixb) + 2 * (p - 1);
         fa.ebeta = reinterpret_cast<double *>(P.ws + P.L.ebeta) + 2 * (p - 1);
@@ -1495,11 +1617,12 @@ int evolve_plan_create(int n, int m, const uint8_t *cost, int p, int dtype, int 
     P.ws = reinterpret_cast<char *>(ws);
     P.L = sv_layout(1, n, p, dtype, 0, false);
     P.cost = cost;
-    // The round passes with their separate fold / finalize launches: on the
-    // one-tile grid they replay faster than the fused finalize at every size
-    // measured (n = 16..22, complex64).
+    // Round passes on the one-tile grid, chained or with separate fold / finalize
+    // launches: they replay faster than the fused finalize at every size measured
+    // (n = 16..22, complex64).
     P.fuse_mode = -1;
     P.shape = pass_shape(P.N, 1, dtype, dev);
+    P.chain = chain_rule(P);
     GQ_HIP(hipHostMalloc(reinterpret_cast<void **>(&E->stage), sizeof(double) * (2 * (size_t)p + 3 * ((size_t)p + 1)),
                          hipHostMallocDefault));
     {
@@ -1594,6 +1717,7 @@ int sv_items_stream(int n, int count, const int32_t *item_inst, const int32_t *i
         P.L = sv_layout(cnt, n, p, GQAOA_C64, 0, false);
         P.shape = pass_shape(N, cnt, GQAOA_C64, dev);
         P.fuse_mode = -1;
+        P.chain = chain_rule(P);
         auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
         const size_t o_cost = al(P.L.total), o_psi = o_cost + al(cnt * N), o_off = o_psi + al(cnt * N * 8);
         const size_t o_m = o_off + al(8 * (size_t)cnt), o_out = o_m + al(4 * (size_t)cnt);

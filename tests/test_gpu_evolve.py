@@ -204,3 +204,36 @@ def test_sampled_profiling_counts():
     assert g.gqaoa_profile_read("sv_round_c128")[1] == 0
     g.gqaoa_profile_reset()
     assert cnt == 1 and ms > 0
+
+
+@pytest.mark.parametrize("n,count", [(15, 129), (19, 9), (20, 5), (21, 3)])
+def test_chained_rounds_are_the_separate_ones(n, count):
+    """Round passes of small complex64 states finalize the pass before them (up
+    to 512 partial rows and 2,048 blocks); a batch over that bound launches its
+    finalizes by themselves. Both add the same rows in the same order: the same
+    bits, in evolutions of one and two rounds, plans and gradients, and within
+    the complex64 tolerance of the oracle. (n = 21: neither is chained.)"""
+    torch = need_gpu()
+    m = 60
+    lits = rand_lits(n, m, 500 + n)
+    ref_cost = cost_table(n, lits)
+    beta, gamma = inst.uniform_angles(500 + n, 2)
+    cost, _ = g.gqaoa_cost_table(n, lits)
+    psi0 = rand_state(n, n).astype(np.complex64)
+    for p in (1, 2):
+        log(f"chained rounds n={n} p={p}")
+        psi = torch.tensor(psi0, device="cuda")
+        res = g.gqaoa_evolve(n, m, cost, beta[:p], gamma[:p], dtype=g.C64, psi=psi, init_uniform=False)
+        _check(res, evolve_sv(n, ref_cost, beta[:p], gamma[:p], psi0=psi0.astype(np.complex128)), g.C64, m)
+        plan = g.EvolvePlan(n, m, cost, p, dtype=g.C64)
+        one = g.gqaoa_evolve(n, m, cost, beta[:p], gamma[:p], dtype=g.C64)
+        for _ in range(3):
+            for a, b in zip(plan.run(beta[:p], gamma[:p]), one[1:]):
+                assert np.abs(a - b).max() < 1e-6 * m   # tables of the device and of the host
+        P, db, dg = g.gqaoa_grad_batched(n, [m], cost.view(1, -1), beta[None, :p], gamma[None, :p], dtype=g.C64,
+                                         ckpt_every=1)
+        B, dB, dG = g.gqaoa_grad_batched(n, [m] * count, cost.view(1, -1).repeat(count, 1),
+                                         np.tile(beta[:p], (count, 1)), np.tile(gamma[:p], (count, 1)), dtype=g.C64,
+                                         ckpt_every=0)
+        assert P[0] == one[1][-1]
+        assert (B == P[0]).all() and (dB == db).all() and (dG == dg).all()
