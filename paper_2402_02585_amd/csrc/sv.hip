@@ -310,6 +310,7 @@ struct FwdArgs {
     double *partials;        // [inst][gridDim.x][kFwdR]
     unsigned int *counter;   // [inst] blocks finished (fused finalize only; zero between launches)
     FinArgs fin;             // finalize of this round (fused), or of the pass before (chained)
+    int backward;            // blocks take the tiles in descending order
     int chain;               // finalize the pass before (complex64, one tile of 2 x 4 per lane and block)
 };
 
@@ -338,6 +339,8 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
             return;
         }
     }
+    // ^ 7: the tile stays with the XCD (block number mod 8) that had it in the pass before
+    const unsigned block = !CHAIN && a.backward ? (gridDim.x - 1 - blockIdx.x) ^ 7u : blockIdx.x;
     const uint32_t target = (uint32_t)a.target[inst];
     Cx<T> dl{T(0), T(0)};
     const uint8_t *cost = a.cost + ioff;
@@ -347,7 +350,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
 
     double accSr = 0, accSi = 0, accP = 0, accE = 0, accN = 0, accTr = 0, accTi = 0;
     const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t wave = ((uint64_t)blockIdx.x * kSvThreads + threadIdx.x) / kWave;
+    const uint64_t wave = ((uint64_t)block * kSvThreads + threadIdx.x) / kWave;
     const uint64_t nwaves = (uint64_t)nblocks * kSvThreads / kWave;
     constexpr uint64_t kTile = (uint64_t)kWave * AMP * UNROLL;
     uint32_t c[UNROLL][AMP];
@@ -422,7 +425,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
     }
     if constexpr (CHAIN) __syncthreads();  // red_s: read above, written below
     double r[kFwdR] = {accSr, accSi, accP, accE, accN, accTr, accTi};
-    block_sum_row<kFwdR>(r, red_s, a.partials + ((size_t)inst * nblocks + blockIdx.x) * kFwdR);
+    block_sum_row<kFwdR>(r, red_s, a.partials + ((size_t)inst * nblocks + block) * kFwdR);
     if constexpr (FUSED) {
         __syncthreads();
         __shared__ int last_s;
@@ -1143,6 +1146,16 @@ static void chain_pass(FwdPlan &P, int j, FwdArgs &a, FinArgs &f) {
     P.pending = f;
 }
 
+// From 2^28 amplitudes on, every second pass takes its tiles in descending order,
+// so that it begins with what the pass before touched last. Per round, complex64:
+// n = 28 749 -> 733 us, n = 29 1,573 -> 1,540, n = 30 unchanged; below, where the
+// ascending pass already runs at the card's copy rate, it gives nothing (n = 27:
+// 369 and 370 us), and a descending order that also moves tiles between XCDs costs
+// a third at n = 20. Contiguous runs of tiles per XCD lose 3 to 10% either way.
+static bool turn_rule(const FwdPlan &P) {
+    return P.num_inst == 1 && P.N >= (1ull << 28) && P.shape.blocks_x % 8 == 0;
+}
+
 // One forward round j (1-based): psi_in holds phi_{j-1} (or |s> if j == 1 and
 // uniform), psi_out receives phi_j. With finalize, writes delta_j, S_j and the
 // readout of round j-1.
@@ -1155,6 +1168,7 @@ static int forward_round(FwdPlan &P, int j, const void *psi_in, void *psi_out, b
     a.lut = P.ws + P.L.lut + (size_t)(j - 1) * 256 * cs;
     a.delta = j > 1 ? reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * (j - 1) : nullptr;
     a.init_uniform = uniform ? 1 : 0;
+    a.backward = !(j & 1) && turn_rule(P);
     FinArgs f = base_fin_args(P);
     f.mixf = reinterpret_cast<double *>(P.ws + P.L.mixf) + 2 * (j - 1);
     f.delta_out = reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * j;
@@ -1183,6 +1197,7 @@ static int final_pass(FwdPlan &P, const void *psi_in, void *psi_out, bool unifor
     a.lut = nullptr;
     a.delta = P.p > 0 ? reinterpret_cast<double *>(P.ws + P.L.delta) + 2 * P.p : nullptr;
     a.init_uniform = uniform ? 1 : 0;
+    a.backward = (P.p & 1) && turn_rule(P);
     FinArgs f = base_fin_args(P);
     if (P.chain) chain_pass(P, P.p + 1, a, f);
     launch_fwd(P.dtype, false, write, P.shape, P.num_inst, a, st);

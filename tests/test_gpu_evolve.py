@@ -237,3 +237,30 @@ def test_chained_rounds_are_the_separate_ones(n, count):
                                          ckpt_every=0)
         assert P[0] == one[1][-1]
         assert (B == P[0]).all() and (dB == db).all() and (dG == dg).all()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+def test_alternating_tile_order_n28(p):
+    """From 2^28 amplitudes on every second pass takes its tiles in descending
+    order (the final pass too, when p is odd). From a state whose phase grows with
+    z, so that no two tiles are alike, readouts and amplitudes agree with the
+    complex128 level form to complex64 rounding."""
+    torch = need_gpu()
+    n, m = 28, 118
+    it = c2_instance()
+    beta, gamma = inst.uniform_angles(28 + p, p)
+    cost, _ = g.gqaoa_cost_table(n, it.lits)
+    log(f"alternating order n=28 p={p}")
+    psi0 = torch.full((1 << n,), 2.0 ** -14, dtype=torch.complex128, device="cuda")
+    ramp = torch.arange(1 << n, device="cuda", dtype=torch.float64) * (0.5 / (1 << n))
+    psi0 *= torch.polar(torch.ones_like(ramp), ramp)
+    del ramp
+    a = psi0.to(torch.complex64)
+    want = g.gqaoa_evolve(n, m, cost, beta, gamma, dtype=g.C128, psi=psi0, init_uniform=False)
+    got = g.gqaoa_evolve(n, m, cost, beta, gamma, dtype=g.C64, psi=a, init_uniform=False)
+    for x, y, scale in zip(got[1:], want[1:], (1, m, 1)):
+        assert np.abs(x - y).max() < TOL[g.C64] * scale
+    # amplitudes of size 2^-14: (p + 1) rounds of a few float32 roundings each
+    assert (got[0] - want[0]).abs().max().item() < 2.0 ** -14 * (p + 1) * 8 * 2.0 ** -24
+    del a, psi0, want, got
+    torch.cuda.empty_cache()
