@@ -537,8 +537,12 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
 // A block takes kXCopyTiles consecutive tiles: their rows are runs of 2^mlo
 // bytes of the table, adjacent for adjacent tiles while the tile index's low
 // bits are z bits, so lanes read consecutive 8-byte pieces; the tiles are
-// staged in LDS in element order and each thread then gathers its 2^R bytes
-// and writes them with one vector store.
+// staged in LDS in element order. A thread's 2^R bytes there are 2^rb apart and
+// those of the next threads beside them (rb >= mlo >= 3), so a lane gathers the
+// words of four threads and turns each 4 x 4 bytes over with permutes: 16 LDS
+// reads for 64 bytes of the copy. Eight pieces of the table are in flight per
+// lane. n = 26, complex64: 36 us a copy, 56 with one piece in flight and one
+// LDS read per byte.
 constexpr int kXCopyTilesLog2 = 3;
 constexpr int kXCopyBytesLog2 = 15;  // LDS of the copy kernel
 // Tiles per block of the copy kernel, log2: kXCopyTilesLog2, fewer when the
@@ -548,55 +552,91 @@ __host__ __device__ inline int x_copy_ntl(int tb, uint64_t ntiles) {
     while (ntl > 0 && (1ull << ntl) > ntiles) --ntl;
     return ntl;
 }
+template <int R>
 __global__ void __launch_bounds__(256) x_cost_tiles_kernel(const uint8_t *__restrict__ cost, uint8_t *__restrict__ out,
-                                                          int tb, int mlo, int q0, int rb, int R, uint64_t ntiles) {
+                                                          int tb, int mlo, int q0, int rb, uint64_t ntiles) {
     __shared__ __align__(16) uint8_t st[1 << kXCopyBytesLog2];
     const int lowbits = q0 - mlo, hishift = q0 + tb - mlo;
     const int ntl = x_copy_ntl(tb, ntiles);
     const int runl = mlo - 3;  // 8-byte pieces per row run, log2
-    const int E = 1 << R;
+    constexpr int E = 1 << R;
     for (uint64_t tile0 = (uint64_t)blockIdx.x << ntl; tile0 < ntiles; tile0 += (uint64_t)gridDim.x << ntl) {
-        for (int k = threadIdx.x; k < (1 << (ntl + tb - 3)); k += blockDim.x) {
-            const int pb = k & ((1 << runl) - 1);
-            const int j = (k >> runl) & ((1 << ntl) - 1);
-            const int row = k >> (runl + ntl);
-            const uint64_t tile = tile0 + j;
-            const uint64_t base = ((tile & ((1ull << lowbits) - 1)) << mlo) | ((tile >> lowbits) << hishift);
-            const uint2 v = *reinterpret_cast<const uint2 *>(cost + (base | ((uint64_t)pb << 3) | ((uint64_t)row << q0)));
-            *reinterpret_cast<uint2 *>(st + (j << tb) + (row << mlo) + (pb << 3)) = v;
+        const int pieces = 1 << (ntl + tb - 3);
+        for (int k0 = threadIdx.x; k0 < pieces; k0 += 8 * blockDim.x) {
+            uint2 v[8];
+            int at[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {  // past the last piece: that one again
+                const int k = min(k0 + i * (int)blockDim.x, pieces - 1);
+                const int pb = k & ((1 << runl) - 1);
+                const int j = (k >> runl) & ((1 << ntl) - 1);
+                const int row = k >> (runl + ntl);
+                const uint64_t tile = tile0 + j;
+                const uint64_t base = ((tile & ((1ull << lowbits) - 1)) << mlo) | ((tile >> lowbits) << hishift);
+                v[i] = *reinterpret_cast<const uint2 *>(cost + (base | ((uint64_t)pb << 3) | ((uint64_t)row << q0)));
+                at[i] = (j << tb) + (row << mlo) + (pb << 3);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *reinterpret_cast<uint2 *>(st + at[i]) = v[i];
         }
         __syncthreads();
-        for (int w0 = threadIdx.x * E; w0 < (1 << (ntl + tb)); w0 += blockDim.x * E) {
+        for (int w0 = threadIdx.x * 4 * E; w0 < (1 << (ntl + tb)); w0 += blockDim.x * 4 * E) {
             const int j = w0 >> tb, t = (w0 & ((1 << tb) - 1)) >> R;
             const uint8_t *src = st + (j << tb);
-            uint32_t wd[4] = {0u, 0u, 0u, 0u};
-            for (int i = 0; i < E; ++i) wd[i >> 2] |= (uint32_t)src[x_elem(t, i, rb, R)] << (8 * (i & 3));
+            uint32_t wd[4][E / 4];  // [thread t + b][its costs, 4 a word]
+#pragma unroll
+            for (int g = 0; g < E / 4; ++g) {
+                uint32_t w[4];  // elements 4g .. 4g + 3 of the four threads, one thread a byte
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const uint32_t *>(src + x_elem(t, 4 * g + i, rb, R));
+                const uint32_t l01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
+                const uint32_t h01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+                const uint32_t l23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+                const uint32_t h23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+                wd[0][g] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
+                wd[1][g] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
+                wd[2][g] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+                wd[3][g] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+            }
             uint8_t *dst = out + (tile0 << tb) + w0;
-            if (E == 16) *reinterpret_cast<uint4 *>(dst) = uint4{wd[0], wd[1], wd[2], wd[3]};
-            else *reinterpret_cast<uint2 *>(dst) = uint2{wd[0], wd[1]};
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if constexpr (E == 16) reinterpret_cast<uint4 *>(dst)[b] = uint4{wd[b][0], wd[b][1], wd[b][2], wd[b][3]};
+                else reinterpret_cast<uint2 *>(dst)[b] = uint2{wd[b][0], wd[b][1]};
+            }
         }
         __syncthreads();
     }
 }
 
 // ---- host ------------------------------------------------------------------------
+// Readouts of consecutive rounds, one block each. Nothing on the device waits
+// for them, so the rows of as many rounds as the partials hold are summed in one
+// launch: a launch and its gaps per round (6 us of the 120 us of a round at n =
+// 24, complex64) become one in up to kXFinMax.
+constexpr int kXFinMax = 32;
+
 struct XPartialFin {
     const double *partials;
-    int nblocks, stride, off;  // block b's P_sol, E, norm at partials[b*stride + off + 0..2]
-    double *readout;           // psol, E, norm
+    int stride, off;          // row b of block i: P_sol, E, norm at partials[first[i] + b*stride + off + 0..2]
+    uint32_t first[kXFinMax];
+    int32_t nblocks[kXFinMax];
+    double *readout;          // [gridDim.x][3]: psol, E, norm
 };
 
 __global__ void __launch_bounds__(1024) x_finalize_kernel(XPartialFin f) {
     __shared__ double lds[3 * 1024 / kWave];
     double r[3] = {0, 0, 0};
+    const double *rows = f.partials + f.first[blockIdx.x] + f.off;
+    const int nblocks = f.nblocks[blockIdx.x];
     // up to one row per pass block (32768 for the high groups at n = 28):
     // unrolled so that several rows' loads are in flight per thread
 #pragma unroll 8
-    for (int b = threadIdx.x; b < f.nblocks; b += 1024)
-        for (int k = 0; k < 3; ++k) r[k] += f.partials[(size_t)b * f.stride + f.off + k];
+    for (int b = threadIdx.x; b < nblocks; b += 1024)
+        for (int k = 0; k < 3; ++k) r[k] += rows[(size_t)b * f.stride + k];
     block_sum<3, 1024>(r, lds);
     if (threadIdx.x == 0)
-        for (int k = 0; k < 3; ++k) f.readout[k] = r[k];
+        for (int k = 0; k < 3; ++k) f.readout[3 * blockIdx.x + k] = r[k];
 }
 
 // Workspace: phase LUTs [max(p,1)][256] complex, readouts [p+1][3] doubles,
@@ -729,10 +769,33 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
     GQ_HIP(hipMemcpyAsync(L.lut, tab.data(), tab.size(), hipMemcpyHostToDevice, st));
     const double amp0 = 1.0 / std::sqrt((double)(1ull << n));
     auto lut = [&](int j) -> const void * { return L.lut + (size_t)j * 256 * cs; };  // phase of round j + 1
-    auto finalize = [&](int nblocks, int stride, int off, int j) -> int {
-        XPartialFin f{L.part, nblocks, stride, off, L.ro + 3 * (size_t)j};
-        hipLaunchKernelGGL(x_finalize_kernel, dim3(1), dim3(1024), 0, st, f);
+    // the readouts of rounds fin_j .. fin_j + fin_n - 1 wait in the partials;
+    // round j's are queued in the order of j
+    XPartialFin fin{};
+    fin.partials = L.part;
+    fin.stride = n <= TB ? kXR : 3;
+    fin.off = n <= TB ? 2 : 0;
+    int fin_j = 0, fin_n = 0;
+    size_t fin_used = 0;
+    auto flush = [&]() -> int {
+        if (!fin_n) return GQAOA_OK;
+        fin.readout = L.ro + 3 * (size_t)fin_j;
+        hipLaunchKernelGGL(x_finalize_kernel, dim3(fin_n), dim3(1024), 0, st, fin);
         GQ_LAUNCH_CHECK();
+        fin_j += fin_n;
+        fin_n = 0;
+        fin_used = 0;
+        return GQAOA_OK;
+    };
+    // room for the rows of the next readout (at most kXMaxBlocks)
+    auto rows_for = [&](int nblocks, double **rows) -> int {
+        const size_t want = (size_t)nblocks * fin.stride;
+        if (fin_n == kXFinMax || fin_used + want > 3 * (size_t)kXMaxBlocks)
+            if (const int rc = flush()) return rc;
+        fin.first[fin_n] = (uint32_t)fin_used;
+        fin.nblocks[fin_n++] = nblocks;
+        *rows = L.part + fin_used;
+        fin_used += want;
         return GQAOA_OK;
     };
 
@@ -753,7 +816,7 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
             a.target = target;
             a.c = c;
             a.s = sn;
-            a.partials = L.part;
+            if (const int rc = rows_for(1, &a.partials)) return rc;
             ProfScope ps(prof, st);
             if (dtype == GQAOA_C64)
                 hipLaunchKernelGGL(x_low_kernel<float>, dim3(1), dim3(kXThreads), smem, st, a);
@@ -761,7 +824,7 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
                 hipLaunchKernelGGL(x_low_kernel<double>, dim3(1), dim3(kXThreads), smem, st, a);
             ps.end();
             GQ_LAUNCH_CHECK();
-            return finalize(1, kXR, 2, j);
+            return GQAOA_OK;
         };
         for (int j = 0; j < p; ++j)
             if ((s = low(j, true, init_uniform && j == 0, std::cos(beta[j]), std::sin(beta[j])))) return s;
@@ -814,14 +877,19 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
                 const int cb = (int)std::max<uint64_t>(
                     1, std::min<uint64_t>(ntiles_of(gr) >> kXCopyTilesLog2, (uint64_t)dev.num_cus * 16));
                 uint8_t *dst = L.cost_t + (size_t)slot++ * ((total + 255) & ~uint64_t(255));
-                hipLaunchKernelGGL(x_cost_tiles_kernel, dim3(cb), dim3(256), 0, st, cost, dst, gr.tb, gr.mlo, gr.q0,
-                                   gr.plan.rb[gr.plan.nchunks - 1], R, ntiles_of(gr));
+                const int rb = gr.plan.rb[gr.plan.nchunks - 1];
+                if (R == 4)
+                    hipLaunchKernelGGL(x_cost_tiles_kernel<4>, dim3(cb), dim3(256), 0, st, cost, dst, gr.tb, gr.mlo,
+                                       gr.q0, rb, ntiles_of(gr));
+                else
+                    hipLaunchKernelGGL(x_cost_tiles_kernel<3>, dim3(cb), dim3(256), 0, st, cost, dst, gr.tb, gr.mlo,
+                                       gr.q0, rb, ntiles_of(gr));
                 GQ_LAUNCH_CHECK();
                 cost_of[b] = dst;
             }
             if (slot != x_copies(n, dtype)) return fail(GQAOA_EINVAL, "internal: %d X cost copies", slot);
         }
-        auto pass = [&](int gi, int ops, bool uniform, int ja, int jb, int readout_j) -> int {
+        auto pass = [&](int gi, int ops, bool uniform, int ja, int jb, bool readout) -> int {
             const XGroup &gr = groups[gi];
             const int blocks = blocks_of(gr);
             const size_t smem = smem_of(gr);
@@ -847,20 +915,20 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
                 a.cb = std::cos(beta[jb]);
                 a.sb = std::sin(beta[jb]);
             }
-            a.partials = L.part;
+            if (readout)
+                if (const int rc = rows_for(blocks, &a.partials)) return rc;
             ProfScope ps(prof, st);
             const int rc = dtype == GQAOA_C64 ? launch_pass<float>(ops, blocks, smem, st, a)
                                               : launch_pass<double>(ops, blocks, smem, st, a);
             ps.end();
-            if (rc) return rc;
-            return readout_j >= 0 ? finalize(blocks, 3, 0, readout_j) : GQAOA_OK;
+            return rc;
         };
         if (p == 0) {
             // readout of the initial state (written as |s> when init_uniform):
             // a pass with the identity phase and no mixer on group 0
             if (init_uniform) {
-                if ((s = pass(0, XOP_PRE | XOP_MIX_A, true, 0, 0, 0))) return s;
-            } else if ((s = pass(0, XOP_POST, false, 0, 0, 0))) {
+                if ((s = pass(0, XOP_PRE | XOP_MIX_A, true, 0, 0, true))) return s;
+            } else if ((s = pass(0, XOP_POST, false, 0, 0, true))) {
                 return s;
             }
         }
@@ -870,25 +938,26 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
             for (int k = 0; k < G; ++k) {
                 if (k == 0 && j > 0) continue;  // fused into the previous round's last pass
                 const int gi = x_order(G, fwd ? k : G - 1 - k);
-                int ops = XOP_MIX_A, readout = -1, jb = 0;
+                int ops = XOP_MIX_A, jb = 0;
+                bool readout = false;
                 if (j == 0 && k == 0) {
                     ops |= XOP_PRE;
-                    readout = 0;
+                    readout = true;
                 }
                 if (k == G - 1) {
+                    readout = true;
                     if (j + 1 < p) {
                         ops |= XOP_MID;
                         jb = j + 1;
-                        readout = j + 1;
                     } else {
                         ops |= XOP_POST;
-                        readout = p;
                     }
                 }
                 if ((s = pass(gi, ops, init_uniform && j == 0 && k == 0, j, jb, readout))) return s;
             }
         }
     }
+    if ((s = flush())) return s;
     std::vector<double> out((size_t)3 * (p + 1));
     GQ_HIP(hipMemcpyAsync(out.data(), L.ro, out.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     GQ_HIP(hipStreamSynchronize(st));

@@ -185,3 +185,30 @@ def test_every_size_of_the_last_group(dt, t):
         assert np.abs(ps - rp).max() < tol and np.abs(no - rn).max() < tol, n
         assert np.abs(en - re).max() < tol * m, n
         assert np.abs(psi.cpu().numpy() - rpsi).max() < tol, n
+
+
+@pytest.mark.parametrize("n,p", [(5, 31), (5, 32), (13, 33), (13, 64), (26, 10)])
+@pytest.mark.parametrize("dt", [g.C64, g.C128])
+def test_readouts_of_many_rounds(n, p, dt):
+    """Readouts are summed for up to 32 rounds in one launch, fewer when their
+    rows fill the partials (complex128 n = 26: 16,384 rows a round, four rounds):
+    p + 1 of them at, below and above those counts, each round's against the
+    same evolution stopped there (the same bits) and small n against the oracle
+    (rounds x rounding of the tested tolerance of five rounds)."""
+    need_gpu()
+    m = 8 if n == 5 else 60
+    lits = rand_lits(n, m, 700 + n)
+    cost, _ = g.gqaoa_cost_table(n, lits)
+    beta, gamma = inst.uniform_angles(700 + p, p)
+    log(f"x-qaoa readouts n={n} p={p} dtype={dt}")
+    got = g.gqaoa_evolve_x(n, m, cost, beta, gamma, dtype=dt)[1:]
+    for j in (0, 1, p // 2, p - 1):
+        part = g.gqaoa_evolve_x(n, m, cost, beta[:j], gamma[:j], dtype=dt)[1:]
+        for a, b in zip(got, part):
+            assert np.abs(a[:j + 1] - b).max() <= TOL[dt] * m   # the last readout of a shorter call: another pass's sums
+            if j > 1:
+                assert (a[:j] == b[:j]).all()
+    if n <= 13:
+        _, rpsol, renergy, rnorm = evolve_x(n, cost_table(n, lits), beta, gamma)
+        for a, r, scale in zip(got, (rpsol, renergy, rnorm), (1, m, 1)):
+            assert np.abs(a - r).max() < TOL[dt] * scale * max(1.0, p / 5)
