@@ -259,13 +259,13 @@ __device__ __forceinline__ void block_sum_row(double (&v)[R], double *lds, doubl
     }
 }
 
-// Sums of the first R entries of nrows <= kChainRows partial rows, in every
+// Sums of the first R entries of nrows <= kChainRows partial rows of STRIDE, in every
 // thread of a kSvThreads block: row 64 w + l by lane l of wave w (mod the
 // block's waves), then the waves' sums in order, as the finalize of one row per
 // thread adds them. Ends behind a barrier; lds is free again after the next.
 constexpr int kChainRows = 512;
 
-template <int R>
+template <int R, int STRIDE>
 __device__ __forceinline__ void sum_rows(const double *p, int nrows, double (&r)[R], double *lds) {
     constexpr int kWaves = kSvThreads / kWave, kPer = kChainRows / kSvThreads;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void sum_rows(const double *p, int nrows, double (&r)
     for (int i = 0; i < kPer; ++i) {
         const int b = (i * kWaves + wave) * kWave + lane;
 #pragma unroll
-        for (int k = 0; k < R; ++k) v[i][k] = b < nrows ? p[(size_t)b * kFwdR + k] : 0.0;
+        for (int k = 0; k < R; ++k) v[i][k] = b < nrows ? p[(size_t)b * STRIDE + k] : 0.0;
     }
     const int nw = (nrows + kWave - 1) / kWave;
 #pragma unroll
@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
         nblocks = a.fin.nblocks;
         if ((int)blockIdx.x == nblocks) {
             double r[kFwdR];
-            sum_rows<kFwdR>(rows, nblocks, r, red_s);
+            sum_rows<kFwdR, kFwdR>(rows, nblocks, r, red_s);
             if (threadIdx.x == 0) finalize_apply(a.fin, inst, r);
             return;
         }
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
         const double *mf = a.fin.mixf + (size_t)inst * a.fin.mixf_stride;
         const double mr = mf[0], mi = mf[1];
         double S[2], dr, di;
-        sum_rows<2>(rows, a.fin.nblocks, S, red_s);
+        sum_rows<2, kFwdR>(rows, a.fin.nblocks, S, red_s);
         mixer_delta(mr, mi, a.fin.inv_N, S[0], S[1], dr, di);
         dl = {T(dr), T(di)};
     } else {
@@ -612,6 +612,43 @@ static int launch_resident(const ResArgs &a, hipStream_t st) {
 }
 
 // ---- reverse (adjoint) pass -------------------------------------------------------
+struct RevFinArgs {
+    const double *partials;  // [inst][nblocks][kRevR]
+    int nblocks;
+    double inv_N;
+    double *dgamma_k;        // [inst * grad_stride]
+    // for k > 1: eps_{k-1} and dbeta_{k-1}
+    const double *mixb_km1;  // e^{+i beta_{k-1}} - 1
+    const double *ebeta_km1; // e^{-i beta_{k-1}}
+    const double *S_km1;     // S_{k-1}
+    int S_stride;
+    double *eps_out;
+    double *dbeta_km1;
+    int grad_stride;
+};
+
+// eps_{k-1} = (e^{+i beta_{k-1}} - 1) sum(lambda_{k-1}) / N
+__device__ __forceinline__ void rev_eps(double mr, double mi, double inv_N, double lr, double li, double &er,
+                                        double &ei) {
+    er = (mr * lr - mi * li) * inv_N;
+    ei = (mr * li + mi * lr) * inv_N;
+}
+
+__device__ __forceinline__ void rev_finalize_apply(const RevFinArgs &a, int inst, const double (&r)[kRevR]) {
+    a.dgamma_k[(size_t)inst * a.grad_stride] = 2.0 * r[3];
+    if (a.mixb_km1) {
+        const double *mb = a.mixb_km1 + (size_t)inst * a.grad_stride * 2;
+        const double lr = r[0], li = r[1];
+        double *e = a.eps_out + (size_t)inst * 2;
+        rev_eps(mb[0], mb[1], a.inv_N, lr, li, e[0], e[1]);
+        const double *eb = a.ebeta_km1 + (size_t)inst * a.grad_stride * 2;
+        const double *sp = a.S_km1 + (size_t)inst * a.S_stride;
+        const double xr = lr * sp[0] + li * sp[1], xi = lr * sp[1] - li * sp[0];
+        const double yi = eb[0] * xi + eb[1] * xr;
+        a.dbeta_km1[(size_t)inst * a.grad_stride] = 2.0 * yi * a.inv_N;
+    }
+}
+
 struct RevArgs {
     const uint8_t *cost;
     const void *phi;        // phi_k, [inst][N]
@@ -626,23 +663,30 @@ struct RevArgs {
     const double *delta_p;  // [inst][delta_stride] complex delta_p (first step only)
     int delta_stride;
     const int32_t *target;
-    double *partials;       // [inst][gridDim.x][kRevR]
+    double *partials;       // [inst][blocks][kRevR]
+    int chain;              // finalize the reverse pass before (fin), as the chained forward passes do
+    RevFinArgs fin;
 };
 
-template <typename T, bool FIRST, bool WRITE, int AMP, int UNROLL>
+template <typename T, bool FIRST, bool WRITE, int AMP, int UNROLL, bool CHAIN = false>
 __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
     __shared__ Cx<T> lut_s[256];
-    __shared__ double red_s[kRevR * kSvThreads / kWave];
+    __shared__ double red_s[kRevR * (CHAIN ? kChainRows : kSvThreads) / kWave];
     const int inst = blockIdx.y;
     const uint64_t ioff = (uint64_t)inst * a.N;
-    {
-        const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
-        for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
-        __syncthreads();
+    const double *rows = nullptr;
+    int nblocks = gridDim.x;
+    if constexpr (CHAIN) {
+        rows = a.fin.partials + (size_t)inst * a.fin.nblocks * kRevR;
+        nblocks = a.fin.nblocks;
+        if ((int)blockIdx.x == nblocks) {
+            double r[kRevR];
+            sum_rows<kRevR, kRevR>(rows, nblocks, r, red_s);
+            if (threadIdx.x == 0) rev_finalize_apply(a.fin, inst, r);
+            return;
+        }
     }
     const uint32_t target = (uint32_t)a.target[inst];
-    const double *e = a.eps + (size_t)inst * a.eps_stride;
-    const Cx<T> eps{T(e[0]), T(e[1])};
     Cx<T> dp{T(0), T(0)};
     if constexpr (FIRST) {
         const double *d = a.delta_p + (size_t)inst * a.delta_stride;
@@ -656,11 +700,11 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
     double accLr = 0, accLi = 0, accGr = 0, accGi = 0;
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t wave = ((uint64_t)blockIdx.x * kSvThreads + threadIdx.x) / kWave;
-    const uint64_t nwaves = (uint64_t)gridDim.x * kSvThreads / kWave;
+    const uint64_t nwaves = (uint64_t)nblocks * kSvThreads / kWave;
     constexpr uint64_t kTile = (uint64_t)kWave * AMP * UNROLL;
-    for (uint64_t base = wave * kTile; base < a.N; base += nwaves * kTile) {
-        uint32_t c[UNROLL][AMP];
-        Cx<T> f[UNROLL][AMP], l[UNROLL][AMP];
+    uint32_t c[UNROLL][AMP];
+    Cx<T> f[UNROLL][AMP], l[UNROLL][AMP];
+    auto load_tile = [&](uint64_t base) {
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const uint64_t idx = base + (uint64_t)u * kWave * AMP + (uint64_t)lane * AMP;
@@ -670,6 +714,25 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
                 if constexpr (!FIRST) AmpIO<T, AMP>::load(lin + idx, l[u]);
             }
         }
+    };
+    if constexpr (CHAIN) load_tile(wave * kTile);  // in flight during the sums below
+    const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
+    for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
+    Cx<T> eps;
+    if constexpr (CHAIN) {
+        const double *mb = a.fin.mixb_km1 + (size_t)inst * a.fin.grad_stride * 2;
+        const double mr = mb[0], mi = mb[1];
+        double L[2], er, ei;
+        sum_rows<2, kRevR>(rows, nblocks, L, red_s);
+        rev_eps(mr, mi, a.fin.inv_N, L[0], L[1], er, ei);
+        eps = {T(er), T(ei)};
+    } else {
+        __syncthreads();
+        const double *e = a.eps + (size_t)inst * a.eps_stride;
+        eps = {T(e[0]), T(e[1])};
+    }
+    for (uint64_t base = wave * kTile; base < a.N; base += nwaves * kTile) {
+        if constexpr (!CHAIN) load_tile(base);
         typename Acc<T>::t sLr = 0, sLi = 0, sGr = 0, sGi = 0;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
@@ -705,8 +768,9 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
             }
         }
     }
+    if constexpr (CHAIN) __syncthreads();  // red_s: read above, written below
     double r[kRevR] = {accLr, accLi, accGr, accGi};
-    block_sum_row<kRevR>(r, red_s, a.partials + ((size_t)inst * gridDim.x + blockIdx.x) * kRevR);
+    block_sum_row<kRevR>(r, red_s, a.partials + ((size_t)inst * nblocks + blockIdx.x) * kRevR);
 }
 
 // ---- finalizers (fixed-order sums of the per-block partial rows) -----------------
@@ -760,41 +824,13 @@ __global__ void __launch_bounds__(T) sv_finalize_kernel(FinArgs a) {
     if (threadIdx.x == 0) finalize_apply(a, inst, r);
 }
 
-struct RevFinArgs {
-    const double *partials;  // [inst][nblocks][kRevR]
-    int nblocks;
-    double inv_N;
-    double *dgamma_k;        // [inst * grad_stride]
-    // for k > 1: eps_{k-1} and dbeta_{k-1}
-    const double *mixb_km1;  // e^{+i beta_{k-1}} - 1
-    const double *ebeta_km1; // e^{-i beta_{k-1}}
-    const double *S_km1;     // S_{k-1}
-    int S_stride;
-    double *eps_out;
-    double *dbeta_km1;
-    int grad_stride;
-};
-
 template <int T>
 __global__ void __launch_bounds__(T) sv_rev_finalize_kernel(RevFinArgs a) {
     __shared__ double lds[kRevR * T / kWave];
     const int inst = blockIdx.x;
     double r[kRevR];
     reduce_partials<kRevR, T>(a.partials + (size_t)inst * a.nblocks * kRevR, a.nblocks, r, lds);
-    if (threadIdx.x != 0) return;
-    a.dgamma_k[(size_t)inst * a.grad_stride] = 2.0 * r[3];
-    if (a.mixb_km1) {
-        const double *mb = a.mixb_km1 + (size_t)inst * a.grad_stride * 2;
-        const double lr = r[0], li = r[1];
-        double *e = a.eps_out + (size_t)inst * 2;
-        e[0] = (mb[0] * lr - mb[1] * li) * a.inv_N;
-        e[1] = (mb[0] * li + mb[1] * lr) * a.inv_N;
-        const double *eb = a.ebeta_km1 + (size_t)inst * a.grad_stride * 2;
-        const double *sp = a.S_km1 + (size_t)inst * a.S_stride;
-        const double xr = lr * sp[0] + li * sp[1], xi = lr * sp[1] - li * sp[0];
-        const double yi = eb[0] * xi + eb[1] * xr;
-        a.dbeta_km1[(size_t)inst * a.grad_stride] = 2.0 * yi * a.inv_N;
-    }
+    if (threadIdx.x == 0) rev_finalize_apply(a, inst, r);
 }
 
 // ---- launch shapes ------------------------------------------------------------------
@@ -904,6 +940,12 @@ template <typename T, bool FIRST, bool WRITE>
 static void launch_rev_t(const PassShape &s, int num_inst, const RevArgs &a, hipStream_t st) {
     const dim3 grid(s.blocks_x, num_inst), block(kSvThreads);
     if constexpr (sizeof(T) == 4) {
+        if constexpr (!FIRST)
+            if (a.chain) {
+                const dim3 g1(s.blocks_x + 1, num_inst);
+                hipLaunchKernelGGL((sv_reverse_kernel<T, false, WRITE, 2, 4, true>), g1, block, 0, st, a);
+                return;
+            }
         if (s.unroll == 1) hipLaunchKernelGGL((sv_reverse_kernel<T, FIRST, WRITE, 2, 1>), grid, block, 0, st, a);
         else if (s.unroll == 4) hipLaunchKernelGGL((sv_reverse_kernel<T, FIRST, WRITE, 2, 4>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((sv_reverse_kernel<T, FIRST, WRITE, 2, 8>), grid, block, 0, st, a);
@@ -1124,13 +1166,15 @@ static bool fused_round(const FwdPlan &P) {
 // us, n = 18 7.7 -> 6.0, n = 20 10.5 -> 7.5). Every block pays for the rows, so
 // with more of them it turns: at n = 21 (1024 rows) 13.0 -> 13.2 us, and a batch
 // of 64 gradients of n = 20 (512 rows, 32,768 blocks) loses 6%; at 2,048 blocks in
-// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing.
+// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing. The
+// reverse passes of a gradient chain in the same way (1 of n = 18, p = 32: 613 ->
+// 535 us with both sweeps chained, 691 with neither).
 constexpr int kChainBlocks = 2048;
 
 static bool chain_rule(const FwdPlan &P) {
     const PassShape &s = P.shape;
     return P.dtype == GQAOA_C64 && P.p > 0 && s.amp == 2 && s.unroll == 4 && s.nt == 1 &&
-           s.blocks_x <= kChainRows && (uint64_t)s.blocks_x * kSvThreads * 8 == P.N &&
+           s.blocks_x <= kChainRows && (uint64_t)s.blocks_x * kSvThreads * 8 >= P.N &&
            (int64_t)P.num_inst * s.blocks_x <= kChainBlocks && !fused_round(P);
 }
 
@@ -1449,6 +1493,7 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
         if ((s = launch_finalize(P, fa, st))) return s;
     }
     // reverse sweep, segment by segment
+    RevFinArgs rev_pending{};  // finalize of the last chained pass, due in the next one
     const size_t cs = dtype == GQAOA_C64 ? 8 : 16;
     for (int sg = nseg - 1; sg >= 0; --sg) {
         const int k0 = sg * c, k1 = std::min(p, k0 + c);
@@ -1475,6 +1520,12 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
             r.delta_stride = 2 * (p + 1);
             r.target = reinterpret_cast<const int32_t *>(P.ws + P.L.target);
             r.partials = reinterpret_cast<double *>(P.ws + P.L.partials);
+            if (P.chain) {  // past the rows of the forward passes, which a recomputed segment writes
+                const size_t rows = (size_t)P.num_inst * P.shape.blocks_x;
+                r.partials += rows * (2 * kFwdR + (k & 1) * kRevR);
+                r.chain = k < p;
+                r.fin = rev_pending;
+            }
             ProfScope ps(dtype == GQAOA_C64 ? "sv_reverse_c64" : "sv_reverse_c128", st);
             launch_rev(dtype, k == p, k > 1, P.shape, P.num_inst, r, st);
             ps.end();
@@ -1492,6 +1543,10 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
                 rf.S_stride = 2 * (p + 1);
                 rf.eps_out = reinterpret_cast<double *>(P.ws + P.L.eps);
                 rf.dbeta_km1 = reinterpret_cast<double *>(P.ws + P.L.dbeta) + (k - 2);
+            }
+            if (P.chain && k > 1) {
+                rev_pending = rf;
+                continue;
             }
             if ((s = fold_for_finalize<kRevR>(P, rf.partials, &rf.partials, &rf.nblocks, st))) return s;
             if (rf.nblocks <= kFinWave)
