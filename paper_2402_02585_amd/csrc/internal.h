@@ -69,6 +69,12 @@ struct DeviceInfo {
 };
 int device_info(DeviceInfo *out);
 
+// Phase and mixer tables of num_inst instances' rounds from their angles on the
+// device (sv.hip).
+int phase_tables(int dtype, int num_inst, int p, const double *beta, const double *gamma, int stride,
+                 const int32_t *m_dev, int m_all, void *lut, double *mixf, double *mixb, double *ebeta,
+                 hipStream_t st);
+
 // ---- device-side helpers -----------------------------------------------------
 constexpr int kWave = 64;
 

@@ -1025,49 +1025,55 @@ size_t sv_workspace_bytes(int num_inst, int n, int p, int dtype, int ckpt_every,
     return sv_layout(num_inst, n, p, dtype, ckpt_every, grad).total;
 }
 
-// Host tables: phase LUTs e^{-i gamma_j k} (k = 0..m, gamma_j k reduced mod 2 pi in
-// double, rounded once to the state's precision), mixer factors per round.
-static void build_tables(int num_inst, const int32_t *m_of, int p, const double *beta,
-                         const double *gamma, int dtype, std::vector<char> &lut,
-                         std::vector<double> &mixf, std::vector<double> &mixb,
-                         std::vector<double> &ebeta) {
-    const size_t cs = dtype == GQAOA_C64 ? 8 : 16;
-    lut.assign((size_t)num_inst * p * 256 * cs, 0);
-    mixf.assign((size_t)num_inst * p * 2, 0.0);
-    mixb.assign((size_t)num_inst * p * 2, 0.0);
-    ebeta.assign((size_t)num_inst * p * 2, 0.0);
-    const double two_pi = 2.0 * M_PI;
-    for (int i = 0; i < num_inst; ++i) {
-        for (int j = 0; j < p; ++j) {
-            const double g = gamma[(size_t)i * p + j], b = beta[(size_t)i * p + j];
-            for (int k = 0; k <= m_of[i]; ++k) {
-                const double ang = std::fmod(g * (double)k, two_pi);
-                const double re = std::cos(ang), im = -std::sin(ang);
-                const size_t e = ((size_t)i * p + j) * 256 + k;
-                if (dtype == GQAOA_C64) {
-                    float *f = reinterpret_cast<float *>(lut.data()) + 2 * e;
-                    f[0] = (float)re;
-                    f[1] = (float)im;
-                } else {
-                    double *d = reinterpret_cast<double *>(lut.data()) + 2 * e;
-                    d[0] = re;
-                    d[1] = im;
-                }
-            }
-            const size_t q = ((size_t)i * p + j) * 2;
-            mixf[q] = std::cos(b) - 1.0;
-            mixf[q + 1] = -std::sin(b);
-            mixb[q] = std::cos(b) - 1.0;
-            mixb[q + 1] = std::sin(b);
-            ebeta[q] = std::cos(b);
-            ebeta[q + 1] = -std::sin(b);
+// Tables of every round: phases e^{-i gamma_j k} (k = 0..m, gamma_j k reduced mod
+// 2 pi in double, rounded once to the state's precision; zero above m) and mixer
+// factors. Block (j, i): round j of instance i, angles beta[i stride + j] and gamma
+// the same, m from m_dev (or m_all when m_dev is null); tables [i][p][256] and
+// [i][p][2], the mixer ones null where not wanted. They are made here and not on
+// the host because a sine and a cosine there cost 25 ns and the tables' bytes a
+// pageable copy: 64 gradients of n = 10, p = 20 spent 1.4 of 1.9 ms on them.
+template <typename T>
+__global__ void __launch_bounds__(256) phase_tables_kernel(const double *__restrict__ beta,
+                                                           const double *__restrict__ gamma, int stride, int p,
+                                                           const int32_t *__restrict__ m_dev, int m_all,
+                                                           T *__restrict__ lut, double *__restrict__ mixf,
+                                                           double *__restrict__ mixb, double *__restrict__ ebeta) {
+    const int j = blockIdx.x, k = threadIdx.x, i = blockIdx.y;
+    const int m = m_dev ? m_dev[i] : m_all;
+    const size_t a = (size_t)i * stride + j, e = (size_t)i * p + j;
+    T re = 0, im = 0;
+    if (k <= m) {
+        double sn, cs;
+        sincos(fmod(gamma[a] * (double)k, 2.0 * M_PI), &sn, &cs);
+        re = (T)cs;
+        im = (T)-sn;
+    }
+    lut[2 * (e * 256 + k)] = re;
+    lut[2 * (e * 256 + k) + 1] = im;
+    if (k == 0 && mixf) {
+        double sb, cb;
+        sincos(beta[a], &sb, &cb);
+        mixf[2 * e] = cb - 1.0;
+        mixf[2 * e + 1] = -sb;
+        if (mixb) {
+            mixb[2 * e] = cb - 1.0;
+            mixb[2 * e + 1] = sb;
+            ebeta[2 * e] = cb;
+            ebeta[2 * e + 1] = -sb;
         }
     }
 }
 
-static int upload(void *dst, const void *src, size_t bytes, hipStream_t st) {
-    if (!bytes) return GQAOA_OK;
-    GQ_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
+int phase_tables(int dtype, int num_inst, int p, const double *beta, const double *gamma, int stride,
+                 const int32_t *m_dev, int m_all, void *lut, double *mixf, double *mixb, double *ebeta,
+                 hipStream_t st) {
+    if (dtype == GQAOA_C64)
+        hipLaunchKernelGGL(phase_tables_kernel<float>, dim3(p, num_inst), dim3(256), 0, st, beta, gamma, stride, p, m_dev,
+                           m_all, reinterpret_cast<float *>(lut), mixf, mixb, ebeta);
+    else
+        hipLaunchKernelGGL(phase_tables_kernel<double>, dim3(p, num_inst), dim3(256), 0, st, beta, gamma, stride, p, m_dev,
+                           m_all, reinterpret_cast<double *>(lut), mixf, mixb, ebeta);
+    GQ_LAUNCH_CHECK();
     return GQAOA_OK;
 }
 
@@ -1250,12 +1256,12 @@ static int final_pass(FwdPlan &P, const void *psi_in, void *psi_out, bool unifor
     return launch_finalize(P, f, st);
 }
 
-static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, const uint8_t *cost,
-                        int p, const double *beta, const double *gamma, int dtype,
-                        const int32_t *targets, void *ws, int ckpt_every, bool grad,
-                        hipStream_t st, std::vector<char> &keep_lut, std::vector<double> &keep_f,
-                        std::vector<double> &keep_b, std::vector<double> &keep_e,
-                        std::vector<int32_t> &keep_t) {
+// Fills P and the tables of its rounds: angles, targets, the (zero) block
+// counters and the instances' m go up in one copy, the last into the partials,
+// which the first pass overwrites after the tables are made.
+static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int p,
+                        const double *beta, const double *gamma, int dtype, const int32_t *targets, void *ws,
+                        int ckpt_every, bool grad, hipStream_t st, std::unique_ptr<char[]> &up) {
     DeviceInfo dev;
     int s = device_info(&dev);
     if (s) return s;
@@ -1269,19 +1275,26 @@ static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, co
     P.shape = pass_shape(P.N, num_inst, dtype, dev, fuse_requested());
     P.chain = chain_rule(P);
     P.cost = cost;
+    const SvLayout &L = P.L;
+    const size_t I = (size_t)num_inst, m_at = L.partials - L.angles, bytes = m_at + I * 4;
+    up.reset(new (std::nothrow) char[bytes]);
+    if (!up) return fail(GQAOA_EINVAL, "out of host memory");
+    const size_t ang = I * p * sizeof(double);
     if (p > 0) {
-        build_tables(num_inst, m_of, p, beta, gamma, dtype, keep_lut, keep_f, keep_b, keep_e);
-        // the LUT block is laid out [inst][p][256]; the kernels index it with lut_stride p*256
-        if ((s = upload(P.ws + P.L.lut, keep_lut.data(), keep_lut.size(), st))) return s;
-        if ((s = upload(P.ws + P.L.mixf, keep_f.data(), keep_f.size() * 8, st))) return s;
-        if ((s = upload(P.ws + P.L.mixb, keep_b.data(), keep_b.size() * 8, st))) return s;
-        if ((s = upload(P.ws + P.L.ebeta, keep_e.data(), keep_e.size() * 8, st))) return s;
+        memcpy(up.get(), beta, ang);
+        memcpy(up.get() + ang, gamma, ang);
     }
-    keep_t.assign(targets, targets + num_inst);
-    if ((s = upload(P.ws + P.L.target, keep_t.data(), keep_t.size() * 4, st))) return s;
-    GQ_HIP(hipMemsetAsync(P.ws + P.L.delta, 0, (size_t)num_inst * (p + 1) * 16, st));
-    GQ_HIP(hipMemsetAsync(P.ws + P.L.counter, 0, (size_t)num_inst * 4, st));
-    return GQAOA_OK;
+    memcpy(up.get() + (L.target - L.angles), targets, I * 4);
+    memset(up.get() + (L.counter - L.angles), 0, I * 4);
+    memcpy(up.get() + m_at, m_of, I * 4);
+    GQ_HIP(hipMemcpyAsync(P.ws + L.angles, up.get(), bytes, hipMemcpyHostToDevice, st));
+    if (p == 0) return GQAOA_OK;
+    return phase_tables(dtype, num_inst, p, reinterpret_cast<const double *>(P.ws + L.angles),
+                        reinterpret_cast<const double *>(P.ws + L.angles + ang), p,
+                        reinterpret_cast<const int32_t *>(P.ws + L.partials), 0, P.ws + L.lut,
+                        reinterpret_cast<double *>(P.ws + L.mixf),
+                        grad ? reinterpret_cast<double *>(P.ws + L.mixb) : nullptr,
+                        grad ? reinterpret_cast<double *>(P.ws + L.ebeta) : nullptr, st);
 }
 
 // ---- entry points (validated by the ABI layer) ---------------------------------------------
@@ -1328,9 +1341,7 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
                int dtype, int init_uniform, void *psi, int target, double *psol, double *energy,
                double *norm, void *ws, hipStream_t st) {
     FwdPlan P;
-    std::vector<char> lut;
-    std::vector<double> f, b, e;
-    std::vector<int32_t> t;
+    std::unique_ptr<char[]> up;
     int s;
     const double *readout;
     if (level_form(dtype, init_uniform, p)) {
@@ -1342,8 +1353,7 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
     } else {
         int32_t m_of[1] = {m};
         int32_t tg[1] = {target};
-        if ((s = prepare_plan(P, 1, n, m_of, cost, p, beta, gamma, dtype, tg, ws, 0, false, st, lut, f, b, e, t)))
-            return s;
+        if ((s = prepare_plan(P, 1, n, m_of, cost, p, beta, gamma, dtype, tg, ws, 0, false, st, up))) return s;
         readout = reinterpret_cast<const double *>(P.ws + P.L.readout);
         if (resident_ok(n, dtype, p)) {
             ResArgs r{cost, psi, P.ws + P.L.lut, reinterpret_cast<const double *>(P.ws + P.L.mixf),
@@ -1371,12 +1381,10 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
 int run_solution_prob(int n, const uint8_t *cost, const void *psi, int dtype, int target,
                       double *out, void *ws, hipStream_t st) {
     FwdPlan P;
-    std::vector<char> lut;
-    std::vector<double> f, b, e;
-    std::vector<int32_t> t;
+    std::unique_ptr<char[]> up;
     int32_t m_of[1] = {255};
     int32_t tg[1] = {target};
-    int s = prepare_plan(P, 1, n, m_of, cost, 0, nullptr, nullptr, dtype, tg, ws, 0, false, st, lut, f, b, e, t);
+    int s = prepare_plan(P, 1, n, m_of, cost, 0, nullptr, nullptr, dtype, tg, ws, 0, false, st, up);
     if (s) return s;
     if ((s = final_pass(P, psi, const_cast<void *>(psi), false, false, st))) return s;
     double ro[3];
@@ -1444,11 +1452,8 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
     if (level_form(dtype, 1, p))
         return run_grad_level(num_inst, n, m_of, cost, p, beta, gamma, targets, psol, dbeta, dgamma, ws, st);
     FwdPlan P;
-    std::vector<char> lut;
-    std::vector<double> f, b, e;
-    std::vector<int32_t> t;
-    int s = prepare_plan(P, num_inst, n, m_of, cost, p, beta, gamma, dtype, targets, ws, ckpt_every,
-                         true, st, lut, f, b, e, t);
+    std::unique_ptr<char[]> up;
+    int s = prepare_plan(P, num_inst, n, m_of, cost, p, beta, gamma, dtype, targets, ws, ckpt_every, true, st, up);
     if (s) return s;
     const int c = (ckpt_every <= 0 || ckpt_every >= p) ? p : ckpt_every;
     const int nseg = (p + c - 1) / c;
@@ -1556,19 +1561,18 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
             GQ_LAUNCH_CHECK();
         }
     }
-    std::vector<double> ro((size_t)num_inst * (p + 1) * 3), db((size_t)num_inst * p), dg((size_t)num_inst * p);
-    GQ_HIP(hipMemcpyAsync(ro.data(), P.ws + P.L.readout, ro.size() * 8, hipMemcpyDeviceToHost, st));
-    GQ_HIP(hipMemcpyAsync(db.data(), P.ws + P.L.dbeta, db.size() * 8, hipMemcpyDeviceToHost, st));
-    GQ_HIP(hipMemcpyAsync(dg.data(), P.ws + P.L.dgamma, dg.size() * 8, hipMemcpyDeviceToHost, st));
+    // readouts .. dgamma: one run of the workspace, one copy
+    const SvLayout &L = P.L;
+    const size_t down_bytes = L.dgamma - L.readout + sizeof(double) * num_inst * p;
+    const std::unique_ptr<char[]> down(new (std::nothrow) char[down_bytes]);
+    if (!down) return fail(GQAOA_EINVAL, "out of host memory");
+    GQ_HIP(hipMemcpyAsync(down.get(), P.ws + L.readout, down_bytes, hipMemcpyDeviceToHost, st));
     GQ_HIP(hipStreamSynchronize(st));
     if (prof_on()) prof_collect();
-    for (int i = 0; i < num_inst; ++i) {
-        if (psol) psol[i] = ro[((size_t)i * (p + 1) + p) * 3];
-        for (int k = 0; k < p; ++k) {
-            if (dbeta) dbeta[(size_t)i * p + k] = db[(size_t)i * p + k];
-            if (dgamma) dgamma[(size_t)i * p + k] = dg[(size_t)i * p + k];
-        }
-    }
+    const double *ro = reinterpret_cast<const double *>(down.get());
+    for (int i = 0; i < num_inst && psol; ++i) psol[i] = ro[((size_t)i * (p + 1) + p) * 3];
+    if (dbeta) memcpy(dbeta, down.get() + (L.dbeta - L.readout), sizeof(double) * num_inst * p);
+    if (dgamma) memcpy(dgamma, down.get() + (L.dgamma - L.readout), sizeof(double) * num_inst * p);
     return GQAOA_OK;
 }
 
@@ -1578,37 +1582,7 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
 // launches dominate): the whole call — angle tables, p round passes with
 // their finalizes, the final readout pass — is captured once into a HIP
 // graph. A run uploads the 2p angles, replays the graph and reads back the
-// readouts; the tables are computed on the device from the angles, with the
-// same float64 reduction and rounding as the host tables of run_evolve.
-// Block (j, i): round j of instance i; ang[i] = (beta[p], gamma[p]), the
-// instance's m from m_dev (or m_all when m_dev is null); tables [i][p][256]
-// and [i][p][2].
-template <typename T>
-__global__ void __launch_bounds__(256) evolve_tables_kernel(const double *__restrict__ ang, int p,
-                                                            const int32_t *__restrict__ m_dev, int m_all,
-                                                            T *__restrict__ lut, double *__restrict__ mixf) {
-    const int j = blockIdx.x, k = threadIdx.x, i = blockIdx.y;
-    const int m = m_dev ? m_dev[i] : m_all;
-    ang += (size_t)i * 2 * p;
-    lut += (size_t)i * p * 256 * 2;
-    mixf += (size_t)i * p * 2;
-    T re = 0, im = 0;
-    if (k <= m) {
-        double sn, cs;
-        sincos(fmod(ang[p + j] * (double)k, 2.0 * M_PI), &sn, &cs);
-        re = (T)cs;
-        im = (T)-sn;
-    }
-    lut[2 * ((size_t)j * 256 + k)] = re;
-    lut[2 * ((size_t)j * 256 + k) + 1] = im;
-    if (k == 0) {
-        double sb, cb;
-        sincos(ang[j], &sb, &cb);
-        mixf[2 * j] = cb - 1.0;
-        mixf[2 * j + 1] = -sb;
-    }
-}
-
+// readouts.
 struct EvolvePlan {
     FwdPlan P;
     int device = -1, m = 0;
@@ -1647,21 +1621,17 @@ static int enqueue_evolve(EvolvePlan *E, int init_uniform, void *psi, hipStream_
     FwdPlan &P = E->P;
     if (level_form(P.dtype, init_uniform, P.p))
         return level_evolve(level_args(P.n, E->m, P.cost, P.p, init_uniform, psi, *E->target_host, P.ws), true, st);
-    const double *ang = reinterpret_cast<const double *>(P.ws + P.L.angles);
     double *mixf = reinterpret_cast<double *>(P.ws + P.L.mixf);
-    if (P.dtype == GQAOA_C64)
-        hipLaunchKernelGGL(evolve_tables_kernel<float>, dim3(P.p), dim3(256), 0, st, ang, P.p, nullptr, E->m,
-                           reinterpret_cast<float *>(P.ws + P.L.lut), mixf);
-    else
-        hipLaunchKernelGGL(evolve_tables_kernel<double>, dim3(P.p), dim3(256), 0, st, ang, P.p, nullptr, E->m,
-                           reinterpret_cast<double *>(P.ws + P.L.lut), mixf);
-    GQ_LAUNCH_CHECK();
+    int s;
+    const double *ang = reinterpret_cast<const double *>(P.ws + P.L.angles);
+    if ((s = phase_tables(P.dtype, 1, P.p, ang, ang + P.p, P.p, nullptr, E->m, P.ws + P.L.lut, mixf, nullptr, nullptr,
+                          st)))
+        return s;
     if (resident_ok(P.n, P.dtype, P.p)) {
         ResArgs r{P.cost, psi, P.ws + P.L.lut, mixf, reinterpret_cast<double *>(P.ws + P.L.readout), P.n, P.p,
                   init_uniform, *E->target_host};
         return launch_resident(r, st);
     }
-    int s;
     for (int j = 1; j <= P.p; ++j)
         if ((s = forward_round(P, j, psi, psi, init_uniform && j == 1, true, st))) return s;
     return final_pass(P, psi, psi, false, true, st);
@@ -1819,11 +1789,11 @@ int sv_items_stream(int n, int count, const int32_t *item_inst, const int32_t *i
                            dim3(256), 0, st, costs, reinterpret_cast<const uint64_t *>(base + o_off), N,
                            reinterpret_cast<uint8_t *>(base + o_cost));
         GQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(evolve_tables_kernel<float>, dim3(p, cnt), dim3(256), 0, st,
-                           reinterpret_cast<const double *>(base + P.L.angles), p,
-                           reinterpret_cast<const int32_t *>(base + o_m), 0, reinterpret_cast<float *>(base + P.L.lut),
-                           reinterpret_cast<double *>(base + P.L.mixf));
-        GQ_LAUNCH_CHECK();
+        const double *ang_dev = reinterpret_cast<const double *>(base + P.L.angles);
+        if ((s = phase_tables(GQAOA_C64, cnt, p, ang_dev, ang_dev + p, 2 * p,
+                              reinterpret_cast<const int32_t *>(base + o_m), 0, base + P.L.lut,
+                              reinterpret_cast<double *>(base + P.L.mixf), nullptr, nullptr, st)))
+            return s;
         void *psi = base + o_psi;
         for (int j = 1; j <= p; ++j)
             if ((s = forward_round(P, j, psi, psi, j == 1, true, st))) return s;

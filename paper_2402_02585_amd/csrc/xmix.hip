@@ -745,28 +745,13 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
     const int TBW = dtype == GQAOA_C64 ? XCfg<float>::TBW : XCfg<double>::TBW;
     const int R = dtype == GQAOA_C64 ? XCfg<float>::R : XCfg<double>::R;
     const char *prof = dtype == GQAOA_C64 ? "x_pass_c64" : "x_pass_c128";
-    std::vector<char> tab((size_t)std::max(p, 1) * 256 * cs, 0);
-    const double two_pi = 2.0 * M_PI;
-    for (int j = 0; j < p; ++j)
-        for (int k = 0; k < 256; ++k) {
-            const double ang = std::fmod(gamma[j] * (double)k, two_pi);
-            if (dtype == GQAOA_C64) {
-                float *f = reinterpret_cast<float *>(tab.data()) + 2 * ((size_t)j * 256 + k);
-                f[0] = (float)std::cos(ang);
-                f[1] = (float)-std::sin(ang);
-            } else {
-                double *d = reinterpret_cast<double *>(tab.data()) + 2 * ((size_t)j * 256 + k);
-                d[0] = std::cos(ang);
-                d[1] = -std::sin(ang);
-            }
-        }
-    if (p == 0) {  // the identity phase, for the p = 0 readout pass
-        for (int k = 0; k < 256; ++k) {
-            if (dtype == GQAOA_C64) reinterpret_cast<float *>(tab.data())[2 * k] = 1.0f;
-            else reinterpret_cast<double *>(tab.data())[2 * k] = 1.0;
-        }
-    }
-    GQ_HIP(hipMemcpyAsync(L.lut, tab.data(), tab.size(), hipMemcpyHostToDevice, st));
+    // The tables' angles wait in the partials (room for more rounds than the entry
+    // points take), which the first pass overwrites after the tables are made. One
+    // round of angle 0 for p = 0: the identity phase of its readout pass.
+    const double zero = 0.0;
+    GQ_HIP(hipMemcpyAsync(L.part, p > 0 ? gamma : &zero, (size_t)std::max(p, 1) * sizeof(double), hipMemcpyHostToDevice, st));
+    if ((s = phase_tables(dtype, 1, std::max(p, 1), nullptr, L.part, 0, nullptr, 255, L.lut, nullptr, nullptr, nullptr, st)))
+        return s;
     const double amp0 = 1.0 / std::sqrt((double)(1ull << n));
     auto lut = [&](int j) -> const void * { return L.lut + (size_t)j * 256 * cs; };  // phase of round j + 1
     // the readouts of rounds fin_j .. fin_j + fin_n - 1 wait in the partials;

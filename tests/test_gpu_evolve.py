@@ -10,6 +10,7 @@ from gpu_common import c2_instance, log, need_gpu, rand_lits, rand_state
 from oracle import brute
 from oracle.cost import cost_table, level_histogram, min_level
 from oracle.evolve import evolve_hist, evolve_sv
+from oracle.grad import grad_sv
 from paper_2402_02585_amd import gqaoa as g
 from paper_2402_02585_amd import instances as inst
 
@@ -267,3 +268,28 @@ def test_alternating_tile_order_n28(p):
     assert (got[0] - want[0]).abs().max().item() < 2.0 ** -14 * (p + 1) * 8 * 2.0 ** -24
     del a, psi0, want, got
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dt", [g.C64, g.C128])
+def test_tables_of_a_batch_with_uneven_m(dt, monkeypatch):
+    """Phase and mixer tables are made on the device for all rounds of all
+    instances: sweeps of instances with different m, targets and angles in one
+    call are those of single calls (the same bits), the largest gamma k included
+    (its reduction is exact), and within the tolerance of the oracle."""
+    torch = need_gpu()
+    monkeypatch.setenv("GQAOA_SV_RESIDENT", "0")   # complex128 by sweeps too
+    n, p, ms = 8, 3, [1, 40, 255]
+    lits = [rand_lits(n, m, 900 + m) for m in ms]
+    refs = [cost_table(n, x) for x in lits]
+    costs = torch.stack([g.gqaoa_cost_table(n, x)[0] for x in lits])
+    beta, gamma = (np.stack(a) for a in zip(*(inst.uniform_angles(900 + m, p) for m in ms)))
+    gamma[2] *= 1e3
+    targets = [min_level(level_histogram(c, m)) for c, m in zip(refs, ms)]
+    P, db, dg = g.gqaoa_grad_batched(n, ms, costs, beta, gamma, dtype=dt, targets=targets, ckpt_every=0)
+    for i, m in enumerate(ms):
+        log(f"tables m={m} dt={dt}")
+        one = g.gqaoa_grad(n, m, costs[i].contiguous(), beta[i], gamma[i], dtype=dt, target_level=targets[i], ckpt_every=0)
+        assert P[i] == one[0] and (db[i] == one[1]).all() and (dg[i] == one[2]).all()
+        rP, rb, rg = grad_sv(n, refs[i], beta[i], gamma[i], target=targets[i])
+        assert abs(P[i] - rP) < TOL[dt]
+        assert np.abs(db[i] - rb).max() < TOL[dt] * 4 and np.abs(dg[i] - rg).max() < TOL[dt] * 4 * m
