@@ -222,10 +222,14 @@ __device__ __forceinline__ void planes_to_bytes(const uint32_t (&v)[8], uint32_t
 }
 
 // Per-lane level counters for NB aligned blocks of 32 levels starting at
-// level 32 a0, fed straight from the bit planes: the assignments of a word at
-// level 32 a + k are the word bits where the planes spell a (planes 5..7) and
-// k (planes 0..4), found with a shared AND tree and counted with popcounts.
-// Levels outside the window are returned as a word-bit mask for the caller.
+// level 32 a0, fed straight from the bit planes. A block's word bits are those
+// where planes 5..7 spell a; cnt[S] counts the ones where the planes of the
+// set S (of 0..4) are all set, one AND and one popcount a set, and the level
+// counts follow by inclusion and exclusion once, at the flush. That is 58
+// instructions a block where a mask for each level takes 80, and the sets of
+// plane 4 (levels 16..31), or of planes 3 and 4 (24..31), are skipped where no
+// lane has them. Levels outside the window are returned as a word-bit mask for
+// the caller.
 template <int NB>
 struct LevelWindow {
     uint32_t cnt[NB][32];
@@ -245,19 +249,21 @@ struct LevelWindow {
             const uint32_t hi = (v[5] ^ ((a & 1) ? 0u : ~0u)) & (v[6] ^ ((a & 2) ? 0u : ~0u)) &
                                 (v[7] ^ ((a & 4) ? 0u : ~0u));
             in |= hi;
+            uint32_t p[16];  // p[S]: the planes of S and hi
+            p[0] = hi;
 #pragma unroll
-            for (int k43 = 0; k43 < 4; ++k43) {
-                const uint32_t t3 = hi & ((k43 & 2) ? v[4] : ~v[4]) & ((k43 & 1) ? v[3] : ~v[3]);
-#pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) {
-                    const uint32_t t2 = t3 & (b2 ? v[2] : ~v[2]);
-#pragma unroll
-                    for (int k10 = 0; k10 < 4; ++k10) {
-                        const uint32_t leaf = t2 & ((k10 & 2) ? v[1] : ~v[1]) & ((k10 & 1) ? v[0] : ~v[0]);
-                        cnt[i][(k43 << 3) | (b2 << 2) | k10] += (uint32_t)__builtin_popcount(leaf);
-                    }
-                }
+            for (int s = 1; s < 16; ++s) {
+                const int top = s >= 8 ? 3 : s >= 4 ? 2 : s >= 2 ? 1 : 0, rest = s ^ (1 << top);
+                p[s] = v[top] & p[rest];
             }
+#pragma unroll
+            for (int s = 0; s < 16; ++s) cnt[i][s] += (uint32_t)__builtin_popcount(p[s]);
+            if (__ballot((v[4] & hi) != 0u) == 0) continue;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) cnt[i][16 + s] += (uint32_t)__builtin_popcount(v[4] & p[s]);
+            if (__ballot((v[4] & p[8]) != 0u) == 0) continue;
+#pragma unroll
+            for (int s = 8; s < 16; ++s) cnt[i][16 + s] += (uint32_t)__builtin_popcount(v[4] & p[s]);
         }
         return ~in;
     }
@@ -268,17 +274,26 @@ struct LevelWindow {
         const int lane = threadIdx.x & (kWave - 1);
         uint32_t *copy = h + (lane >> 4) * kHistStride;  // h: the wave's first copy
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+        for (int i = 0; i < NB; ++i) {
+            uint32_t lev[32];  // sets to levels: exactly S = S less S and one more plane
+#pragma unroll
+            for (int k = 0; k < 32; ++k) lev[k] = cnt[i][k];
+#pragma unroll
+            for (int b = 0; b < 5; ++b)
+#pragma unroll
+                for (int k = 0; k < 32; ++k)
+                    if (!((k >> b) & 1)) lev[k] -= lev[k | (1 << b)];
 #pragma unroll
             for (int k = 0; k < 32; ++k) {
-                if (a0 + i >= 8 || __ballot(cnt[i][k] != 0u) == 0) continue;
-                int s = (int)cnt[i][k];
+                if (a0 + i >= 8 || __ballot(lev[k] != 0u) == 0) continue;
+                int s = (int)lev[k];
                 s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, true);  // row_shr:1
                 s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, true);  // row_shr:2
                 s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, true);  // row_shr:4
                 s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, true);  // row_shr:8
                 if ((lane & 15) == 15) atomicAdd(copy + 32 * (a0 + i) + k, (uint32_t)s);
             }
+        }
     }
 };
 
@@ -395,6 +410,10 @@ __global__ void __launch_bounds__(256) hist_reduce_kernel(const uint32_t *__rest
 // Clause ingest runs on the device here: each block builds its instance's
 // records from the raw literals straight into LDS, so the host uploads 12
 // bytes per clause and packs nothing.
+// The kernel is bound by its vector instructions (76% of the issue slots at 4096
+// instances of n = 8..20). NB, the 32-level blocks of the counting window, is 1
+// for m <= 129: 126 registers and four waves a SIMD against 160 and three, and
+// half the counting; with the sets of LevelWindow 330 -> 190 us.
 struct HistInst {
     uint32_t lit_off;   // first clause of the instance in the literal array
     int32_t n, m;
@@ -407,6 +426,7 @@ struct HistUnit {
 
 constexpr uint32_t kSumsRun = 8;  // shortest run of tiles per wave that takes the class sums
 
+template <int NB>
 __global__ void __launch_bounds__(kCostThreads)
 hist_batched_kernel(const HistInst *__restrict__ insts, const HistUnit *__restrict__ units,
                     const int32_t *__restrict__ lits, int neff, unsigned long long *__restrict__ hists,
@@ -449,7 +469,7 @@ hist_batched_kernel(const HistInst *__restrict__ insts, const HistUnit *__restri
     __syncthreads();
     uint32_t *h = hist_copy(lds);
     EffEntry(*eff)[2] = lds.wave_eff(neff);
-    LevelWindow<2> win;
+    LevelWindow<NB> win;
     win.clear(in.win_a0);
     // the unit's tiles in equal runs, one per wave
     const uint32_t run = (unit.ntiles + kCostWaves - 1) / kCostWaves;
@@ -457,8 +477,8 @@ hist_batched_kernel(const HistInst *__restrict__ insts, const HistUnit *__restri
     uint8_t *cost = costs ? costs + in.cost_off : nullptr;
     if (t0 < unit.ntiles) {
         const uint32_t nt = min(run, unit.ntiles - t0);
-        if (run >= kSumsRun) wave_tiles<2, true>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
-        else wave_tiles<2, false>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
+        if (run >= kSumsRun) wave_tiles<NB, true>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
+        else wave_tiles<NB, false>(lds.rec, cc, eff, unit.tile0 + t0, nt, in.n, cost, win, h);
     }
     win.flush(wave_copies(lds));
     __syncthreads();
@@ -627,18 +647,33 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
     int max_m = 1;
     for (int i = 0; i < num_inst; ++i) max_m = std::max(max_m, m_host[i]);
     uint64_t cost_off = 0;
-    int win_a0[256];  // by m, filled as they occur
+    int win_a0[256], win_nb[256];  // by m, filled as they occur
     std::fill(win_a0, win_a0 + 256, -1);
     units.reserve((size_t)num_inst + all_tiles / unit_tiles);
+    // Units in the order of their launches (windows of one 32-level block, then
+    // of two) and by falling n in each, so that the last blocks to start are the
+    // shortest. start[key]: where the instances of a key begin in `order`.
+    auto key = [&](int i) { return (win_nb[m_host[i]] - 1) * 32 + 31 - n_host[i]; };
+    int start[65] = {0};
     for (int i = 0; i < num_inst; ++i) {
-        int &a0 = win_a0[m_host[i]], nb = 1;
-        if (a0 < 0) level_window(m_host[i], &a0, &nb);
+        int &a0 = win_a0[m_host[i]];
+        if (a0 < 0) level_window(m_host[i], &a0, &win_nb[m_host[i]]);
         insts[i] = HistInst{(uint32_t)off, n_host[i], m_host[i], a0, cost_off};
         cost_off += ((1ull << n_host[i]) + 63) & ~63ull;
         off += (size_t)m_host[i];
+        ++start[key(i) + 1];
+    }
+    for (int k = 0; k < 64; ++k) start[k + 1] += start[k];
+    const int num_one = start[32];
+    std::vector<int32_t> order(num_inst);
+    for (int i = 0; i < num_inst; ++i) order[start[key(i)]++] = i;
+    size_t units_one = 0;
+    for (int o = 0; o < num_inst; ++o) {
+        const int i = order[o];
         const uint32_t ntiles = n_host[i] > kHighBit0 ? 1u << (n_host[i] - kHighBit0) : 1u;
         for (uint32_t t0 = 0; t0 < ntiles; t0 += unit_tiles)
             units.push_back(HistUnit{(uint32_t)i, t0, std::min(unit_tiles, ntiles - t0), 0u});
+        if (o + 1 == num_one) units_one = units.size();
     }
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t b_inst = sizeof(HistInst) * insts.size();
@@ -653,12 +688,19 @@ int launch_hist_batched(int num_inst, const int32_t *n_host, const int32_t *m_ho
     GQ_HIP(hipMemcpyAsync(base + o_unit, units.data(), b_unit, hipMemcpyHostToDevice, stream));
     GQ_HIP(hipMemcpyAsync(base + o_lits, lits, b_lits, hipMemcpyHostToDevice, stream));
     if (hists) GQ_HIP(hipMemsetAsync(hists, 0, sizeof(uint64_t) * (size_t)num_inst * hist_stride, stream));
-    hipLaunchKernelGGL(hist_batched_kernel, dim3((unsigned)units.size()), dim3(kCostThreads), cost_lds_bytes(max_m),
-                       stream,
-                       reinterpret_cast<const HistInst *>(base), reinterpret_cast<const HistUnit *>(base + o_unit),
-                       reinterpret_cast<const int32_t *>(base + o_lits), eff_entries(max_m),
-                       reinterpret_cast<unsigned long long *>(hists), hist_stride, costs);
-    GQ_LAUNCH_CHECK();
+    auto launch = [&](auto kernel, size_t first, size_t count) -> int {
+        if (!count) return GQAOA_OK;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3(kCostThreads), cost_lds_bytes(max_m), stream,
+                           reinterpret_cast<const HistInst *>(base),
+                           reinterpret_cast<const HistUnit *>(base + o_unit) + first,
+                           reinterpret_cast<const int32_t *>(base + o_lits), eff_entries(max_m),
+                           reinterpret_cast<unsigned long long *>(hists), hist_stride, costs);
+        GQ_LAUNCH_CHECK();
+        return GQAOA_OK;
+    };
+    int s;
+    if ((s = launch(hist_batched_kernel<1>, 0, units_one))) return s;
+    if ((s = launch(hist_batched_kernel<2>, units_one, units.size() - units_one))) return s;
     GQ_HIP(hipStreamSynchronize(stream));  // the host tables above end with this call
     return GQAOA_OK;
 }

@@ -100,3 +100,32 @@ def test_full_size_n28_whole_table_and_histogram():
     np.testing.assert_array_equal(hist.cpu().numpy(), ref_hist)
     del cost
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("mono", [False, True])
+def test_batches_of_both_window_widths(mono):
+    """Batches whose instances need one or two 32-level windows (m up to 129,
+    from 130 on, and from 200 on a window that starts at level 0 or higher) and
+    whose blocks are launched by falling n: histograms and tables in the order
+    of the call, exact. `mono` repeats clauses, so that states sit in every
+    fourth of a window and far outside it."""
+    need_gpu()
+    ns = [3, 14, 5, 12, 11, 16, 12, 9, 13, 4, 15, 12]
+    ms = [1, 130, 20, 129, 255, 131, 64, 24, 200, 8, 250, 7]
+    lits = []
+    for i, (n, m) in enumerate(zip(ns, ms)):
+        x = np.asarray(rand_lits(n, min(m, 4), 40 + i)) if mono else np.asarray(rand_lits(n, m, 40 + i))
+        lits.append(np.resize(x.reshape(-1, 3), (m, 3)) if mono else x)
+    log(f"window batches mono={mono}")
+    hd = g.gqaoa_hist_batched(ns, ms, lits).cpu().numpy()
+    costs, off, hc = g.gqaoa_cost_batched(ns, ms, lits)
+    costs = costs.cpu().numpy()
+    for i, (n, m) in enumerate(zip(ns, ms)):
+        ref = cost_table(n, lits[i])
+        np.testing.assert_array_equal(hd[i, :m + 1], level_histogram(ref, m))
+        np.testing.assert_array_equal(hc[i, :m + 1].cpu().numpy(), level_histogram(ref, m))
+        assert not hd[i, m + 1:].any()
+        np.testing.assert_array_equal(costs[off[i]:off[i] + (1 << n)], ref.astype(np.uint8))
+        c1, h1 = g.gqaoa_cost_table(n, lits[i])
+        np.testing.assert_array_equal(c1.cpu().numpy(), ref.astype(np.uint8))
+        np.testing.assert_array_equal(h1.cpu().numpy(), level_histogram(ref, m))
