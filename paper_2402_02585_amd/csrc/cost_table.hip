@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(256) hist_reduce_kernel(const uint32_t *__rest
 // bytes per clause and packs nothing.
 // The kernel is bound by its vector instructions (76% of the issue slots at 4096
 // instances of n = 8..20). NB, the 32-level blocks of the counting window, is 1
-// for m <= 129: 126 registers and four waves a SIMD against 160 and three, and
+// for m <= 128: 126 registers and four waves a SIMD against 160 and three, and
 // half the counting; with the sets of LevelWindow 330 -> 190 us.
 struct HistInst {
     uint32_t lit_off;   // first clause of the instance in the literal array

@@ -104,8 +104,8 @@ def test_full_size_n28_whole_table_and_histogram():
 
 @pytest.mark.parametrize("mono", [False, True])
 def test_batches_of_both_window_widths(mono):
-    """Batches whose instances need one or two 32-level windows (m up to 129,
-    from 130 on, and from 200 on a window that starts at level 0 or higher) and
+    """Batches whose instances need one or two 32-level windows (m up to 128,
+    from 129 on, and from 200 on a window that starts at level 0 or higher) and
     whose blocks are launched by falling n: histograms and tables in the order
     of the call, exact. `mono` repeats clauses, so that states sit in every
     fourth of a window and far outside it."""
