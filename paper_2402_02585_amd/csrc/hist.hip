@@ -246,7 +246,7 @@ struct ScanReach {
     // P after a round with r more to come
     __device__ __forceinline__ bool out_of_reach(float P, int r) const {
         const float t = th - (float)r * d;
-        const float s = sinf(t);
+        const float s = __sinf(t);  // 0 < t <= pi/2: good to 1e-6, far within the margins
         return t > 0.f && P < rel * s * s - 1e-4f;
     }
 };
@@ -306,11 +306,14 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
             sr = __builtin_fmaf(e.w, nr, sr);
             si = __builtin_fmaf(e.w, ni, si);
         }
-        cr = mr * sr - mi * si;
-        ci = mr * si + mi * sr;
+        // Which product is rounded first is written out: first crossings are whole
+        // numbers, compared exactly, and each size keeps the order it has had.
+        cr = __builtin_fmaf(mr, sr, -(mi * si));
+        if constexpr (CROSS && KMAX >= 20 && KMAX <= 32) ci = __builtin_fmaf(mi, sr, mr * si);
+        else ci = __builtin_fmaf(mr, si, mi * sr);
         if constexpr (CROSS) {
             const float b0r = pr[0] + cr, b0i = pi[0] + ci;
-            const float P = w0 * (b0r * b0r + b0i * b0i);
+            const float P = w0 * __builtin_fmaf(b0r, b0r, b0i * b0i);
             if (found == 0 && P >= a.threshold) found = j;
             bool live = active && found == 0;
             if (j % kReachEvery == 0) live = live && !reach.out_of_reach(P, pmax - j);
@@ -320,10 +323,10 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const float br = pr[k] + cr, bi = pi[k] + ci;
-                E = __builtin_fmaf(kw[k], br * br + bi * bi, E);
+                E = __builtin_fmaf(kw[k], __builtin_fmaf(br, br, bi * bi), E);
             }
             const float b0r = pr[0] + cr, b0i = pi[0] + ci;
-            const float P = w0 * (b0r * b0r + b0i * b0i);
+            const float P = w0 * __builtin_fmaf(b0r, b0r, b0i * b0i);
             if (active) {
                 const size_t o = (((size_t)sl.inst * a.num_p + q) * a.ng + it.g) * a.nb + b;
                 a.psol[o] = P;
@@ -351,6 +354,17 @@ __device__ __forceinline__ void scan_mixer(const ScanArgs &a, const ScanSlot &sl
     mi = (float)(-sb);
 }
 
+// Waves per SIMD a crossing kernel is held to. Two waves can keep a SIMD issuing,
+// but only while neither waits for a result; a third covers that. Without a bound
+// the compiler keeps the constants of the tables' sines in registers from item to
+// item (185 for KMAX = 20, 209 for 24, 205 for 28: two waves); held to 168 it
+// reloads what it has to once an item, never in a round. 128 instances, 360 x 181
+// pairs: n = 12..20 of density 4.6..8 8,500 -> 7,980 us, of 3..5 6,300 -> 5,800; 32
+// levels at three waves would spill in their rounds (8,900 us). The fixed rounds of
+// the other kernels are too short for it: 1,024 instances of 64 x 64 pairs, 64
+// rounds within 1%, 16 rounds 413 -> 430 us.
+constexpr int scan_waves_per_simd(int kmax) { return kmax <= 12 ? 4 : kmax <= 28 ? 3 : 1; }
+
 // CROSS = false: P_sol (and E) after each p in p_list. Every item of a bucket
 // costs the same (same padded level count, same rounds), so wave w of the
 // grid takes items w, w + W, w + 2W, ... (W waves), and the next item's
@@ -359,7 +373,7 @@ __device__ __forceinline__ void scan_mixer(const ScanArgs &a, const ScanSlot &sl
 // once every lane has crossed, so items differ in length and come from a
 // global queue (the next index is fetched while the current item runs).
 template <int KMAX, bool CROSS>
-__global__ void __launch_bounds__(kScanMaxWaves * 64) scan_kernel(ScanArgs a) {
+__global__ void __launch_bounds__(kScanMaxWaves * 64, CROSS ? scan_waves_per_simd(KMAX) : 1) scan_kernel(ScanArgs a) {
     constexpr int NL = (KMAX + 63) / 64;
     __shared__ float4 tab_s[kScanMaxWaves][KMAX];
     const int lane = threadIdx.x & 63;
