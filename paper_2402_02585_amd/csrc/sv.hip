@@ -9,8 +9,13 @@
 // psi', multiplies by the phase LUT entry e^{-i gamma_j C(z)} and stores
 // phi_j. One pass = one read and one write of psi plus one byte of cost per
 // amplitude. Block partial sums are reduced in a fixed order by a one-block
-// finalize kernel per instance, which also forms delta_j on the device, so no
-// value crosses to the host between rounds.
+// finalize kernel per instance, or by the next pass itself where the rows are few
+// (chained passes), which also forms delta_j on the device, so no value crosses to
+// the host between rounds.
+//
+// complex128 evolutions and gradients take the level form (level.hip) instead of
+// these passes; complex64 ones, whose float32 rounding in every round is part of
+// their results, and the tuning hooks take the passes.
 //
 // The reverse sweep of the adjoint gradient uses the same streaming shape:
 // pass k reads lambda_k, phi_k and C, forms mu_k = lambda_k + eps_k
@@ -1003,7 +1008,7 @@ static SvLayout sv_layout(int num_inst, int n, int p, int dtype, int ckpt_every,
     L.eps = o;      o += al256(I * 16);
     L.dbeta = o;    o += al256(I * P * 8);
     L.dgamma = o;   o += al256(I * P * 8);
-    L.angles = o;   o += al256(I * P * 16);   // beta[p] then gamma[p], uploaded by graph-plan runs
+    L.angles = o;   o += al256(I * P * 16);   // all betas, then all gammas
     L.target = o;   o += al256(I * 4);
     L.counter = o;  o += al256(I * 4);
     L.partials = o; o += al256(std::max<size_t>(kMaxPassBlocks, I) * kFwdR * 8);
