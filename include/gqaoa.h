@@ -129,6 +129,10 @@ int gqaoa_cost_batched(int num_inst, const int32_t *n_host, const int32_t *m_hos
  *   energy_host[j] = <psi|H_P|psi>, the cost function of Eq. (4),
  *   norm_host[j]   = <psi|psi>.
  * cost_dev must hold C(z) for all z (from gqaoa_cost_table) with values <= m.
+ * complex64 states are evolved round by round, every round rounding to float32.
+ * complex128 ones take the level form: the rounds run in float64 on the level
+ * weights (and, from a given state, on its level sums) and the final state is
+ * written once, so their cost hardly depends on p.
  * ws_dev/ws_bytes: device scratch of gqaoa_workspace_bytes(n, p, dt, 0) bytes.
  * Errors: EINVAL (NULL cost/psi/angles/ws, bad dtype), ERANGE (n, m, p,
  * target_level outside [0, m]), EWORKSPACE. */
@@ -152,18 +156,19 @@ int gqaoa_evolve_x(int n, int m, const uint8_t *cost_dev, int p, const double *b
                    int target_level, double *psol_host, double *energy_host,
                    double *norm_host, void *ws_dev, size_t ws_bytes, void *stream);
 
-/* Graph-captured form of gqaoa_evolve for callers that evolve one instance
- * many times with new angles (angle searches, where at small n each round is
- * a few microseconds and launch overhead dominates): create captures the
- * whole call (device-side angle tables, p >= 1 rounds, final readout) into
- * one HIP graph; each run uploads the 2p angles, replays it and returns the
- * readouts as gqaoa_evolve does (synchronizes the stream). Arguments of
+/* Planned form of gqaoa_evolve for callers that evolve one instance many times
+ * with new angles (angle searches, where at small n each round is a few
+ * microseconds and launch overhead dominates). complex64: create captures the
+ * whole call (device-side angle tables, p >= 1 rounds, final readout) into one
+ * HIP graph, and each run uploads the 2p angles and replays it; complex128: a
+ * run enqueues the few launches of the level form. A run returns the readouts
+ * as gqaoa_evolve does (synchronizes the stream). Arguments of
  * create as gqaoa_evolve (workspace: gqaoa_workspace_bytes(n, p, dtype, 0));
  * cost_dev, psi_dev and ws_dev must stay valid while the plan lives. With
  * init_uniform = 1 every run starts from |s>; with 0, from psi's contents,
  * which a run overwrites with its final state. Runs of one plan come from
- * one host thread at a time. The results equal gqaoa_evolve's up to the last
- * bit of the phase tables (device vs host float64 sin/cos).
+ * one host thread at a time. The results are gqaoa_evolve's: the same kernels
+ * on the same tables.
  * Errors: as gqaoa_evolve, ERANGE for p < 1, EINVAL for a NULL plan_out or
  * angles, non-finite angles, or another device current at a run. */
 typedef struct gqaoa_evolve_plan gqaoa_evolve_plan;
@@ -189,9 +194,11 @@ int gqaoa_solution_prob(int n, const uint8_t *cost_dev, const void *psi_dev, int
  * sweep: lambda_p = Pi_t psi_p; mu_k = lambda_k + (e^{+i beta_k} - 1)|s><s|lambda_k>;
  * dP/dbeta_k = 2 Re(-i e^{-i beta_k} <lambda_k|s><s|phi_k>);
  * dP/dgamma_k = 2 Im(sum_z conj(mu_z) C(z) phi_z); lambda_{k-1} = e^{+i gamma_k C} mu_k,
- * with phi_k the state after round k's phase. Forward states are
- * checkpointed every ckpt_every rounds and recomputed per segment
- * (ckpt_every = 0 keeps every round's state).
+ * with phi_k the state after round k's phase. With complex64 states the sweep
+ * runs over the statevector, forward states checkpointed every ckpt_every
+ * rounds and recomputed per segment (ckpt_every = 0 keeps every round's state).
+ * With complex128 it runs on the levels of each instance, counted from its cost
+ * table, and stores no states; ckpt_every then only sizes the workspace.
  * Batched form: num_inst instances with the same n, m_host[i] clauses,
  * costs at cost_dev + i*2^n, angles at beta_host + i*p. Outputs psol_host[i],
  * dbeta_host[i*p + k], dgamma_host[i*p + k].

@@ -3,9 +3,10 @@
 ``GQAOAProb.apply(betas, gammas, cost, n, m, ...)`` returns P_sol after
 len(betas) rounds of Eq. (3) from |s> (float64 scalar tensor); its backward
 returns dP/dbeta_k and dP/dgamma_k from the device adjoint sweep
-(``gqaoa_grad``: reverse sweep with checkpoints every ``ckpt_every`` rounds;
-None keeps every round's state when that fits in device memory and
-checkpoints only when it does not).
+(``gqaoa_grad``: complex128 on the levels of the cost table; complex64 a
+reverse sweep over the state with checkpoints every ``ckpt_every`` rounds, None
+keeping every round's state when that fits in device memory and checkpointing
+only when it does not).
 The forward call computes the gradient too (one adjoint sweep) and keeps it
 for the backward. ``GQAOAProbBatched`` does the same for a batch of
 instances with equal n (betas, gammas: [I, p]; returns P_sol[I]).

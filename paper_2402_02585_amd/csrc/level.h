@@ -15,17 +15,16 @@ struct LevelEvolve {
     int init_uniform;
     const uint8_t *cost;
     void *psi;              // [2^n] complex128: the initial state unless init_uniform, the final one
-    const double *beta_host, *gamma_host;  // eager calls: p host angles each
-    double *angles_dev;     // beta[p], gamma[p]: read by captured calls, scratch of long eager ones
+    const double *beta_host, *gamma_host;  // p host angles each
+    double *angles_dev;     // beta[p], gamma[p]: scratch of calls of more than kLevelInlineRounds
     void *rows;             // [kLevelMaxRows + 1][256][4] doubles: counts or level sums of the blocks
     void *table;            // [512] complex128: the final level table
     double *readout;        // [p+1][3]
 };
 
-// Enqueues the whole evolution. captured: the angles are read from
-// angles_dev when the launches run; otherwise from beta_host / gamma_host,
-// which must stay valid until the stream has been synchronized.
-int level_evolve(const LevelEvolve &e, bool captured, hipStream_t st);
+// Enqueues the whole evolution. beta_host and gamma_host must stay valid until
+// the stream has been synchronized.
+int level_evolve(const LevelEvolve &e, hipStream_t st);
 
 // Adjoint gradient of P_sol in the level space: the occupied levels of one
 // instance per block, counted from its cost table or given compacted.

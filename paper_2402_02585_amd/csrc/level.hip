@@ -590,12 +590,12 @@ static void launch_run(const LevelRunArgs &r, const LevelEvolve &e, bool inl, hi
     }
 }
 
-int level_evolve(const LevelEvolve &e, bool captured, hipStream_t st) {
+int level_evolve(const LevelEvolve &e, hipStream_t st) {
     DeviceInfo dev;
     int s = device_info(&dev);
     if (s) return s;
-    const bool inl = !captured && e.p <= kLevelInlineRounds;
-    if (!captured && !inl) {
+    const bool inl = e.p <= kLevelInlineRounds;
+    if (!inl) {
         GQ_HIP(hipMemcpyAsync(e.angles_dev, e.beta_host, 8 * (size_t)e.p, hipMemcpyHostToDevice, st));
         GQ_HIP(hipMemcpyAsync(e.angles_dev + e.p, e.gamma_host, 8 * (size_t)e.p, hipMemcpyHostToDevice, st));
     }

@@ -1353,7 +1353,7 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
         LevelEvolve le = level_args(n, m, cost, p, init_uniform, psi, target, ws);
         le.beta_host = beta;
         le.gamma_host = gamma;
-        if ((s = level_evolve(le, false, st))) return s;
+        if ((s = level_evolve(le, st))) return s;
         readout = le.readout;
     } else {
         int32_t m_of[1] = {m};
@@ -1593,6 +1593,8 @@ struct EvolvePlan {
     int device = -1, m = 0;
     int target_host[1] = {0};
     double *stage = nullptr;  // pinned: angles [2p], then readouts [(p+1) * 3]
+    bool level = false;       // the level form: its one to four launches, with the angles among their
+    LevelEvolve le{};         // arguments, are enqueued by each run (n = 10, p = 20: 43 us, as a graph 54)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t cap = nullptr;
@@ -1624,8 +1626,6 @@ struct EvolvePlanGuard {
 
 static int enqueue_evolve(EvolvePlan *E, int init_uniform, void *psi, hipStream_t st) {
     FwdPlan &P = E->P;
-    if (level_form(P.dtype, init_uniform, P.p))
-        return level_evolve(level_args(P.n, E->m, P.cost, P.p, init_uniform, psi, *E->target_host, P.ws), true, st);
     double *mixf = reinterpret_cast<double *>(P.ws + P.L.mixf);
     int s;
     const double *ang = reinterpret_cast<const double *>(P.ws + P.L.angles);
@@ -1670,6 +1670,15 @@ int evolve_plan_create(int n, int m, const uint8_t *cost, int p, int dtype, int 
     P.chain = chain_rule(P);
     GQ_HIP(hipHostMalloc(reinterpret_cast<void **>(&E->stage), sizeof(double) * (2 * (size_t)p + 3 * ((size_t)p + 1)),
                          hipHostMallocDefault));
+    if (level_form(dtype, init_uniform, p)) {
+        E->level = true;
+        E->le = level_args(n, m, cost, p, init_uniform, psi, target, ws);
+        E->le.beta_host = E->stage;
+        E->le.gamma_host = E->stage + p;
+        *out = E;
+        G.e = nullptr;
+        return GQAOA_OK;
+    }
     {
         std::vector<hipStream_t> c;
         s = stream_pool_take(1, &c);
@@ -1704,8 +1713,12 @@ int evolve_plan_run(EvolvePlan *E, const double *beta, const double *gamma, doub
     std::copy(beta, beta + p, ang);
     std::copy(gamma, gamma + p, ang + p);
     const FwdPlan &P = E->P;
-    GQ_HIP(hipMemcpyAsync(P.ws + P.L.angles, ang, 16 * (size_t)p, hipMemcpyHostToDevice, st));
-    GQ_HIP(hipGraphLaunch(E->exec, st));
+    if (E->level) {
+        if (const int s = level_evolve(E->le, st)) return s;
+    } else {
+        GQ_HIP(hipMemcpyAsync(P.ws + P.L.angles, ang, 16 * (size_t)p, hipMemcpyHostToDevice, st));
+        GQ_HIP(hipGraphLaunch(E->exec, st));
+    }
     GQ_HIP(hipMemcpyAsync(ro, P.ws + P.L.readout, 24 * ((size_t)p + 1), hipMemcpyDeviceToHost, st));
     GQ_HIP(hipStreamSynchronize(st));
     for (int j = 0; j <= p; ++j) {

@@ -286,10 +286,11 @@ def gqaoa_evolve(n: int, m: int, cost, betas, gammas, dtype=C64, psi=None, init_
 
 
 class EvolvePlan:
-    """Graph-captured gqaoa_evolve (gqaoa_evolve_plan_*) for one instance and a
-    fixed p: each run(betas, gammas) uploads the angles, replays the graph and
-    returns (psol, energy, norm) numpy arrays [p+1]; the final state is left
-    in ``psi``. The plan holds the cost table, state and workspace tensors."""
+    """Planned gqaoa_evolve (gqaoa_evolve_plan_*) for one instance and a fixed p:
+    each run(betas, gammas) replays a captured graph (complex64) or enqueues the
+    level form's launches (complex128) and returns (psol, energy, norm) numpy
+    arrays [p+1]; the final state is left in ``psi``. The plan holds the cost
+    table, state and workspace tensors."""
 
     def __init__(self, n: int, m: int, cost, p: int, dtype=C64, init_uniform: bool = True, target_level: int = 0,
                  psi=None, stream=None):
