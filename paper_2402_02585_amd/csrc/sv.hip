@@ -1721,6 +1721,7 @@ int evolve_plan_run(EvolvePlan *E, const double *beta, const double *gamma, doub
     }
     GQ_HIP(hipMemcpyAsync(ro, P.ws + P.L.readout, 24 * ((size_t)p + 1), hipMemcpyDeviceToHost, st));
     GQ_HIP(hipStreamSynchronize(st));
+    if (E->level && prof_on()) prof_collect();  // its launches are not under capture
     for (int j = 0; j <= p; ++j) {
         if (psol) psol[j] = ro[3 * j];
         if (energy) energy[j] = ro[3 * j + 1];
