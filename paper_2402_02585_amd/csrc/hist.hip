@@ -17,6 +17,7 @@
 // instantiation) and, inside a bucket, ordered by level count descending so
 // the dynamic queue ends with the short items.
 #include "batch.h"
+#include "stream_pool.h"
 
 #include <algorithm>
 #include <chrono>
@@ -659,6 +660,37 @@ int scan_choose_tile(int bucket, const DeviceInfo &dev, const ScanArgs &a, unsig
     return tune_bucket(bucket, dev, a, counter, st, out);
 }
 
+// Streams of a call's own beside the caller's: forked from it behind what it has
+// enqueued so far, joined to it at the end. They come from the device's pool and go
+// back when their work has ended, also when the call fails.
+struct SideStreams {
+    int device;
+    std::vector<hipStream_t> streams;
+    hipEvent_t ev = nullptr;
+    SideStreams(int d) : device(d) {}
+    SideStreams(const SideStreams &) = delete;
+    SideStreams &operator=(const SideStreams &) = delete;
+    int fork(size_t n, hipStream_t st) {
+        if (const int s = stream_pool_take(n, &streams)) return s;
+        GQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        GQ_HIP(hipEventRecord(ev, st));
+        for (hipStream_t x : streams) GQ_HIP(hipStreamWaitEvent(x, ev, 0));
+        return GQAOA_OK;
+    }
+    int join(hipStream_t st) {
+        for (hipStream_t x : streams) {
+            GQ_HIP(hipEventRecord(ev, x));
+            GQ_HIP(hipStreamWaitEvent(st, ev, 0));
+        }
+        return GQAOA_OK;
+    }
+    ~SideStreams() {
+        for (hipStream_t x : streams) (void)hipStreamSynchronize(x);
+        if (!streams.empty()) stream_pool_give(device, streams);
+        if (ev) (void)hipEventDestroy(ev);
+    }
+};
+
 int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const uint64_t *hists,
              int hist_stride, const int32_t *target_host, int nb, const double *betas, int ng,
              const double *gammas, int per_inst, int num_p, const int32_t *p_list, float *psol, float *energy,
@@ -694,18 +726,33 @@ int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const u
     a.num_p = num_p;
     a.per_inst = per_inst;
     for (int q = 0; q < num_p; ++q) a.p_list[q] = p_list[q];
-    for (int bk = 0; bk < kNumBuckets; ++bk) {
-        const int nslots = H.bucket_first[bk + 1] - H.bucket_first[bk];
-        if (!nslots) continue;
+    // The crossing form's buckets run side by side on up to four streams, the most
+    // levels first: its items end anywhere between one round and their cap, so a
+    // bucket ends with few waves, and one of a few instances never fills the device
+    // (128 instances in six buckets, 360 x 181 pairs: 8,050 -> 7,400 us; 23 in four,
+    // 230 x 92 pairs: 1,590 -> 815). The scan's items are equal and its buckets end
+    // full: one after another.
+    std::vector<int> used;
+    for (int bk = kNumBuckets - 1; bk >= 0; --bk)
+        if (H.bucket_first[bk + 1] > H.bucket_first[bk]) used.push_back(bk);
+    if (!first_p) std::reverse(used.begin(), used.end());
+    SideStreams side(dev.device);
+    if (first_p && used.size() > 1)
+        if ((s = side.fork(std::min<size_t>(used.size(), 4) - 1, st))) return s;
+    for (size_t u = 0; u < used.size(); ++u) {
+        const int bk = used[u];
+        const size_t branch = u % (side.streams.size() + 1);
+        const hipStream_t bs = branch ? side.streams[branch - 1] : st;
         ScanArgs ab = a;
         ab.slots = D.slots + H.bucket_first[bk];
-        ab.total_items = (unsigned)nslots * (unsigned)ng * (unsigned)ab.ntiles;
+        ab.total_items = (unsigned)(H.bucket_first[bk + 1] - H.bucket_first[bk]) * (unsigned)ng * (unsigned)ab.ntiles;
         TileChoice tc;
-        if ((s = scan_choose_tile(bk, dev, ab, D.counters + bk, tile, st, &tc))) return s;
-        ProfScope ps("scan", st);
-        if ((s = scan_launch_bucket(bk, tc, dev, ab, D.counters + bk, st))) return s;
+        if ((s = scan_choose_tile(bk, dev, ab, D.counters + bk, tile, bs, &tc))) return s;
+        ProfScope ps("scan", bs);
+        if ((s = scan_launch_bucket(bk, tc, dev, ab, D.counters + bk, bs))) return s;
         ps.end();
     }
+    if ((s = side.join(st))) return s;
     GQ_HIP(hipStreamSynchronize(st));  // host staging vectors end here
     if (prof_on()) prof_collect();
     return GQAOA_OK;

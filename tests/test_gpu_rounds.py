@@ -226,3 +226,34 @@ def test_crossing_caps_only_cut(S, unit):
         want = np.where(full <= cap[:, None, None], full, 0)
         assert np.array_equal(got, want), (S, f)
     log(f"crossing caps S={S} unit={unit}: {(full > 0).mean():.4f} of the cells cross")
+
+
+def test_crossing_buckets_side_by_side():
+    """A batch with many level counts runs its kernels on several streams; an
+    instance alone runs on the caller's. The first crossings are the same whole
+    numbers, on the default stream and on another, twice in a row (the second call
+    takes the streams back from the pool)."""
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(77))
+    ns, ms, rows = [], [], []
+    for K in (2, 5, 9, 14, 18, 22, 27, 31, 35, 41):
+        n = 12
+        h = np.zeros(64, dtype=np.uint64)
+        cut = np.sort(rng.choice(np.arange(1, 1 << n), K - 1, replace=False))
+        h[np.sort(rng.choice(64, K, replace=False))] = np.diff(np.concatenate([[0], cut, [1 << n]])).astype(np.uint64)
+        ns.append(n)
+        ms.append(63)
+        rows.append(h)
+    H = np.stack(rows)
+    tg = (H > 0).argmax(axis=1).astype(np.int32)
+    gb, gg = optim.fundamental_grid(36, 18)
+    caps = rng.integers(20, 200, len(ns)).astype(np.int32)
+    log("crossing buckets side by side")
+    alone = np.concatenate([g.gqaoa_scan_crossing(ns[i:i + 1], ms[i:i + 1], H[i:i + 1], gb, gg, caps[i:i + 1], 0.5,
+                                                  targets=tg[i:i + 1]).cpu().numpy() for i in range(len(ns))])
+    assert (alone > 0).any() and (alone == 0).any()
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            for _ in range(2):
+                got = g.gqaoa_scan_crossing(ns, ms, H, gb, gg, caps, 0.5, targets=tg)
+                assert (got.cpu().numpy() == alone).all()
