@@ -333,13 +333,13 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
     const int inst = blockIdx.y;
     const uint64_t ioff = (uint64_t)inst * a.N;
     const double *rows = nullptr;
-    int nblocks = gridDim.x;
+    int nblocks = gridDim.x;  // blocks with a tile
     if constexpr (CHAIN) {
         rows = a.fin.partials + (size_t)inst * a.fin.nblocks * kFwdR;
-        nblocks = a.fin.nblocks;
+        --nblocks;
         if ((int)blockIdx.x == nblocks) {
             double r[kFwdR];
-            sum_rows<kFwdR, kFwdR>(rows, nblocks, r, red_s);
+            sum_rows<kFwdR, kFwdR>(rows, a.fin.nblocks, r, red_s);
             if (threadIdx.x == 0) finalize_apply(a.fin, inst, r);
             return;
         }
@@ -683,10 +683,10 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
     int nblocks = gridDim.x;
     if constexpr (CHAIN) {
         rows = a.fin.partials + (size_t)inst * a.fin.nblocks * kRevR;
-        nblocks = a.fin.nblocks;
+        --nblocks;
         if ((int)blockIdx.x == nblocks) {
             double r[kRevR];
-            sum_rows<kRevR, kRevR>(rows, nblocks, r, red_s);
+            sum_rows<kRevR, kRevR>(rows, a.fin.nblocks, r, red_s);
             if (threadIdx.x == 0) rev_finalize_apply(a.fin, inst, r);
             return;
         }
@@ -728,7 +728,7 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
         const double *mb = a.fin.mixb_km1 + (size_t)inst * a.fin.grad_stride * 2;
         const double mr = mb[0], mi = mb[1];
         double L[2], er, ei;
-        sum_rows<2, kRevR>(rows, nblocks, L, red_s);
+        sum_rows<2, kRevR>(rows, a.fin.nblocks, L, red_s);
         rev_eps(mr, mi, a.fin.inv_N, L[0], L[1], er, ei);
         eps = {T(er), T(ei)};
     } else {
@@ -1177,7 +1177,10 @@ static bool fused_round(const FwdPlan &P) {
 // us, n = 18 7.7 -> 6.0, n = 20 10.5 -> 7.5). Every block pays for the rows, so
 // with more of them it turns: at n = 21 (1024 rows) 13.0 -> 13.2 us, and a batch
 // of 64 gradients of n = 20 (512 rows, 32,768 blocks) loses 6%; at 2,048 blocks in
-// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing. The
+// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing. At n = 22
+// the fold leaves two rows for the chain (21.5 -> 19.9 us per round, a gradient of
+// 16 rounds 813 -> 744); from n = 24 on the sums at the head of every block cost the
+// stream more than the launch (54.2 -> 57.5, n = 28 708 -> 785). The
 // reverse passes of a gradient chain in the same way (1 of n = 18, p = 32: 613 ->
 // 535 us with both sweeps chained, 691 with neither).
 constexpr int kChainBlocks = 2048;
@@ -1185,7 +1188,7 @@ constexpr int kChainBlocks = 2048;
 static bool chain_rule(const FwdPlan &P) {
     const PassShape &s = P.shape;
     return P.dtype == GQAOA_C64 && P.p > 0 && s.amp == 2 && s.unroll == 4 && s.nt == 1 &&
-           s.blocks_x <= kChainRows && (uint64_t)s.blocks_x * kSvThreads * 8 >= P.N &&
+           (s.blocks_x <= kChainRows || s.blocks_x > kFinThreads) && (uint64_t)s.blocks_x * kSvThreads * 8 >= P.N &&
            (int64_t)P.num_inst * s.blocks_x <= kChainBlocks && !fused_round(P);
 }
 
@@ -1198,7 +1201,6 @@ static void chain_pass(FwdPlan &P, int j, FwdArgs &a, FinArgs &f) {
         a.chain = 1;
         a.fin = P.pending;
     }
-    P.pending = f;
 }
 
 // From 2^28 amplitudes on, every second pass takes its tiles in descending order,
@@ -1239,7 +1241,12 @@ static int forward_round(FwdPlan &P, int j, const void *psi_in, void *psi_out, b
     launch_fwd(P.dtype, true, true, P.shape, P.num_inst, a, st);
     ps.end();
     GQ_LAUNCH_CHECK();
-    if (finalize && !fused && !P.chain) return launch_finalize(P, f, st);
+    if (finalize && P.chain) {
+        if (const int s = fold_for_finalize<kFwdR>(P, f.partials, &f.partials, &f.nblocks, st)) return s;
+        P.pending = f;
+    } else if (finalize && !fused) {
+        return launch_finalize(P, f, st);
+    }
     return GQAOA_OK;
 }
 
@@ -1554,11 +1561,11 @@ int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int 
                 rf.eps_out = reinterpret_cast<double *>(P.ws + P.L.eps);
                 rf.dbeta_km1 = reinterpret_cast<double *>(P.ws + P.L.dbeta) + (k - 2);
             }
+            if ((s = fold_for_finalize<kRevR>(P, rf.partials, &rf.partials, &rf.nblocks, st))) return s;
             if (P.chain && k > 1) {
                 rev_pending = rf;
                 continue;
             }
-            if ((s = fold_for_finalize<kRevR>(P, rf.partials, &rf.partials, &rf.nblocks, st))) return s;
             if (rf.nblocks <= kFinWave)
                 hipLaunchKernelGGL(sv_rev_finalize_kernel<kFinWave>, dim3(P.num_inst), dim3(kFinWave), 0, st, rf);
             else

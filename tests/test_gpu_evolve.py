@@ -207,15 +207,15 @@ def test_sampled_profiling_counts():
     assert cnt == 1 and ms > 0
 
 
-@pytest.mark.parametrize("n,count", [(9, 2049), (10, 2049), (15, 129), (19, 9), (20, 5), (21, 3)])
+@pytest.mark.parametrize("n,count", [(9, 2049), (10, 2049), (15, 129), (19, 9), (20, 5), (21, 3), (22, 2)])
 def test_chained_rounds_are_the_separate_ones(n, count):
     """Round passes of small complex64 states finalize the pass before them (up
     to 512 partial rows and 2,048 blocks); a batch over that bound launches its
     finalizes by themselves. Both add the same rows in the same order: the same
     bits, in evolutions of one to four rounds, plans and gradients with and without
     recomputed segments, and within the complex64 tolerance of the oracle. (n = 21:
-    neither is chained; n = 9, 10: one block with less than a tile, which only
-    gradients stream.)"""
+    neither is chained; n = 22: chained behind a fold; n = 9, 10: one block with
+    less than a tile, which only gradients stream.)"""
     torch = need_gpu()
     m = 60
     lits = rand_lits(n, m, 500 + n)
