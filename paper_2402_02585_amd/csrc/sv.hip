@@ -271,32 +271,37 @@ __device__ __forceinline__ void block_sum_row(double (&v)[R], double *lds, doubl
 constexpr int kChainRows = 512;
 
 template <int R, int STRIDE>
-__device__ __forceinline__ void sum_rows(const double *p, int nrows, double (&r)[R], double *lds) {
-    constexpr int kWaves = kSvThreads / kWave, kPer = kChainRows / kSvThreads;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+struct RowSums {
+    static constexpr int kWaves = kSvThreads / kWave, kPer = kChainRows / kSvThreads;
     double v[kPer][R];
+    __device__ __forceinline__ void load(const double *p, int nrows) {
+        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int b = (i * kWaves + wave) * kWave + lane;
+        for (int i = 0; i < kPer; ++i) {
+            const int b = (i * kWaves + wave) * kWave + lane;
 #pragma unroll
-        for (int k = 0; k < R; ++k) v[i][k] = b < nrows ? p[(size_t)b * STRIDE + k] : 0.0;
+            for (int k = 0; k < R; ++k) v[i][k] = b < nrows ? p[(size_t)b * STRIDE + k] : 0.0;
+        }
     }
-    const int nw = (nrows + kWave - 1) / kWave;
+    __device__ __forceinline__ void sum(int nrows, double (&r)[R], double *lds) {
+        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+        const int nw = (nrows + kWave - 1) / kWave;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
-        if (i * kWaves + wave < nw)
+        for (int i = 0; i < kPer; ++i)
+            if (i * kWaves + wave < nw)
 #pragma unroll
-            for (int k = 0; k < R; ++k) {
-                v[i][k] = wave_sum_dpp(v[i][k]);
-                if (lane == 0) lds[(i * kWaves + wave) * R + k] = v[i][k];
-            }
-    __syncthreads();
+                for (int k = 0; k < R; ++k) {
+                    v[i][k] = wave_sum_dpp(v[i][k]);
+                    if (lane == 0) lds[(i * kWaves + wave) * R + k] = v[i][k];
+                }
+        __syncthreads();
 #pragma unroll
-    for (int k = 0; k < R; ++k) r[k] = 0.0;
-    for (int w = 0; w < nw; ++w)
+        for (int k = 0; k < R; ++k) r[k] = 0.0;
+        for (int w = 0; w < nw; ++w)
 #pragma unroll
-        for (int k = 0; k < R; ++k) r[k] += lds[w * R + k];
-}
+            for (int k = 0; k < R; ++k) r[k] += lds[w * R + k];
+    }
+};
 
 // ---- forward pass ---------------------------------------------------------------
 struct FwdArgs {
@@ -339,7 +344,9 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
         --nblocks;
         if ((int)blockIdx.x == nblocks) {
             double r[kFwdR];
-            sum_rows<kFwdR, kFwdR>(rows, a.fin.nblocks, r, red_s);
+            RowSums<kFwdR, kFwdR> all;
+            all.load(rows, a.fin.nblocks);
+            all.sum(a.fin.nblocks, r, red_s);
             if (threadIdx.x == 0) finalize_apply(a.fin, inst, r);
             return;
         }
@@ -373,16 +380,26 @@ __global__ void __launch_bounds__(kSvThreads) sv_forward_kernel(FwdArgs a) {
             }
         }
     };
-    if constexpr (CHAIN) load_tile(wave * kTile);  // in flight during the sums below
+    // loads come back in order: the rows and the phase table first, the tile in
+    // flight during the sums
+    RowSums<2, kFwdR> prev;
+    if constexpr (CHAIN) prev.load(rows, a.fin.nblocks);
+    Cx<T> lut_first{T(0), T(0)};
     if constexpr (PHASE) {
         const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
-        for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
+        if constexpr (CHAIN) {
+            if ((int)threadIdx.x < a.lut_len) lut_first = lut[threadIdx.x];
+        } else {
+            for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
+        }
     }
     if constexpr (CHAIN) {
         const double *mf = a.fin.mixf + (size_t)inst * a.fin.mixf_stride;
         const double mr = mf[0], mi = mf[1];
+        load_tile(wave * kTile);
         double S[2], dr, di;
-        sum_rows<2, kFwdR>(rows, a.fin.nblocks, S, red_s);
+        if constexpr (PHASE) lut_s[threadIdx.x] = lut_first;
+        prev.sum(a.fin.nblocks, S, red_s);
         mixer_delta(mr, mi, a.fin.inv_N, S[0], S[1], dr, di);
         dl = {T(dr), T(di)};
     } else {
@@ -686,7 +703,9 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
         --nblocks;
         if ((int)blockIdx.x == nblocks) {
             double r[kRevR];
-            sum_rows<kRevR, kRevR>(rows, a.fin.nblocks, r, red_s);
+            RowSums<kRevR, kRevR> all;
+            all.load(rows, a.fin.nblocks);
+            all.sum(a.fin.nblocks, r, red_s);
             if (threadIdx.x == 0) rev_finalize_apply(a.fin, inst, r);
             return;
         }
@@ -720,18 +739,22 @@ __global__ void __launch_bounds__(kSvThreads) sv_reverse_kernel(RevArgs a) {
             }
         }
     };
-    if constexpr (CHAIN) load_tile(wave * kTile);  // in flight during the sums below
     const Cx<T> *lut = reinterpret_cast<const Cx<T> *>(a.lut) + (size_t)inst * a.lut_stride;
-    for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
     Cx<T> eps;
-    if constexpr (CHAIN) {
+    if constexpr (CHAIN) {  // in the order of the forward pass
+        RowSums<2, kRevR> prev;
+        prev.load(rows, a.fin.nblocks);
+        const Cx<T> lut_first = (int)threadIdx.x < a.lut_len ? lut[threadIdx.x] : Cx<T>{T(0), T(0)};
         const double *mb = a.fin.mixb_km1 + (size_t)inst * a.fin.grad_stride * 2;
         const double mr = mb[0], mi = mb[1];
+        load_tile(wave * kTile);
         double L[2], er, ei;
-        sum_rows<2, kRevR>(rows, a.fin.nblocks, L, red_s);
+        lut_s[threadIdx.x] = lut_first;
+        prev.sum(a.fin.nblocks, L, red_s);
         rev_eps(mr, mi, a.fin.inv_N, L[0], L[1], er, ei);
         eps = {T(er), T(ei)};
     } else {
+        for (int i = threadIdx.x; i < a.lut_len; i += kSvThreads) lut_s[i] = lut[i];
         __syncthreads();
         const double *e = a.eps + (size_t)inst * a.eps_stride;
         eps = {T(e[0]), T(e[1])};
@@ -1173,17 +1196,16 @@ static bool fused_round(const FwdPlan &P) {
 
 // A round of a small streamed state is launches and latency: a pass of 4.3 us and
 // a finalize of 2 to 3 us at n = 16 .. 18, with a gap of 1.1 us after each. Chained
-// passes drop the second launch (per round, complex64, replayed: n = 16 7.2 -> 5.7
-// us, n = 18 7.7 -> 6.0, n = 20 10.5 -> 7.5). Every block pays for the rows, so
-// with more of them it turns: at n = 21 (1024 rows) 13.0 -> 13.2 us, and a batch
-// of 64 gradients of n = 20 (512 rows, 32,768 blocks) loses 6%; at 2,048 blocks in
-// all a batch still gains (16 of n = 18: 594 -> 574 us), at 8,192 nothing. At n = 22
-// the fold leaves two rows for the chain (21.5 -> 19.9 us per round, a gradient of
-// 16 rounds 813 -> 744); from n = 24 on the sums at the head of every block cost the
-// stream more than the launch (54.2 -> 57.5, n = 28 708 -> 785). The
-// reverse passes of a gradient chain in the same way (1 of n = 18, p = 32: 613 ->
-// 535 us with both sweeps chained, 691 with neither).
-constexpr int kChainBlocks = 2048;
+// passes drop the second launch (per round, complex64, replayed: n = 16 7.2 -> 5.4
+// us, n = 18 7.7 -> 5.7, n = 20 10.5 -> 7.3, and behind a fold, which leaves rows /
+// 1024 for the chain, n = 22 21.5 -> 20.2, n = 24 54.2 -> 52.9). Every block pays
+// for the rows: 1024 of them (n = 21) take as long as the finalize (12.7 and 13.2
+// us), and where many blocks stream the sums cost more than a launch: with 8,192
+// blocks in all a batch still gains 2% (64 gradients of n = 18, 16 of n = 20), at n
+// = 25 a round loses 1%, at n = 28 2%, and 64 gradients of n = 20 (32,768 blocks of
+// 512 rows) 4%. The reverse passes of a gradient chain in the same way (1 of n = 18,
+// p = 32: 700 -> 451 us, the device's tables included).
+constexpr int kChainBlocks = 8192;
 
 static bool chain_rule(const FwdPlan &P) {
     const PassShape &s = P.shape;

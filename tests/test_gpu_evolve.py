@@ -207,10 +207,10 @@ def test_sampled_profiling_counts():
     assert cnt == 1 and ms > 0
 
 
-@pytest.mark.parametrize("n,count", [(9, 2049), (10, 2049), (15, 129), (19, 9), (20, 5), (21, 3), (22, 2)])
+@pytest.mark.parametrize("n,count", [(9, 8193), (10, 8193), (15, 513), (19, 33), (20, 17), (21, 3), (22, 5)])
 def test_chained_rounds_are_the_separate_ones(n, count):
     """Round passes of small complex64 states finalize the pass before them (up
-    to 512 partial rows and 2,048 blocks); a batch over that bound launches its
+    to 512 partial rows, or rows that a fold leaves, and 8,192 blocks); a batch over that bound launches its
     finalizes by themselves. Both add the same rows in the same order: the same
     bits, in evolutions of one to four rounds, plans and gradients with and without
     recomputed segments, and within the complex64 tolerance of the oracle. (n = 21:
