@@ -671,6 +671,13 @@ struct SideStreams {
     SideStreams(const SideStreams &) = delete;
     SideStreams &operator=(const SideStreams &) = delete;
     int fork(size_t n, hipStream_t st) {
+        // a pooled stream never joins a caller's capture (the call fails at its
+        // synchronization and would give it back inside one): none then
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return GQAOA_OK;
+        }
         if (const int s = stream_pool_take(n, &streams)) return s;
         GQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
         GQ_HIP(hipEventRecord(ev, st));
