@@ -20,7 +20,9 @@
 //
 // The costs are counted from the table itself, so any table is taken as it
 // is; entries above m (which the caller promises not to pass) get the phase
-// factor 0 that the round passes' tables hold there.
+// factor 0 that the round passes' tables hold there, from |s> and from a given
+// state. Their amplitudes are all the same after the first round, so the sums of
+// a given state keep one slot m + 1 for all of them (none at m = 255).
 //
 // complex128 only: its results agree with the round passes' to their rounding.
 // A complex64 evolution rounds its state to float32 in every round, and that
@@ -134,15 +136,19 @@ struct LevelLds {
     double ang[2 * kLevelInlineRounds];
 };
 
-// A given state's level means (times 2^{n/2}) and squared deviations, by compacted level.
+// A given state's level means (times 2^{n/2}) and squared deviations, by compacted
+// level; the slot above m holds the sum of |psi_0|^2 as its deviation, for round 0
+// alone, and the mean of its levels.
 struct GivenLds {
     double2 b0[kLevels];
     double var[kLevels];
+    double lev[kLevels];
+    double e_above, c_above;  // sums of C(z) |psi_0(z)|^2 and C(z) over the slot above m
 };
 
 struct LevelRunArgs {
     const uint8_t *cost;
-    const double *sums;    // given state: [levels][4] sums of re, im, |.|^2 and counts
+    const double *sums;    // given state: [slots][4] sums of re, im, |.|^2 and counts (level_sums_kernel)
     const uint32_t *rows;
     int nrows, n, m, p, target;
     const double *angles;  // device: beta[p], gamma[p]; null: the inline angles
@@ -150,6 +156,9 @@ struct LevelRunArgs {
     double2 *table;
     double *readout;
 };
+
+// Slots of a given state's sums: levels 0..m and one for what is above.
+__host__ __device__ constexpr int given_slots(int m) { return m < kLevels - 1 ? m + 2 : kLevels; }
 
 template <int ROUNDS>
 struct LevelAngles {
@@ -223,6 +232,7 @@ __device__ __forceinline__ void level_rounds(const LevelRunArgs &a, LevelLds &L,
         br[i] = on[i] ? 1.0 : 0.0;
         bi[i] = 0.0;
         if constexpr (GIVEN) {
+            lv[i] = on[i] ? G->lev[k] : 0.0;
             br[i] = on[i] ? G->b0[k].x : 0.0;
             bi[i] = on[i] ? G->b0[k].y : 0.0;
         }
@@ -254,7 +264,11 @@ __device__ __forceinline__ void level_rounds(const LevelRunArgs &a, LevelLds &L,
         for (int i = 0; i < LPL; ++i) {
             double pb = on[i] ? w[i] * (x[i].x * x[i].x + x[i].y * x[i].y) : 0.0;
             if constexpr (GIVEN)
-                if (on[i]) pb += G->var[lane + kWave * i];
+                if (on[i]) {
+                    const bool above = lv[i] > (double)a.m;
+                    if (!above || j == 0) pb += G->var[lane + kWave * i];
+                    if (above && j == 0) E += G->e_above - lv[i] * pb;
+                }
             N += pb;
             E += lv[i] * pb;
             if (lane + kWave * i == L.t_idx) ro[0] = pb;
@@ -383,7 +397,7 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
     double2 sum{0.0, 0.0};
     double sq = 0.0;
     if constexpr (GIVEN) {
-        if (t <= a.m) {
+        if (t < given_slots(a.m)) {
             sum = double2{a.sums[4 * t], a.sums[4 * t + 1]};
             sq = a.sums[4 * t + 2];
             count = (uint64_t)a.sums[4 * t + 3];
@@ -397,10 +411,36 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
     }
     const int pos = compact_levels(L, count, a.n, a.target);  // its barriers also end the counters' use of smem
     if constexpr (GIVEN) {
+        if (given_slots(a.m) > a.m + 1 && a.sums[4 * (a.m + 1) + 3] != 0.0) {
+            // the table breaks its promise: this block reads it for the sums of the
+            // levels above m, which the sums kernel has no time for (+8%)
+            __shared__ double red[2 * kRunWaves];
+            double v[2] = {0.0, 0.0};
+            for (uint64_t z = t; z < 1ull << a.n; z += kRunThreads) {
+                const int c = a.cost[z];
+                if (c <= a.m) continue;
+                const double2 x = a.psi[z];
+                v[0] += (double)c * (x.x * x.x + x.y * x.y);
+                v[1] += (double)c;
+            }
+            block_sum<2, kRunThreads>(v, red);
+            if (t == 0) {
+                given[0].e_above = v[0];
+                given[0].c_above = v[1];
+            }
+            __syncthreads();
+        }
         if (pos >= 0) {
             const double inv = 1.0 / (double)count, root = sqrt(ldexp(1.0, a.n));
-            given[0].b0[pos] = double2{root * (sum.x * inv), root * (sum.y * inv)};
-            given[0].var[pos] = fmax(sq - (sum.x * sum.x + sum.y * sum.y) * inv, 0.0);
+            if (t <= a.m) {
+                given[0].b0[pos] = double2{root * (sum.x * inv), root * (sum.y * inv)};
+                given[0].var[pos] = fmax(sq - (sum.x * sum.x + sum.y * sum.y) * inv, 0.0);
+                given[0].lev[pos] = (double)t;
+            } else {
+                given[0].b0[pos] = double2{0.0, 0.0};
+                given[0].var[pos] = sq;
+                given[0].lev[pos] = given[0].c_above * inv;
+            }
         }
         __syncthreads();
     }
@@ -424,32 +464,33 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
 // lanes of an instruction share an address and a wave's adds to one address
 // keep their order. The sums then do not depend on timing, and concentrated
 // levels cost no conflicts. C is the largest of 16, 8 and 4 that fits the LDS
-// of four waves (up to 98, 189 and 255 levels). Bound by the read of the state
+// of four waves (up to 99, 190 and 256 slots). Bound by the read of the state
 // and by the LDS adds; each wave keeps its next 8 vectors' loads in flight (n =
 // 22, m = 92: 22 us, 3.3 TB/s from the 64 MiB state).
 constexpr int kSumThreads = 256, kSumWaves = kSumThreads / kWave, kSumU = 8;
-static size_t level_sums_lds(int nl, int C) {
-    return sizeof(double) * kSumWaves * 3 * (size_t)nl * C + sizeof(uint32_t) * (size_t)nl * 16;
+static size_t level_sums_lds(int ns, int C) {
+    return sizeof(double) * kSumWaves * 3 * (size_t)ns * C + sizeof(uint32_t) * (size_t)ns * 16;
 }
-static int level_sums_cols(int nl) {
+static int level_sums_cols(int ns) {
     for (int C : {16, 8})
-        if (level_sums_lds(nl, C) <= 155 * 1024) return C;
+        if (level_sums_lds(ns, C) <= 155 * 1024) return C;
     return 4;
 }
 
 template <int C>
 __global__ void __launch_bounds__(kSumThreads) level_sums_kernel(const uint8_t *__restrict__ cost,
-                                                                 const double2 *__restrict__ psi, uint64_t N, int nl,
+                                                                 const double2 *__restrict__ psi, uint64_t N, int m,
                                                                  double *__restrict__ rows) {
+    const int ns = given_slots(m);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_sums[];
     double *all = reinterpret_cast<double *>(smem_sums);
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(all + (size_t)kSumWaves * 3 * nl * C);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(all + (size_t)kSumWaves * 3 * ns * C);
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    for (int i = t; i < kSumWaves * 3 * nl * C; i += kSumThreads) all[i] = 0.0;
-    for (int i = t; i < nl * 16; i += kSumThreads) cnt[i] = 0u;
+    for (int i = t; i < kSumWaves * 3 * ns * C; i += kSumThreads) all[i] = 0.0;
+    for (int i = t; i < ns * 16; i += kSumThreads) cnt[i] = 0u;
     __syncthreads();
-    double *mine = all + (size_t)wave * 3 * nl * C + lane % C;
-    const int plane = nl * C;
+    double *mine = all + (size_t)wave * 3 * ns * C + lane % C;
+    const int plane = ns * C;
     const uint64_t step = (uint64_t)gridDim.x * kSumWaves * kWave * kSumU;
     uint64_t base = ((uint64_t)blockIdx.x * kSumWaves + wave) * kWave * kSumU;
     double2 nx[kSumU];
@@ -472,14 +513,14 @@ __global__ void __launch_bounds__(kSumThreads) level_sums_kernel(const uint8_t *
 #pragma unroll
         for (int u = 0; u < kSumU; ++u) {
             x[u] = nx[u];
-            c[u] = min((int)nc[u], nl - 1);
+            c[u] = min((int)nc[u], ns - 1);
         }
         if (base + step < N) load(base + step);
 #pragma unroll
         for (int u = 0; u < kSumU; ++u) {
             const bool ok = base + (uint64_t)u * kWave + lane < N;
-            if (ok) atomicAdd(cnt + c[u] * 16 + (lane & 15), 1u);
             const double q = x[u].x * x[u].x + x[u].y * x[u].y;
+            if (ok) atomicAdd(cnt + c[u] * 16 + (lane & 15), 1u);
             double *p = mine + c[u] * C;
 #pragma unroll
             for (int g = 0; g < kWave / C; ++g) {
@@ -494,7 +535,7 @@ __global__ void __launch_bounds__(kSumThreads) level_sums_kernel(const uint8_t *
     }
     __syncthreads();
     double *row = rows + (size_t)blockIdx.x * kLevels * 4;
-    for (int i = t; i < 4 * nl; i += kSumThreads) {
+    for (int i = t; i < 4 * ns; i += kSumThreads) {
         const int l = i >> 2, v = i & 3;
         double s = 0.0;
         if (v < 3) {
@@ -509,7 +550,7 @@ __global__ void __launch_bounds__(kSumThreads) level_sums_kernel(const uint8_t *
     }
 }
 
-// Block l: the sums of level l over at most 256 rows, in a fixed order.
+// Block l: the sums of slot l over at most 256 rows, in a fixed order.
 __global__ void __launch_bounds__(kSumThreads) level_sums_fold_kernel(const double *__restrict__ rows, int nrows,
                                                                       double *__restrict__ sums) {
     __shared__ double red[4 * kSumWaves];
@@ -524,12 +565,12 @@ __global__ void __launch_bounds__(kSumThreads) level_sums_fold_kernel(const doub
         for (int k = 0; k < 4; ++k) sums[4 * l + k] = v[k];
 }
 
-// psi[z] <- e_k psi[z] + l_k, k = C(z), in place: one read and one write of the
-// state (n = 22: 27 us, 5.1 TB/s).
+// psi[z] <- e_k psi[z] + l_k, k = C(z) (or the slot above m), in place: one read
+// and one write of the state (n = 22: 27 us, 5.1 TB/s).
 constexpr int kApplyThreads = 256, kApplyU = 4;
 __global__ void __launch_bounds__(kApplyThreads) level_apply_kernel(const uint8_t *__restrict__ cost,
                                                                     const double2 *__restrict__ table, uint64_t N,
-                                                                    int nl, double2 *__restrict__ psi) {
+                                                                    int ns, double2 *__restrict__ psi) {
     __shared__ double2 tab[2 * kLevels];
     tab[threadIdx.x] = table[threadIdx.x];
     tab[threadIdx.x + kLevels] = table[threadIdx.x + kLevels];
@@ -550,7 +591,7 @@ __global__ void __launch_bounds__(kApplyThreads) level_apply_kernel(const uint8_
         for (int u = 0; u < kApplyU; ++u) {
             const uint64_t z = base + (uint64_t)u * kApplyThreads + threadIdx.x;
             if (z >= N) continue;
-            const int k = min((int)c[u], nl - 1);
+            const int k = min((int)c[u], ns - 1);
             const double2 e = tab[2 * k], l = tab[2 * k + 1];
             put(double2{e.x * x[u].x - e.y * x[u].y + l.x, e.x * x[u].y + e.y * x[u].x + l.y}, psi + z);
         }
@@ -605,22 +646,22 @@ int level_evolve(const LevelEvolve &e, hipStream_t st) {
     uint32_t *rows = reinterpret_cast<uint32_t *>(e.rows);
     LevelRunArgs r{e.cost, sums, rows, 0, e.n, e.m, e.p, e.target, inl ? nullptr : e.angles_dev, psi, table, e.readout};
     if (!e.init_uniform) {
-        const int nl = e.m + 1;
+        const int ns = given_slots(e.m);
         const unsigned blocks =
             (unsigned)std::min<uint64_t>(kLevelMaxRows, std::max<uint64_t>(1, N / (kSumThreads * kSumU)));
-        const int C = level_sums_cols(nl);
-        const size_t lds = level_sums_lds(nl, C);
+        const int C = level_sums_cols(ns);
+        const size_t lds = level_sums_lds(ns, C);
         if (lds > dev.lds_per_block) return fail(GQAOA_EINVAL, "internal: level sums need %zu bytes of LDS", lds);
         const auto fn = C == 16 ? level_sums_kernel<16> : C == 8 ? level_sums_kernel<8> : level_sums_kernel<4>;
-        hipLaunchKernelGGL(fn, dim3(blocks), dim3(kSumThreads), lds, st, e.cost, psi, N, nl, sum_rows);
+        hipLaunchKernelGGL(fn, dim3(blocks), dim3(kSumThreads), lds, st, e.cost, psi, N, e.m, sum_rows);
         GQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(level_sums_fold_kernel, dim3(nl), dim3(kSumThreads), 0, st, sum_rows, (int)blocks, sums);
+        hipLaunchKernelGGL(level_sums_fold_kernel, dim3(ns), dim3(kSumThreads), 0, st, sum_rows, (int)blocks, sums);
         GQ_LAUNCH_CHECK();
         launch_run<kGiven>(r, e, inl, st);
         GQ_LAUNCH_CHECK();
         const unsigned ab = (unsigned)std::min<uint64_t>(
             std::max<uint64_t>(1, N / (kApplyThreads * kApplyU)), (uint64_t)dev.num_cus * 1024);
-        hipLaunchKernelGGL(level_apply_kernel, dim3(ab), dim3(kApplyThreads), 0, st, e.cost, table, N, nl, psi);
+        hipLaunchKernelGGL(level_apply_kernel, dim3(ab), dim3(kApplyThreads), 0, st, e.cost, table, N, ns, psi);
         GQ_LAUNCH_CHECK();
         return GQAOA_OK;
     }

@@ -120,3 +120,33 @@ def test_given_state_in_level_form(n, m, p, odd):
         assert np.abs(got[0] - rp).max() < 1e-12 and np.abs(plan.psi.cpu().numpy() - rpsi).max() < 1e-12
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("uniform", [False, True])
+@pytest.mark.parametrize("n,m,p", [(4, 3, 1), (8, 97, 2), (8, 98, 17), (10, 188, 1), (10, 189, 3), (12, 254, 2),
+                                   (16, 40, 15), (16, 5, 113)])
+def test_costs_above_m_get_the_phase_factor_zero(n, m, p, uniform, monkeypatch):
+    """A cost table with entries above m (m the level sums' column counts on
+    either side, and 254, where one level is above): the level form gives what
+    the round passes give, whose phase tables hold 0 there. 1e-12 on the
+    probabilities, the norm and every amplitude, 255e-12 on E."""
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(850 + 7 * n + m))
+    cost = rng.integers(0, m + 1, 2 ** n).astype(np.uint8)
+    above = rng.random(2 ** n) < 0.1
+    above[1] = True
+    cost[above] = rng.integers(m + 1, 256, int(above.sum()))
+    v = rng.normal(size=2 ** n) + 1j * rng.normal(size=2 ** n)
+    v /= np.linalg.norm(v)
+    dev = torch.from_numpy(cost).cuda()
+    b, gm = rng.uniform(0, 2 * np.pi, p), rng.uniform(0, np.pi, p)
+    target = int(cost[~above][0])
+    log(f"costs above m n={n} m={m} p={p} uniform={uniform}")
+    call = lambda: g.gqaoa_evolve(n, m, dev, b, gm, dtype=g.C128, psi=torch.tensor(v, device="cuda"),
+                                  init_uniform=uniform, target_level=target)
+    psi, ps, en, no = call()
+    monkeypatch.setenv("GQAOA_SV_RESIDENT", "0")
+    rpsi, rp, re, rn = call()
+    assert np.abs(ps - rp).max() < 1e-12 and np.abs(no - rn).max() < 1e-12
+    assert np.abs(en - re).max() < 255e-12
+    assert (psi - rpsi).abs().max().item() < 1e-12
