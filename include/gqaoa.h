@@ -132,7 +132,8 @@ int gqaoa_cost_batched(int num_inst, const int32_t *n_host, const int32_t *m_hos
  * complex64 states are evolved round by round, every round rounding to float32.
  * complex128 ones take the level form: the rounds run in float64 on the level
  * weights (and, from a given state, on its level sums) and the final state is
- * written once, so their cost hardly depends on p.
+ * written once, so their cost hardly depends on p (the few calls of at most one
+ * round that a pass over the state serves faster take the pass).
  * ws_dev/ws_bytes: device scratch of gqaoa_workspace_bytes(n, p, dt, 0) bytes.
  * Errors: EINVAL (NULL cost/psi/angles/ws, bad dtype), ERANGE (n, m, p,
  * target_level outside [0, m]), EWORKSPACE. */

@@ -1334,18 +1334,25 @@ static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, co
 // ---- entry points (validated by the ABI layer) ---------------------------------------------
 // complex128 evolutions take the level form (level.hip): two passes over the
 // cost table (and, for a given state, two reads of it), one write of the state
-// and O(pK) level operations instead of p passes over the state. It is the
-// faster one at every n and p (from |s>: n = 10, p = 20: 40 us against 138 us of
-// the resident rounds; n = 18, p = 32: 49 against 409 us of streamed rounds;
-// n = 28, p = 64: 0.91 against 94 ms, p = 1: 0.89 against 2.5 ms; from a given
-// state: n = 10, p = 20: 50 against 206 us; n = 22, p = 16: 89 against 615 us;
-// n = 28, p = 64: 2.9 against 95 ms, p = 1: 2.8 against 3.0 ms).
+// and O(pK) level operations instead of p passes over the state (from |s>: n = 10,
+// p = 20: 40 us against 138 us of the resident rounds it replaced; n = 18, p = 32:
+// 49 against 409 us of streamed rounds; n = 28, p = 64: 0.91 against 94 ms, p = 1:
+// 0.89 against 2.5 ms; from a given state: n = 10, p = 20: 50 against 206 us;
+// n = 22, p = 16: 89 against 615 us; n = 28, p = 64: 2.9 against 95 ms).
+// Where it does no less work than the passes, they are the faster ones:
+//   p = 0 from |s> with 2^25 amplitudes or more, where the pass counts and writes
+//     at once (n = 25 128 us against 137, n = 28 794 against 886; n = 24 87, 86);
+//   one round from a given state of 2^23 or more with more than 188 levels, whose
+//     sums take four columns of LDS (n = 23 157 against 168 us, n = 28 2.88 against
+//     3.95 ms; n = 22 114, 107; two rounds 4.27, 3.96; up to 188 levels 2.88, 2.83).
 // Round passes stay for complex64, whose float32 rounding in every round is
 // part of its results, and for the tuning hooks, which ask for a form of them
 // (GQAOA_SV_RESIDENT=0, GQAOA_SV_SHAPE, GQAOA_SV_FUSE=1). p = 0 leaves a given
 // state alone: one readout pass.
-static bool level_form(int dtype, int init_uniform, int p) {
-    if (dtype != GQAOA_C128 || (!init_uniform && p == 0)) return false;
+static bool level_form(int dtype, int init_uniform, int n, int m, int p) {
+    if (dtype != GQAOA_C128) return false;
+    if (p == 0 && (!init_uniform || n >= 25)) return false;
+    if (p == 1 && !init_uniform && n >= 23 && m > 188) return false;
     const char *r = getenv("GQAOA_SV_RESIDENT");
     return !(r && r[0] == '0') && !getenv("GQAOA_SV_SHAPE") && !fuse_requested();
 }
@@ -1378,7 +1385,7 @@ int run_evolve(int n, int m, const uint8_t *cost, int p, const double *beta, con
     std::unique_ptr<char[]> up;
     int s;
     const double *readout;
-    if (level_form(dtype, init_uniform, p)) {
+    if (level_form(dtype, init_uniform, n, m, p)) {
         LevelEvolve le = level_args(n, m, cost, p, init_uniform, psi, target, ws);
         le.beta_host = beta;
         le.gamma_host = gamma;
@@ -1483,7 +1490,7 @@ static int run_grad_level(int num_inst, int n, const int32_t *m_of, const uint8_
 int run_grad(int num_inst, int n, const int32_t *m_of, const uint8_t *cost, int p,
              const double *beta, const double *gamma, int dtype, const int32_t *targets,
              int ckpt_every, double *psol, double *dbeta, double *dgamma, void *ws, hipStream_t st) {
-    if (level_form(dtype, 1, p))
+    if (level_form(dtype, 1, n, 0, p))
         return run_grad_level(num_inst, n, m_of, cost, p, beta, gamma, targets, psol, dbeta, dgamma, ws, st);
     FwdPlan P;
     std::unique_ptr<char[]> up;
@@ -1699,7 +1706,7 @@ int evolve_plan_create(int n, int m, const uint8_t *cost, int p, int dtype, int 
     P.chain = chain_rule(P);
     GQ_HIP(hipHostMalloc(reinterpret_cast<void **>(&E->stage), sizeof(double) * (2 * (size_t)p + 3 * ((size_t)p + 1)),
                          hipHostMallocDefault));
-    if (level_form(dtype, init_uniform, p)) {
+    if (level_form(dtype, init_uniform, n, m, p)) {
         E->level = true;
         E->le = level_args(n, m, cost, p, init_uniform, psi, target, ws);
         E->le.beta_host = E->stage;

@@ -150,3 +150,43 @@ def test_costs_above_m_get_the_phase_factor_zero(n, m, p, uniform, monkeypatch):
     assert np.abs(ps - rp).max() < 1e-12 and np.abs(no - rn).max() < 1e-12
     assert np.abs(en - re).max() < 255e-12
     assert (psi - rpsi).abs().max().item() < 1e-12
+
+
+@pytest.mark.parametrize("n,m,p,uniform,passes", [
+    (23, 189, 1, False, 1), (23, 255, 1, False, 1), (23, 188, 1, False, 0), (22, 255, 1, False, 0),
+    (23, 255, 2, False, 0), (23, 255, 1, True, 0), (24, 50, 0, True, 0), (25, 50, 0, True, 0), (25, 50, 1, True, 0)])
+def test_the_faster_form_of_few_rounds(n, m, p, uniform, passes):
+    """One round from a given large state with many levels goes through a round
+    pass (`passes` of them timed under their name), its neighbours and calls
+    from |s> take the level form, and p = 0 from |s> writes |s> either way.
+    Readouts and sampled amplitudes from level sums in float64: 1e-12, E 1e-12 m."""
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(900 + 7 * n + m + p))
+    N = 2 ** n
+    cost = torch.from_numpy(rng.integers(0, m + 1, N).astype(np.uint8)).cuda()
+    b, gm = rng.uniform(0, 2 * np.pi, p), rng.uniform(0, np.pi, p)
+    psi0 = torch.full((N,), 2.0 ** (-n / 2), dtype=torch.complex128, device="cuda")
+    if not uniform:
+        psi0 *= torch.polar(torch.ones(N, dtype=torch.float64, device="cuda"),
+                            torch.linspace(0, 2, N, dtype=torch.float64, device="cuda"))
+    log(f"few rounds n={n} m={m} p={p} uniform={uniform}")
+    want = psi0.clone()
+    E, P = [], []
+    lev = cost.double()
+    for j in range(p + 1):
+        if j:
+            want *= torch.polar(torch.ones_like(lev), -gm[j - 1] * lev)
+            want += complex(np.exp(-1j * b[j - 1]) - 1) * want.mean()
+        q = want.real ** 2 + want.imag ** 2
+        E.append((q * lev).sum().item())
+        P.append(q[cost == 7].sum().item())
+    g.gqaoa_profile_reset()
+    g.gqaoa_profile_enable(1)
+    try:
+        psi, ps, en, no = g.gqaoa_evolve(n, m, cost, b, gm, dtype=g.C128, psi=psi0, init_uniform=uniform, target_level=7)
+        assert g.gqaoa_profile_read("sv_round_c128")[1] == passes
+    finally:
+        g.gqaoa_profile_enable(0)
+        g.gqaoa_profile_reset()
+    assert np.abs(ps - P).max() < 1e-12 and np.abs(en - E).max() < 1e-12 * m and np.abs(no - 1).max() < 1e-12
+    assert (psi - want).abs().max().item() < 1e-12
