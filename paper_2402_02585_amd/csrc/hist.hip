@@ -238,11 +238,14 @@ __device__ __forceinline__ void scan_table(const ScanArgs &a, const ScanSlot &sl
 // (1% and 1e-6 per round of P, 1e-4) are wide of what float32 rounding moves.
 constexpr int kReachEvery = 16;  // rounds between the checks (under 1% of their arithmetic)
 struct ScanReach {
-    float th, d, rel;
+    float th, d, rel;  // th and rel in scalar registers: the rounds have no vector register to spare
+    static __device__ __forceinline__ float uniform(float x) {
+        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+    }
     __device__ __forceinline__ ScanReach(const ScanSlot &sl, float S, float w0, float mr, float mi) {
-        th = sl.unit ? asinf(sqrtf(fminf(fmaxf(S, 0.f), 1.f))) : 0.f;  // th = 0: always within reach
+        th = uniform(sl.unit ? asinf(sqrtf(fminf(fmaxf(S, 0.f), 1.f))) : 0.f);  // th = 0: always within reach
         d = asinf(fminf(sqrtf(w0 * (1.f - w0) * (mr * mr + mi * mi)), 1.f));
-        rel = 0.99f - 1e-6f * (float)sl.pmax;
+        rel = uniform(0.99f - 1e-6f * (float)sl.pmax);
     }
     // P after a round with r more to come
     __device__ __forceinline__ bool out_of_reach(float P, int r) const {
@@ -280,21 +283,21 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
         pi[k] = 0.f;
     }
     float cr = 0.f, ci = 0.f;
-    int q = 0;
-    int found = 0;
-    int pmax = sl.pmax;
-    int next_p = CROSS ? 0 : a.p_list[0];   // next readout round, kept in a register
-    const ScanReach reach(sl, CROSS ? a.threshold : 0.f, w0, mr, mi);
-    if constexpr (CROSS)
-        if (__ballot(active && !reach.out_of_reach(w0, pmax)) == 0) pmax = 0;  // wave-uniform
-    for (int j = 1; j <= pmax; ++j) {
-        // Small tables stay in registers across rounds; larger ones are
-        // re-read from LDS (broadcast) each round to bound register use.
+    // One round: phases, <s|phi> and the mixer's correction. Small tables stay in
+    // registers across rounds (the crossing form's, whose rounds come in runs, by
+    // name: the compiler would load them once a run); larger ones are re-read from
+    // LDS (broadcast) each round to bound register use.
+    constexpr bool kHeld = CROSS && KMAX <= kScanHoist3;
+    float4 held[kHeld ? KMAX : 1];
+    if constexpr (kHeld)
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) held[k] = tab[k];
+    auto round = [&]() {
         if constexpr (KMAX > kScanHoist3) asm volatile("" ::: "memory");
         float sr = 0.f, si = 0.f;
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
-            const float4 e = tab[k];
+            const float4 e = kHeld ? held[kHeld ? k : 0] : tab[k];
             const float xr = pr[k] + cr, xi = pi[k] + ci;               // b_k after the last mixer
             const float nr = __builtin_fmaf(e.x, xr, e.z * xi);         // cos br + sin bi
             float ni;                                                    // cos bi - sin br
@@ -312,22 +315,45 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
         cr = __builtin_fmaf(mr, sr, -(mi * si));
         if constexpr (CROSS && KMAX >= 20 && KMAX <= 32) ci = __builtin_fmaf(mi, sr, mr * si);
         else ci = __builtin_fmaf(mr, si, mi * sr);
-        if constexpr (CROSS) {
-            const float b0r = pr[0] + cr, b0i = pi[0] + ci;
-            const float P = w0 * __builtin_fmaf(b0r, b0r, b0i * b0i);
-            if (found == 0 && P >= a.threshold) found = j;
-            bool live = active && found == 0;
-            if (j % kReachEvery == 0) live = live && !reach.out_of_reach(P, pmax - j);
-            if (__ballot(live) == 0) break;  // wave-uniform
-        } else if (j == next_p) {
+    };
+    auto target_prob = [&]() {
+        const float b0r = pr[0] + cr, b0i = pi[0] + ci;
+        return w0 * __builtin_fmaf(b0r, b0r, b0i * b0i);
+    };
+    if constexpr (CROSS) {
+        // The reach is checked between runs of rounds: inside the round loop the
+        // check cost every round its schedule (one instance of 10 levels, 1,000
+        // rounds: 320 us without a check, 354 with; in runs, and the round's own test
+        // without branches, 306).
+        const ScanReach reach(sl, a.threshold, w0, mr, mi);
+        const int pmax = __builtin_amdgcn_readfirstlane(sl.pmax);  // and so j and stop: scalar
+        int found = 0;
+        // (wave-uniform; P again from its amplitude, which is there anyway)
+        for (int j = 0; __ballot(active && found == 0 && !reach.out_of_reach(target_prob(), pmax - j)) != 0;) {
+            const int stop = min(pmax, j + kReachEvery);
+            while (j < stop) {
+                round();
+                ++j;
+                const bool hit = (found == 0) & (target_prob() >= a.threshold);
+                found = hit ? j : found;
+                if (__builtin_amdgcn_ballot_w64(active & (found == 0)) == 0) break;  // wave-uniform
+            }
+            if (j >= pmax) break;
+        }
+        if (active) a.first_p[((size_t)sl.inst * a.ng + it.g) * a.nb + b] = found;
+    } else {
+        int q = 0;
+        int next_p = a.p_list[0];   // next readout round, kept in a register
+        for (int j = 1; j <= sl.pmax; ++j) {
+            round();
+            if (j != next_p) continue;
             float E = 0.f;
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const float br = pr[k] + cr, bi = pi[k] + ci;
                 E = __builtin_fmaf(kw[k], __builtin_fmaf(br, br, bi * bi), E);
             }
-            const float b0r = pr[0] + cr, b0i = pi[0] + ci;
-            const float P = w0 * __builtin_fmaf(b0r, b0r, b0i * b0i);
+            const float P = target_prob();
             if (active) {
                 const size_t o = (((size_t)sl.inst * a.num_p + q) * a.ng + it.g) * a.nb + b;
                 a.psol[o] = P;
@@ -337,8 +363,6 @@ __device__ __forceinline__ void scan_rounds(const ScanArgs &a, const ScanSlot &s
             next_p = q < a.num_p ? a.p_list[q] : 0;
         }
     }
-    if constexpr (CROSS)
-        if (active) a.first_p[((size_t)sl.inst * a.ng + it.g) * a.nb + b] = found;
 }
 
 // Mixer factor of this lane's beta, recomputed only when the beta row changes

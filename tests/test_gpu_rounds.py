@@ -257,3 +257,20 @@ def test_crossing_buckets_side_by_side():
             for _ in range(2):
                 got = g.gqaoa_scan_crossing(ns, ms, H, gb, gg, caps, 0.5, targets=tg)
                 assert (got.cpu().numpy() == alone).all()
+
+
+@pytest.mark.parametrize("K", [3, 20, 33, 50])
+def test_caps_at_the_runs_of_rounds(K):
+    """Rounds go in runs of 16: caps one below, at and one above a run's end, and
+    of one round, cut the crossings of a longer search and change none."""
+    need_gpu()
+    rng = np.random.Generator(np.random.PCG64(83 + K))
+    h = np.zeros((1, 64), dtype=np.uint64)
+    h[0, :K] = rng.multinomial((1 << 14) - 5 * K, np.ones(K) / K) + 5
+    h[0, 0] -= h[0].sum() - (1 << 14)
+    gb, gg = optim.fundamental_grid(36, 18)
+    full = g.gqaoa_scan_crossing([14], [63], h, gb, gg, 80, 0.3).cpu().numpy()
+    log(f"runs of rounds K={K}: crossings at rounds {sorted(set(full[full > 0].tolist()))}")
+    for cap in (1, 15, 16, 17, 31, 32, 33, 48):
+        got = g.gqaoa_scan_crossing([14], [63], h, gb, gg, cap, 0.3).cpu().numpy()
+        assert (got == np.where(full <= cap, full, 0)).all(), cap
