@@ -722,6 +722,29 @@ struct SideStreams {
     }
 };
 
+// Side streams of a crossing scan over the buckets `used`: as many as run beside
+// the caller's, none where the fork and join cost more than the overlap can give
+// (about 16 us and 14 more per stream). A bucket alone takes about 3 us and 0.1 +
+// 0.02 us per round and level for every fill of the device (8 waves per CU); the
+// overlap saves what exceeds the longest one and an even share. 16 instances of 10
+// to 60 levels, 90 x 45 pairs: 1 round 184 us forked and 142 in turn, 4 rounds 184
+// and 193, 16 rounds 195 and 353; 2 instances, 64 rounds 119 and 121.
+static size_t crossing_side_streams(const ScanHost &H, const std::vector<int> &used, unsigned items_per_slot,
+                                    const DeviceInfo &dev) {
+    const size_t ways = std::min<size_t>(used.size(), 4);
+    double total = 0.0, longest = 0.0;
+    for (int bk : used) {
+        int cap = 0;
+        for (int i = H.bucket_first[bk]; i < H.bucket_first[bk + 1]; ++i) cap = std::max(cap, H.slots[i].pmax);
+        const double fills = (double)(H.bucket_first[bk + 1] - H.bucket_first[bk]) * items_per_slot / (8.0 * dev.num_cus);
+        const double us = std::max(1.0, fills) * (3.0 + cap * (0.1 + 0.02 * kBuckets[bk]));
+        total += us;
+        longest = std::max(longest, us);
+    }
+    const double saves = total - std::max(longest, total / (double)std::max<size_t>(ways, 1));
+    return ways > 1 && saves > 16.0 + 14.0 * (double)(ways - 1) ? ways - 1 : 0;
+}
+
 int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const uint64_t *hists,
              int hist_stride, const int32_t *target_host, int nb, const double *betas, int ng,
              const double *gammas, int per_inst, int num_p, const int32_t *p_list, float *psol, float *energy,
@@ -768,8 +791,9 @@ int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const u
         if (H.bucket_first[bk + 1] > H.bucket_first[bk]) used.push_back(bk);
     if (!first_p) std::reverse(used.begin(), used.end());
     SideStreams side(dev.device);
-    if (first_p && used.size() > 1)
-        if ((s = side.fork(std::min<size_t>(used.size(), 4) - 1, st))) return s;
+    if (first_p)
+        if (const size_t n = crossing_side_streams(H, used, (unsigned)ng * (unsigned)a.ntiles, dev))
+            if ((s = side.fork(n, st))) return s;
     for (size_t u = 0; u < used.size(); ++u) {
         const int bk = used[u];
         const size_t branch = u % (side.streams.size() + 1);

@@ -274,3 +274,22 @@ def test_caps_at_the_runs_of_rounds(K):
     for cap in (1, 15, 16, 17, 31, 32, 33, 48):
         got = g.gqaoa_scan_crossing([14], [63], h, gb, gg, cap, 0.3).cpu().numpy()
         assert (got == np.where(full <= cap, full, 0)).all(), cap
+
+
+@pytest.mark.parametrize("cap", [1, 4, 16, 64])
+def test_crossing_buckets_in_turn_and_side_by_side(cap):
+    """Short searches run their buckets in turn, longer ones side by side: either
+    way the first crossings are those of each instance alone."""
+    need_gpu()
+    rng = np.random.Generator(np.random.PCG64(91))
+    I = 14
+    H = np.zeros((I, 64), dtype=np.uint64)
+    for i, K in enumerate(range(2, 2 + 4 * I, 4)):
+        H[i, :K] = rng.multinomial((1 << 13) - K, rng.dirichlet(np.ones(K))) + 1
+    gb, gg = optim.fundamental_grid(24, 12)
+    ns, ms = np.full(I, 13), np.full(I, 63)
+    log(f"crossing buckets cap={cap}")
+    got = g.gqaoa_scan_crossing(ns, ms, H, gb, gg, cap, 0.2).cpu().numpy()
+    for i in range(I):
+        one = g.gqaoa_scan_crossing(ns[:1], ms[:1], H[i:i + 1], gb, gg, cap, 0.2).cpu().numpy()
+        assert (got[i] == one[0]).all(), i
