@@ -671,14 +671,18 @@ int scan_choose_tile(int bucket, const DeviceInfo &dev, const ScanArgs &a, unsig
         return GQAOA_OK;
     }
     if (a.first_p) {
-        // The crossing form takes its items from a queue, so the more waves the
-        // better as long as they are resident (the rest find the queue empty):
-        // at 2 or more waves per SIMD every shape is within 2% (128 unsatisfiable
-        // instances, 360 x 181 pairs: 12.5 ms), at one wave 22 ms. Timing a
-        // prefix of it cannot tell: items run from one round to their cap, and
-        // a prefix of one fill chose one wave per SIMD. Few items go out as
-        // blocks of one wave, which spread over all CUs.
-        *out = a.total_items < 8u * (unsigned)dev.num_cus ? TileChoice{1, 32} : TileChoice{4, 8};
+        // The crossing form takes its items from a queue. Long items want two waves
+        // per SIMD and gain nothing from more; short ones wait for the queue's
+        // counter, the longer the more waves ask for it. Blocks of one wave, which
+        // the hardware spreads best: 256 instances, 230 x 92 pairs, 1 round 1,262 us
+        // at 1 wave per CU, 1,309 at 2, 1,520 at 8, 2,266 at 32; 32 rounds 2,051 at
+        // 2, 1,612 at 4, 1,704 at 8; 64 rounds 3,716 at 2, 2,478 at 4, 2,475 at 8,
+        // 3,188 at 32; 128 unsatisfiable instances, 360 x 181 pairs, caps of 400
+        // 9,528 at 2, 7,056 at 4, 7,005 at 8, 7,495 at 32 (blocks of four waves).
+        // Timing a prefix of the queue cannot tell: items run from one round to
+        // their cap, and a prefix of one fill chose one wave per SIMD.
+        const int cap = a.p_list[a.num_p - 1];
+        *out = TileChoice{1, cap <= 16 ? 2 : cap <= 50 ? 4 : 8};
         return GQAOA_OK;
     }
     return tune_bucket(bucket, dev, a, counter, st, out);
