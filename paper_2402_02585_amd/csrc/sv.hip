@@ -1204,14 +1204,18 @@ static bool fused_round(const FwdPlan &P) {
 // blocks in all a batch still gains 2% (64 gradients of n = 18, 16 of n = 20), at n
 // = 25 a round loses 1%, at n = 28 2%, and 64 gradients of n = 20 (32,768 blocks of
 // 512 rows) 4%. The reverse passes of a gradient chain in the same way (1 of n = 18,
-// p = 32: 700 -> 451 us, the device's tables included).
-constexpr int kChainBlocks = 8192;
+// p = 32: 700 -> 451 us, the device's tables included), and gain more: sweeps of
+// forward passes alone stop at 2,048 blocks of 512 rows (n = 20, 64 rounds: 4
+// items 1,297 us chained and 1,334 separate, 5 items 1,523 and 1,491, 16 items 3,632
+// and 3,418; gradients of 12 instances 1,996 and 2,007, of 16 2,506 and 2,505).
+constexpr int kChainBlocks = 8192, kChainForwardBlocks = 2048;
 
-static bool chain_rule(const FwdPlan &P) {
+static bool chain_rule(const FwdPlan &P, bool reverse) {
     const PassShape &s = P.shape;
+    const int most = reverse || s.blocks_x <= kChainRows / 2 || s.blocks_x > kFinThreads ? kChainBlocks : kChainForwardBlocks;
     return P.dtype == GQAOA_C64 && P.p > 0 && s.amp == 2 && s.unroll == 4 && s.nt == 1 &&
            (s.blocks_x <= kChainRows || s.blocks_x > kFinThreads) && (uint64_t)s.blocks_x * kSvThreads * 8 >= P.N &&
-           (int64_t)P.num_inst * s.blocks_x <= kChainBlocks && !fused_round(P);
+           (int64_t)P.num_inst * s.blocks_x <= most && !fused_round(P);
 }
 
 // Pass j of a chain (1-based; j = p + 1: the final pass): its rows go to one of
@@ -1307,7 +1311,7 @@ static int prepare_plan(FwdPlan &P, int num_inst, int n, const int32_t *m_of, co
     P.ws = reinterpret_cast<char *>(ws);
     P.L = sv_layout(num_inst, n, p, dtype, ckpt_every, grad);
     P.shape = pass_shape(P.N, num_inst, dtype, dev, fuse_requested());
-    P.chain = chain_rule(P);
+    P.chain = chain_rule(P, grad);
     P.cost = cost;
     const SvLayout &L = P.L;
     const size_t I = (size_t)num_inst, m_at = L.partials - L.angles, bytes = m_at + I * 4;
@@ -1703,7 +1707,7 @@ int evolve_plan_create(int n, int m, const uint8_t *cost, int p, int dtype, int 
     // (n = 16..22, complex64).
     P.fuse_mode = -1;
     P.shape = pass_shape(P.N, 1, dtype, dev);
-    P.chain = chain_rule(P);
+    P.chain = chain_rule(P, false);
     GQ_HIP(hipHostMalloc(reinterpret_cast<void **>(&E->stage), sizeof(double) * (2 * (size_t)p + 3 * ((size_t)p + 1)),
                          hipHostMallocDefault));
     if (level_form(dtype, init_uniform, n, m, p)) {
@@ -1812,7 +1816,7 @@ int sv_items_stream(int n, int count, const int32_t *item_inst, const int32_t *i
         P.L = sv_layout(cnt, n, p, GQAOA_C64, 0, false);
         P.shape = pass_shape(N, cnt, GQAOA_C64, dev);
         P.fuse_mode = -1;
-        P.chain = chain_rule(P);
+        P.chain = chain_rule(P, false);
         auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
         const size_t o_cost = al(P.L.total), o_psi = o_cost + al(cnt * N), o_off = o_psi + al(cnt * N * 8);
         const size_t o_m = o_off + al(8 * (size_t)cnt), o_out = o_m + al(4 * (size_t)cnt);

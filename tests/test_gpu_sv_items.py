@@ -145,3 +145,20 @@ def test_items_at_the_size_limit():
     for k in range(2):
         _, rp, _, _ = evolve_sv(n, ref, np.full(30, beta[k]), np.full(30, gamma[k]))
         assert np.abs(ps.cpu().numpy()[k] - rp[[2, 7, 30]]).max() < 1e-5
+
+
+@pytest.mark.parametrize("n,count", [(19, 5), (20, 4), (20, 5)])
+def test_streamed_items_on_both_sides_of_the_chain(n, count):
+    """Streamed items of n = 20 chain their passes up to four at a time (2,048
+    blocks of 512 rows) and finalize separately beyond: either way an item gives
+    the bits that it gives alone."""
+    torch = need_gpu()
+    m = 60
+    costs, _, _ = g.gqaoa_cost_batched([n], [m], [rand_lits(n, m, 700 + n)], with_hist=False)
+    rng = np.random.Generator(np.random.PCG64(700 + n + count))
+    b, gm = rng.uniform(0, 2 * np.pi, count), rng.uniform(0, np.pi, count)
+    log(f"streamed items n={n} count={count}")
+    psol, en = g.gqaoa_sv_items([n], [m], costs, np.zeros(count, np.int32), b, gm, [1, 3], targets=[7], with_energy=True)
+    for k in range(count):
+        one = g.gqaoa_sv_items([n], [m], costs, [0], b[k:k + 1], gm[k:k + 1], [1, 3], targets=[7], with_energy=True)
+        assert torch.equal(one[0][0], psol[k]) and torch.equal(one[1][0], en[k]), k
