@@ -28,6 +28,12 @@ namespace gqaoa {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+// The same in global memory. Parameters and the activation cache are the caller's
+// and may lie at any float's address (the rows of a stack of networks are 8 bytes
+// off a multiple of 16), where one 16-byte access still serves.
+typedef f32x4 f32x4_g __attribute__((aligned(4)));
+typedef u16x8 u16x8_g __attribute__((aligned(4)));
+typedef unsigned int u32x2_g __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int kDIn = 131, kDInPad = 160, kDH = 256, kDOut = 2;
 constexpr size_t kOffW1 = 0;
@@ -104,7 +110,7 @@ __device__ __forceinline__ void load_blocks(const float *__restrict__ w, f32x4 (
     for (int q = 0; q < Q; ++q)
         if (64 * q + k < ROWS)  // whole waves
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[q][r] = *reinterpret_cast<const f32x4 *>(w + (size_t)(64 * q + k + r) * kDH + n);
+            for (int r = 0; r < 4; ++r) v[q][r] = *reinterpret_cast<const f32x4_g *>(w + (size_t)(64 * q + k + r) * kDH + n);
 }
 // LDS image of a transposed weight matrix: column n's bfloat16 k values in a
 // row of 512 bytes, its 16-byte chunk c (k = 8 c ..) at chunk c ^ (n's bits 3,
@@ -138,8 +144,8 @@ __device__ __forceinline__ void keep_w2(const f32x4 (&v)[kDH / 64][4], uint16_t 
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (((uint32_t)(k + r) & (P - 1)) == blockIdx.x)  // 64 q is a multiple of P
-                *reinterpret_cast<uint2 *>(wb + (size_t)(64 * q + k + r) * kDH + n) =
-                    make_uint2(f2bf2(v[q][r][0], v[q][r][1]), f2bf2(v[q][r][2], v[q][r][3]));
+                *reinterpret_cast<u32x2_g *>(wb + (size_t)(64 * q + k + r) * kDH + n) =
+                    u32x2_g{f2bf2(v[q][r][0], v[q][r][1]), f2bf2(v[q][r][2], v[q][r][3])};
 }
 
 // acc = A B over KS k steps: A rows [ROWS] and B columns (this wave's 16) in
@@ -234,7 +240,7 @@ __global__ void __launch_bounds__(kTrThreads) mlp_forward_kernel(const float *__
     load_blocks<kDH>(prm + kOffW2, v2);
     for (int i = tid; i < rows * (kDInPad / 8); i += kTrThreads) {
         const int r = i / (kDInPad / 8), c = i % (kDInPad / 8) * 8;
-        *reinterpret_cast<u16x8 *>(a.xb + (size_t)(row0 + r) * kDInPad + c) =
+        *reinterpret_cast<u16x8_g *>(a.xb + (size_t)(row0 + r) * kDInPad + c) =
             *reinterpret_cast<const u16x8 *>(s + r * kXLd + c);
     }
     f32x4 acc[ROWS / 16];
@@ -281,7 +287,7 @@ __global__ void __launch_bounds__(kTrThreads) mlp_back_rows_kernel(const float *
     u16x8 c[kCopies];
 #pragma unroll
     for (int q = 0; q < kCopies; ++q)
-        c[q] = *reinterpret_cast<const u16x8 *>(a.wb + kOffW2 + (size_t)(tid + kTrThreads * q) * 8);
+        c[q] = *reinterpret_cast<const u16x8_g *>(a.wb + kOffW2 + (size_t)(tid + kTrThreads * q) * 8);
     // every load of the block before its first use: this thread's z2 (unit j of
     // rows tid / 256 + 4 q) and the z1 of its rows of the product
     const int j = tid % kDH, n = wave * 16 + (lane & 15);
@@ -345,7 +351,7 @@ struct GwOperand {
             for (int r = 0; r < 4; ++r) {
                 const int k = k0 + 128 * q + kr + r;
                 v[q][r] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                if (k < batch) v[q][r] = *reinterpret_cast<const u16x8 *>(p + (size_t)k * ld + c);
+                if (k < batch) v[q][r] = *reinterpret_cast<const u16x8_g *>(p + (size_t)k * ld + c);
             }
     }
     __device__ __forceinline__ void put(const u16x8 (&v)[kGwK / 128][4], uint16_t *dst) const {
@@ -372,7 +378,7 @@ __device__ __forceinline__ void column_sums(const uint16_t *__restrict__ src, co
 #pragma unroll
         for (int o = 0; o < NO; ++o) s[e][o] = 0.0;
     for (int b = rg; b < batch; b += 64) {
-        const u16x8 v = *reinterpret_cast<const u16x8 *>(src + (size_t)b * kDH + c);
+        const u16x8 v = *reinterpret_cast<const u16x8_g *>(src + (size_t)b * kDH + c);
         double d[NO];
 #pragma unroll
         for (int o = 0; o < NO; ++o) d[o] = OUT ? (double)dout[(size_t)b * 2 + o] : 1.0;

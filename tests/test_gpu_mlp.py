@@ -190,3 +190,26 @@ def test_training_forward_independent_of_the_split():
     for a, b in ((0, 1), (0, 500), (3, 20), (8191, 8200)):
         part, _ = g.gqaoa_mlp_forward(prm, x[a:b].contiguous())
         assert torch.equal(part, whole[a:b]), (a, b)
+
+
+@pytest.mark.parametrize("B", [7, 300])
+def test_training_at_any_float_address(B):
+    """Parameters, the activation cache and gradients that start 4, 8 or 12 bytes
+    past a multiple of 16 (the rows of a stack of networks are 8 past one): the
+    same bits as at an aligned address."""
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(78))
+    src = torch.tensor(_pack(_params32(4)), device="cuda")
+    x = torch.tensor((np.abs(rng.normal(size=(B, 131))) * 0.2).astype(np.float32), device="cuda")
+    d = torch.tensor(rng.normal(size=(B, 2)).astype(np.float32), device="cuda")
+    out, act = g.gqaoa_mlp_forward(src, x)
+    grads = g.gqaoa_mlp_backward(src, act, d)
+    for off in (1, 2, 3):
+        log(f"mlp at float offset {off} B={B}")
+        prm = torch.zeros(g.MLP_NPARAMS + 4, device="cuda")[off:off + g.MLP_NPARAMS]
+        prm.copy_(src)
+        cache = torch.zeros(act.numel() + 16, dtype=torch.uint8, device="cuda")[4 * off:4 * off + act.numel()]
+        to = torch.zeros(g.MLP_NPARAMS + 4, device="cuda")[off:off + g.MLP_NPARAMS]
+        o, _ = g.gqaoa_mlp_forward(prm, x, act=cache)
+        gr = g.gqaoa_mlp_backward(prm, cache, d, grads=to)
+        assert torch.equal(o, out) and torch.equal(gr, grads), off
