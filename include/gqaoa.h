@@ -495,9 +495,13 @@ int gqaoa_gather_rows(int rows, const int32_t *idx_dev, int src_rows, const void
  * HIP events on the launch stream and accumulate their durations under a
  * name (k = 0 disables; k < 0 is EINVAL): "sv_round_c64", "sv_round_c128" (forward round
  * passes), "sv_reverse_c64", "sv_reverse_c128" (adjoint passes), "cost_table",
- * "scan", "x_pass_c64", "x_pass_c128" (X-QAOA streaming passes), and
- * "sv_resident_c64", "sv_resident_c128" (the one-launch evolution of a
- * small state, all rounds).
+ * "scan" (a bucket of a scan or crossing scan; the buckets of a crossing scan
+ * that run side by side, as one), "x_pass_c64", "x_pass_c128" (X-QAOA
+ * streaming passes), "sv_resident_c64", "sv_resident_c128" (the one-launch
+ * evolution of a small state, all rounds), and "level_evolve", "level_grad"
+ * (the launches of one complex128 evolution of several launches, and of one
+ * batch of complex128 gradients, in the level form; "sv_round_c128" and
+ * "sv_reverse_c128" count the passes that complex128 calls take otherwise).
  * Durations are collected when the call that launched them synchronizes.
  * gqaoa_profile_read returns GQAOA_EINVAL for an unknown name. */
 int gqaoa_profile_enable(int on);

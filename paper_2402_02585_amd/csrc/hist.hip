@@ -25,6 +25,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <utility>
 #include <vector>
@@ -795,9 +796,13 @@ int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const u
         if (H.bucket_first[bk + 1] > H.bucket_first[bk]) used.push_back(bk);
     if (!first_p) std::reverse(used.begin(), used.end());
     SideStreams side(dev.device);
-    if (first_p)
-        if (const size_t n = crossing_side_streams(H, used, (unsigned)ng * (unsigned)a.ntiles, dev))
-            if ((s = side.fork(n, st))) return s;
+    const size_t nside = first_p ? crossing_side_streams(H, used, (unsigned)ng * (unsigned)a.ntiles, dev) : 0;
+    // buckets side by side are timed as one, from fork to join
+    std::optional<ProfScope> all;
+    if (nside) {
+        all.emplace("scan", st);
+        if ((s = side.fork(nside, st))) return s;
+    }
     for (size_t u = 0; u < used.size(); ++u) {
         const int bk = used[u];
         const size_t branch = u % (side.streams.size() + 1);
@@ -807,11 +812,13 @@ int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const u
         ab.total_items = (unsigned)(H.bucket_first[bk + 1] - H.bucket_first[bk]) * (unsigned)ng * (unsigned)ab.ntiles;
         TileChoice tc;
         if ((s = scan_choose_tile(bk, dev, ab, D.counters + bk, tile, bs, &tc))) return s;
-        ProfScope ps("scan", bs);
+        std::optional<ProfScope> one;
+        if (!all) one.emplace("scan", bs);
         if ((s = scan_launch_bucket(bk, tc, dev, ab, D.counters + bk, bs))) return s;
-        ps.end();
+        if (one) one->end();
     }
     if ((s = side.join(st))) return s;
+    if (all) all->end();
     GQ_HIP(hipStreamSynchronize(st));  // host staging vectors end here
     if (prof_on()) prof_collect();
     return GQAOA_OK;

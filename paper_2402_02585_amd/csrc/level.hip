@@ -646,6 +646,7 @@ int level_evolve(const LevelEvolve &e, hipStream_t st) {
     uint32_t *rows = reinterpret_cast<uint32_t *>(e.rows);
     LevelRunArgs r{e.cost, sums, rows, 0, e.n, e.m, e.p, e.target, inl ? nullptr : e.angles_dev, psi, table, e.readout};
     if (!e.init_uniform) {
+        ProfScope ps("level_evolve", st);
         const int ns = given_slots(e.m);
         const unsigned blocks =
             (unsigned)std::min<uint64_t>(kLevelMaxRows, std::max<uint64_t>(1, N / (kSumThreads * kSumU)));
@@ -663,6 +664,7 @@ int level_evolve(const LevelEvolve &e, hipStream_t st) {
             std::max<uint64_t>(1, N / (kApplyThreads * kApplyU)), (uint64_t)dev.num_cus * 1024);
         hipLaunchKernelGGL(level_apply_kernel, dim3(ab), dim3(kApplyThreads), 0, st, e.cost, table, N, ns, psi);
         GQ_LAUNCH_CHECK();
+        ps.end();
         return GQAOA_OK;
     }
     if (e.n <= kLevelFusedMaxN) {
@@ -672,6 +674,7 @@ int level_evolve(const LevelEvolve &e, hipStream_t st) {
         GQ_LAUNCH_CHECK();
         return GQAOA_OK;
     }
+    ProfScope ps("level_evolve", st);
     r.nrows = (int)std::min<uint64_t>(kLevelMaxRows, std::max<uint64_t>(1, N / 16 / kCountThreads));
     hipLaunchKernelGGL(level_count_kernel, dim3(r.nrows, 1), dim3(kCountThreads), 0, st, e.cost, N, rows);
     GQ_LAUNCH_CHECK();
@@ -680,6 +683,7 @@ int level_evolve(const LevelEvolve &e, hipStream_t st) {
     const unsigned blocks = (unsigned)std::min<uint64_t>(N / (kExpThreads * kExpU), (uint64_t)dev.num_cus * 64);
     hipLaunchKernelGGL(level_expand_kernel, dim3(blocks), dim3(kExpThreads), 0, st, e.cost, table, N, psi);
     GQ_LAUNCH_CHECK();
+    ps.end();
     return GQAOA_OK;
 }
 

@@ -190,3 +190,43 @@ def test_the_faster_form_of_few_rounds(n, m, p, uniform, passes):
         g.gqaoa_profile_reset()
     assert np.abs(ps - P).max() < 1e-12 and np.abs(en - E).max() < 1e-12 * m and np.abs(no - 1).max() < 1e-12
     assert (psi - want).abs().max().item() < 1e-12
+
+
+def test_profile_names_of_the_level_form_and_the_crossing_scan():
+    """A profiled call reads back under its name: evolutions of several launches
+    (from |s> and from a given state), of one launch, gradients, and a crossing
+    scan whose buckets run side by side, timed once and not longer than the call."""
+    import time
+    torch = need_gpu()
+    rng = np.random.Generator(np.random.PCG64(950))
+    n, m, p = 16, 40, 5
+    cost = torch.from_numpy(rng.integers(0, m + 1, 2 ** n).astype(np.uint8)).cuda()
+    b, gm = rng.uniform(0, 6, p), rng.uniform(0, 3, p)
+    psi = torch.full((2 ** n,), 2.0 ** -8, dtype=torch.complex128, device="cuda")
+    h = np.zeros((9, 41), dtype=np.uint64)
+    for i, K in enumerate(range(2, 38, 4)):
+        h[i, :K] = rng.multinomial((1 << 16) - K, np.ones(K) / K) + 1
+    calls = {
+        "level_evolve": [lambda: g.gqaoa_evolve(n, m, cost, b, gm, dtype=g.C128),
+                         lambda: g.gqaoa_evolve(n, m, cost, b, gm, dtype=g.C128, psi=psi, init_uniform=False)],
+        "sv_resident_c128": [lambda: g.gqaoa_evolve(10, m, cost, b, gm, dtype=g.C128)],
+        "level_grad": [lambda: g.gqaoa_grad(n, m, cost, b, gm, dtype=g.C128)],
+        "scan": [lambda: g.gqaoa_scan_crossing([16] * 9, [40] * 9, h, np.linspace(0, 6, 90), np.linspace(0, 3, 45), 400, 0.9)],
+    }
+    for name, fs in calls.items():
+        for f in fs:
+            f()
+            torch.cuda.synchronize()
+            log(f"profile {name}")
+            g.gqaoa_profile_reset()
+            g.gqaoa_profile_enable(1)
+            try:
+                t0 = time.perf_counter()
+                f()
+                torch.cuda.synchronize()
+                wall = (time.perf_counter() - t0) * 1e3
+            finally:
+                g.gqaoa_profile_enable(0)
+            ms, count = g.gqaoa_profile_read(name)
+            g.gqaoa_profile_reset()
+            assert count == 1 and 0 < ms < wall, (name, ms, count, wall)
