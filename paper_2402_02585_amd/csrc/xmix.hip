@@ -538,8 +538,9 @@ __global__ void __launch_bounds__(1 << (TB - XCfg<T>::R)) x_pass_kernel(XPassArg
 // bytes of the table, adjacent for adjacent tiles while the tile index's low
 // bits are z bits, so lanes read consecutive 8-byte pieces; the tiles are
 // staged in LDS in element order. A thread's 2^R bytes there are 2^rb apart and
-// those of the next threads beside them (rb >= mlo >= 3), so a lane gathers the
-// words of four threads and turns each 4 x 4 bytes over with permutes: 16 LDS
+// those of the next threads beside them (rb is mlo, or tb - R for a group of fewer
+// than R qubits; four threads need rb >= 2), so a lane gathers the words of four
+// threads and turns each 4 x 4 bytes over with permutes: 16 LDS
 // reads for 64 bytes of the copy. Eight pieces of the table are in flight per
 // lane. n = 26, complex64: 36 us a copy, 56 with one piece in flight and one
 // LDS read per byte.
@@ -867,7 +868,8 @@ int run_evolve_x(int n, const uint8_t *cost, int p, const double *beta, const do
             for (int b : {x_order(G, 0), x_order(G, G - 1)}) {
                 if (cost_of[b]) continue;
                 const XGroup &gr = groups[b];
-                if (gr.mlo < 3 || (R != 3 && R != 4) || (1 << (x_copy_ntl(gr.tb, ntiles_of(gr)) + gr.tb)) > (1 << kXCopyBytesLog2))
+                if (gr.mlo < 3 || !x_copy_gathers_words(gr.plan) || (R != 3 && R != 4) ||
+                    (1 << (x_copy_ntl(gr.tb, ntiles_of(gr)) + gr.tb)) > (1 << kXCopyBytesLog2))
                     return fail(GQAOA_EINVAL, "internal: X cost copy for tb=%d, mlo=%d, R=%d", gr.tb, gr.mlo, R);
                 const int cb = (int)std::max<uint64_t>(
                     1, std::min<uint64_t>(ntiles_of(gr) >> kXCopyTilesLog2, (uint64_t)dev.num_cus * 16));

@@ -68,6 +68,10 @@ constexpr XPlan x_plan_mix0(int TB, int R) {
     }
     return pl;
 }
+// The cost copies take the costs of four neighbouring threads as one word of a
+// tile, which they are when the bits below the last chunk's window are at least two.
+constexpr bool x_copy_gathers_words(const XPlan &p) { return p.rb[p.nchunks - 1] >= 2; }
+
 // The compile-time plans: MLO >= 0 a group on tile bits [MLO, TB); kXPlanMix0
 // group 0's plan for a mixing-only pass.
 constexpr int kXPlanMix0 = 64;

@@ -99,3 +99,40 @@ def test_plans_have_teeth(driver):
         assert sorted(_covered([(8, 0b1111), (0, 0b1111)], 12, 4)) == list(range(12))
     with pytest.raises(AssertionError):
         assert sorted(_covered([(8, 0b1111), (4, 0b1111), (5, 0b0001), (0, 0b1111)], 12, 4)) == list(range(12))
+
+
+COPY_DRIVER = r"""
+#include "xplan.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char **argv) {
+    const int tb = std::atoi(argv[1]), r = std::atoi(argv[2]);
+    for (int kb = 1; kb <= 8; ++kb) {
+        const gqaoa::XPlan p = gqaoa::x_plan(tb, r, tb - kb);
+        std::printf("%d %d\n", p.rb[p.nchunks - 1], (int)gqaoa::x_copy_gathers_words(p));
+    }
+    gqaoa::XPlan low{};
+    low.nchunks = 1;
+    low.rb[0] = 1;
+    std::printf("1 %d\n", (int)gqaoa::x_copy_gathers_words(low));
+}
+"""
+
+
+@pytest.mark.parametrize("tb,r", [(13, 4), (12, 3)])
+def test_cost_copies_gather_words(tmp_path, tb, r):
+    """Every high group of 1 to 8 qubits leaves at least two tile bits below its
+    last chunk, so that the costs of four neighbouring threads are one word of the
+    copy; a window on tile bit 1 is refused."""
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    src = tmp_path / "copy.cpp"
+    src.write_text(COPY_DRIVER)
+    exe = tmp_path / "copy"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe), str(tb), str(r)], capture_output=True, text=True, check=True).stdout
+    rows = [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+    for kb, (rb, ok) in zip(range(1, 9), rows):
+        assert rb == max(tb - kb, 0) if kb > r else rb == tb - r
+        assert ok == 1 and rb >= 2
+    assert rows[-1] == (1, 0)
