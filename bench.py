@@ -728,7 +728,7 @@ def mlp_leg(torch, g):
         "training": {"ms_per_step": t_step * 1e3, "samples_per_s": b / t_step,
                      "TFLOPs": 3 * b * flops_fwd / t_step / 1e12},
         "note": "65,536 x 2e5 flops is about 5 us of MFMA work at peak and the inference moves about 100 MB; "
-                "training steps at batch 512 are launch-bound (13 launches per step)",
+                "training steps at batch 512 are launch-bound (5 launches per step)",
     }
 
 

@@ -85,7 +85,7 @@ int gqaoa_cost_table(int n, int m, const int32_t *lits_host, uint8_t *cost_dev,
  * device memory (serving loops, harnesses that forbid hipMalloc): the same
  * arguments, errors and results (cost table and histogram bit-identical), with
  * the call's scratch (clause records and per-block histogram rows) in a static
- * device array of 12 KiB + 2 MiB instead of stream-ordered allocations. Every
+ * device array of 8 KiB + 2 MiB instead of stream-ordered allocations. Every
  * valid (n, m) fits in it. Each GPU the library runs on holds its own copy
  * until the process ends. All calls on one GPU share that copy: calls that
  * overlap on one GPU (different streams without ordering, several host

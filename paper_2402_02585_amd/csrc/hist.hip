@@ -385,8 +385,9 @@ __device__ __forceinline__ void scan_mixer(const ScanArgs &a, const ScanSlot &sl
 // the compiler keeps the constants of the tables' sines in registers from item to
 // item (185 for KMAX = 20, 209 for 24, 205 for 28: two waves); held to 168 it
 // reloads what it has to once an item, never in a round. 128 instances, 360 x 181
-// pairs: n = 12..20 of density 4.6..8 8,500 -> 7,980 us, of 3..5 6,300 -> 5,800; 32
-// levels at three waves would spill in their rounds (8,900 us). The fixed rounds of
+// pairs: n = 12..20 of density 4.6..8 8,500 -> 7,980 us, of 3..5 6,300 -> 5,800, the
+// buckets one after another; 32 levels at three waves would spill in their rounds
+// (8,900 us). The fixed rounds of
 // the other kernels are too short for it: 1,024 instances of 64 x 64 pairs, 64
 // rounds within 1%, 16 rounds 413 -> 430 us.
 constexpr int scan_waves_per_simd(int kmax) { return kmax <= 12 ? 4 : kmax <= 28 ? 3 : 1; }
@@ -788,9 +789,9 @@ int run_scan(int num_inst, const int32_t *n_host, const int32_t *m_host, const u
     // The crossing form's buckets run side by side on up to four streams, the most
     // levels first: its items end anywhere between one round and their cap, so a
     // bucket ends with few waves, and one of a few instances never fills the device
-    // (128 instances in six buckets, 360 x 181 pairs: 8,050 -> 7,400 us; 23 in four,
-    // 230 x 92 pairs: 1,590 -> 815). The scan's items are equal and its buckets end
-    // full: one after another.
+    // (16 instances of 10 to 60 levels, 90 x 45 pairs, 64 rounds 980 -> 359 us; 256 of
+    // them 2,050 -> 875). The scan's items are equal and its buckets end full: one
+    // after another.
     std::vector<int> used;
     for (int bk = kNumBuckets - 1; bk >= 0; --bk)
         if (H.bucket_first[bk + 1] > H.bucket_first[bk]) used.push_back(bk);

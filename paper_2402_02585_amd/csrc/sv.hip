@@ -1634,7 +1634,7 @@ struct EvolvePlan {
     int target_host[1] = {0};
     double *stage = nullptr;  // pinned: angles [2p], then readouts [(p+1) * 3]
     bool level = false;       // the level form: its one to four launches, with the angles among their
-    LevelEvolve le{};         // arguments, are enqueued by each run (n = 10, p = 20: 43 us, as a graph 54)
+    LevelEvolve le{};         // arguments, are enqueued by each run (n = 10, p = 20: 32 us, as a graph 54)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t cap = nullptr;
