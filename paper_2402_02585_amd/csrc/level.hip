@@ -144,6 +144,7 @@ struct GivenLds {
     double var[kLevels];
     double lev[kLevels];
     double e_above, c_above;  // sums of C(z) |psi_0(z)|^2 and C(z) over the slot above m
+    bool above;               // the slot is occupied
 };
 
 struct LevelRunArgs {
@@ -402,6 +403,7 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
             sq = a.sums[4 * t + 2];
             count = (uint64_t)a.sums[4 * t + 3];
         }
+        if (t == a.m + 1) given[0].above = count != 0;  // (read behind the barriers below)
     } else if constexpr (START == kFused) {
         uint32_t *h = reinterpret_cast<uint32_t *>(smem);
         count_levels<kRunThreads>(a.cost, 1ull << a.n, 0, 1, h);
@@ -411,7 +413,7 @@ __global__ void __launch_bounds__(kRunThreads) level_run_kernel(LevelRunArgs a, 
     }
     const int pos = compact_levels(L, count, a.n, a.target);  // its barriers also end the counters' use of smem
     if constexpr (GIVEN) {
-        if (given_slots(a.m) > a.m + 1 && a.sums[4 * (a.m + 1) + 3] != 0.0) {
+        if (given[0].above) {
             // the table breaks its promise: this block reads it for the sums of the
             // levels above m, which the sums kernel has no time for (+8%)
             __shared__ double red[2 * kRunWaves];
